@@ -25,12 +25,13 @@ typedef const __attribute__((address_space(4))) uint64_t ConstU64;
 
 // Conv_{B->C}: y_i = [x_i (B/b_i)^-1]_{b_i} (Shoup; skipped when the inverse
 // NTT already produced y_i), then every output row c gets
-// [sum_i y_i [B/b_i]_c]_c, accumulated exactly in 128 bits and reduced once
-// (as the paper does): by MacSplit's four carry-free columns when the row's
-// prime is below 2^50 (its constants stored split), else by mac_cols.  `job` selects the digit (or polynomial),
-// `bz` a group of kBconvRowGroup output rows.  The source count NS is a
-// template parameter (no predicated iterations), and the constants [B/b_i]_c,
-// uniform over the workgroup, come through the scalar cache.
+// [sum_i y_i [B/b_i]_c]_c, reduced once (as the paper does): by FoldSum when
+// the row's prime is below 2^50 and the sources are at most kFoldMaxTerms,
+// else exactly in 128 bits (MacSplit's columns below 2^50, mac_cols above).
+// `job` selects the digit (or polynomial), `bz` a group of kBconvRowGroup
+// output rows.  The source count NS is a template parameter (no predicated
+// iterations), and the constant rows and the prime's constants, uniform over
+// the workgroup, come through the scalar cache.
 template <class Acc, int NS>
 __device__ __forceinline__ uint64_t conv_sum(const uint64_t (&y)[NS], ConstU64 *h, const Prime &P)
 {
@@ -38,6 +39,30 @@ __device__ __forceinline__ uint64_t conv_sum(const uint64_t (&y)[NS], ConstU64 *
 #pragma unroll
     for (int i = 0; i < NS; ++i) acc.add(y[i], h[i]);
     return reduce128(acc.total(), P);
+}
+
+template <int NS>
+__device__ __forceinline__ uint64_t conv_fold(const uint64_t (&y)[NS], ConstU64 *h, FpMod m)
+{
+    FoldSum acc = {h[kConvStart], h[kConvStart + 1]};
+#pragma unroll
+    for (int i = 0; i < NS; ++i) acc.add(y[i], h[2 * i], h[2 * i + 1]);
+    return fp_canonical(acc.residue(m), m);
+}
+
+// Constants of prime pi through the scalar cache (the rows' stores keep the
+// compiler from doing this by itself: a load per row and thread otherwise).
+__device__ __forceinline__ Prime uniform_prime(const Prime *primes, uint32_t pi)
+{
+    static_assert(sizeof(Prime) % 8 == 0, "read as 8-byte words");
+    ConstU64 *src = (ConstU64 *)(primes + pi);
+    Prime P;
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(Prime) / 8; ++i) {
+        const uint64_t w = src[i];
+        __builtin_memcpy((char *)&P + 8 * i, &w, 8);
+    }
+    return P;
 }
 
 template <int NS>
@@ -64,9 +89,13 @@ __device__ __forceinline__ void bconv_rows(const BconvArgs &a, const BconvJob &J
             continue;
         }
         const uint32_t pi = row_prime(r, a.level, a.nq);
-        ConstU64 *h = (ConstU64 *)(J.hmod + (size_t)pi * kMaxDigitPrimes);
-        const Prime &P = a.primes[pi];
-        J.dst[(size_t)r * N + n] = P.q < kSplitMaxConst ? conv_sum<MacSplit, NS>(y, h, P) : conv_sum<MacColsAcc, NS>(y, h, P);
+        ConstU64 *h = (ConstU64 *)(J.hmod + (size_t)pi * kConvRow);
+        const Prime P = uniform_prime(a.primes, pi);
+        uint64_t v;
+        if (P.q >= kFpMaxPrime) v = conv_sum<MacColsAcc, NS>(y, h, P);
+        else if constexpr (NS <= (int)kFoldMaxTerms) v = conv_fold<NS>(y, h, FpMod{(double)P.q, P.qinv});
+        else v = conv_sum<MacSplit, NS>(y, h, P);
+        J.dst[(size_t)r * N + n] = v;
     }
 }
 

@@ -179,12 +179,13 @@ extern "C" ckks_status ckks_ctx_create(uint32_t log_n, const uint64_t *q, uint32
     }
     // base-conversion sets: every digit j of every possible size, then P
     ctx->nsets = dnum * alpha + 1;
-    const size_t hm_stride = (size_t)np_all * kMaxDigitPrimes;
+    const size_t hm_stride = (size_t)np_all * kConvRow;
     std::vector<ulonglong2> bc_hinv((size_t)ctx->nsets * kMaxDigitPrimes);
     std::vector<uint64_t> bc_hmod((size_t)ctx->nsets * hm_stride, 0);
     std::vector<ulonglong2> bc_ys((size_t)ctx->nsets * kMaxDigitPrimes);
     std::vector<double> bc_ysd((size_t)ctx->nsets * kMaxDigitPrimes, 0.0);
-    auto build_set = [&](uint32_t set, const uint64_t *src, uint32_t ns) {
+    // shifted: the inputs are the centred y_i plus b_i (ModDown), so the sum is ns [B]_c too large
+    auto build_set = [&](uint32_t set, const uint64_t *src, uint32_t ns, bool shifted) {
         for (uint32_t i = 0; i < ns; ++i) {
             uint64_t prod = 1;
             for (uint32_t k = 0; k < ns; ++k)
@@ -194,22 +195,16 @@ extern "C" ckks_status ckks_ctx_create(uint32_t log_n, const uint64_t *q, uint32
             uint64_t ys = mul_mod(hinv, inv_mod(N % src[i], src[i]), src[i]);
             bc_ys[(size_t)set * kMaxDigitPrimes + i] = pair(ys, src[i]);
             bc_ysd[(size_t)set * kMaxDigitPrimes + i] = (double)ys;
-            for (uint32_t c = 0; c < np_all; ++c) {
-                uint64_t v = 1;
-                for (uint32_t k = 0; k < ns; ++k)
-                    if (k != i) v = mul_mod(v, src[k] % primes[c], primes[c]);
-                // targets below 2^50 keep the constant split for the conversions' MacSplit sums
-                bc_hmod[(size_t)set * hm_stride + (size_t)c * kMaxDigitPrimes + i] =
-                    primes[c] < kSplitMaxConst ? split_const(v) : v;
-            }
         }
+        for (uint32_t c = 0; c < np_all; ++c)
+            conv_row(&bc_hmod[(size_t)set * hm_stride + (size_t)c * kConvRow], src, ns, primes[c], shifted);
     };
     for (uint32_t j = 0; j < dnum; ++j)
         for (uint32_t s = 1; s <= alpha; ++s) {
             uint32_t lo = j * alpha;
-            if (lo + s <= n_q) build_set(ctx->set_index(j, s), &primes[lo], s);
+            if (lo + s <= n_q) build_set(ctx->set_index(j, s), &primes[lo], s, false);
         }
-    build_set(ctx->pset_index(), &primes[n_q], n_p);
+    build_set(ctx->pset_index(), &primes[n_q], n_p, true);
     std::vector<ulonglong2> pinv(np_all);
     std::vector<uint64_t> pmod(np_all, 0);
     for (uint32_t i = 0; i < np_all; ++i) {

@@ -8,11 +8,11 @@
 #include <vector>
 
 #include "../../include/ckks.h"
+#include "conv_row.h"
 #include "modarith.h"
 
 namespace ckks {
 
-constexpr int kMaxDigitPrimes = 16;  // primes per digit / in the special basis
 constexpr int kMaxDigits = 16;
 constexpr int kMaxPrimes = 64;
 constexpr uint32_t kAllPrimes = 0xFFFFFFFFu;
@@ -93,17 +93,13 @@ struct NttArgs {
     uint32_t alpha, nlev, nprimes, pset;
     const ulonglong2 *ys;       // [nsets][kMaxDigitPrimes] Shoup pairs
     const double *ysd;          // the same constants as doubles
-    // PRO_BCONV: the first forward pass computes its input as a fast base conversion of scaled
-    // rows (written by an inverse with ys_mode 1 or 2).  bc_mode 1: ModUp, polynomial j of the
-    // launch is digit j and its source rows are bc_src rows j alpha ..; bc_mode 2: ModDown,
-    // polynomial t reads the K rows at bc_src + t bc_poly_stride.
+    // PRO_BCONV (ModDown): the first forward pass computes its input as the fast base conversion
+    // from the special basis of the scaled rows of an inverse with ys_mode 2: polynomial t reads
+    // the K rows at bc_src + t bc_poly_stride.  They are centred and shifted by p_k (inv_store);
+    // the constant rows take the shift out again.
     const uint64_t *bc_src;
     int64_t bc_poly_stride;
-    uint32_t bc_mode;
-    const uint64_t *hmod;       // [nsets][n_primes][kMaxDigitPrimes]
-    // bc_mode 2 converts with centred inputs y_k in [-(p_k-1)/2, (p_k-1)/2]: every y_k above
-    // (p_k-1)/2 subtracts [P]_q once, read from pmod[prime]
-    const uint64_t *pmod;
+    const uint64_t *hmod;       // [nsets][n_primes][kConvRow]
     // Grid launches at N = 2^16 place the limbs on the 64-bit integer path (primes of 2^50 and
     // above, about 2.4 times the work of an FP64 limb) apart from the others; see grid_unit.
     uint64_t int_primes;        // bit i: prime i is on the integer path
@@ -263,7 +259,7 @@ struct BconvJob {
     uint64_t *dst;              // output rows at dst + r N
     const uint64_t *copy_src;   // rows [lo, hi) copied from here to dst (may be null)
     const ulonglong2 *hinv;     // ns pairs {[(B/b_i)^-1]_{b_i}, shoup}
-    const uint64_t *hmod;       // [n_primes][kMaxDigitPrimes]: [B/b_i]_c (split_const form for c < 2^50)
+    const uint64_t *hmod;       // [n_primes][kConvRow]
     uint32_t ns;
     uint32_t src_prime0;
     uint32_t lo, hi;            // output rows not converted
@@ -436,7 +432,7 @@ struct ckks_ctx {
     double *d_twd_inv = nullptr;
     // base-conversion sets: digit sets indexed (j * alpha + size - 1), then the P set
     ulonglong2 *d_bc_hinv = nullptr;    // [nsets][kMaxDigitPrimes]
-    uint64_t *d_bc_hmod = nullptr;      // [nsets][n_primes][kMaxDigitPrimes], split_const form for c < 2^50
+    uint64_t *d_bc_hmod = nullptr;      // [nsets][n_primes][kConvRow]
     ulonglong2 *d_bc_ys = nullptr;      // [nsets][kMaxDigitPrimes]: N^-1 [(B/b_i)^-1]_{b_i}
     double *d_bc_ysd = nullptr;         // the same as doubles (primes below 2^50)
     ulonglong2 *d_pinv = nullptr;       // [n_primes] P^-1 mod q_i

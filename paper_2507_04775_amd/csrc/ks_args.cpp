@@ -74,7 +74,7 @@ BconvArgs args_modup_bconv(const ckks_ctx *c, const uint64_t *d, uint32_t g, uin
     KsSizes s = ks_sizes(c, level);
     BconvArgs b;
     memset(&b, 0, sizeof(b));
-    const size_t hm_stride = (size_t)(c->nq + c->np) * kMaxDigitPrimes;
+    const size_t hm_stride = (size_t)(c->nq + c->np) * kConvRow;
     for (uint32_t j = 0; j < s.beta; ++j) {
         uint32_t lo = j * c->alpha, hi = lo + c->alpha < s.n ? lo + c->alpha : s.n;
         uint32_t set = c->set_index(j, hi - lo);
@@ -179,13 +179,11 @@ NttArgs args_moddown_ntt(const ckks_ctx *c, const uint64_t *acc, int64_t acc_str
     a.map.src_poly_stride = a.map.dst_poly_stride = nN;
     a.galois = g;
     a.cst = c->d_pinv;
-    a.bc_mode = 2;
     a.bc_src = pc;
     a.bc_poly_stride = kN;
     a.pset = c->pset_index();
     a.nprimes = c->nq + c->np;
     a.hmod = c->d_bc_hmod;
-    a.pmod = c->d_pmod;
     for (uint32_t t = 0; t < npoly; ++t) {
         a.aux[t] = acc + t * acc_stride;
         a.add[t] = add ? add[t] : nullptr;

@@ -230,6 +230,63 @@ __host__ __device__ __forceinline__ uint64_t fp_canonical(double x, FpMod m)
     r = r < 0.0 ? r + m.q : r;
     return (uint64_t)r;
 }
+
+// ------------------------------------ base conversion into primes below 2^50
+// Sum of y_i h_i modulo q < 2^50 for at most kFoldMaxTerms inputs y_i < 2^62
+// and constants h_i < q, as a centred-ish FP64 representative.  An input is cut
+// at bit 32, and the weight of its upper word goes into a second constant:
+//   y h == y0 h + y1 [2^32 h]_q (mod q),  y0 < 2^32, y1 < 2^30.
+// The sum S of these products is then below 2^86 instead of 2^116, and with
+// both constants split at bit 25 it needs two 64-bit columns (S = 2^25 a + b),
+// each below 2^61 over 12 terms: four multiply-adds a term, no carries.  The
+// column a starts at -floor(Smax / 2^26), Smax the largest possible sum (the
+// host computes it from the constants), and b at the residue that makes up for
+// it, so that |S| < 2^85 and S / 2^32 is an exact double.  One quotient
+// estimate then leaves S mod q: k = rint(S / q) < 2^37 is within 1/2 + 2^-14 of
+// S / q, and S - k q is exact (every partial result is an integer below 2^53):
+// fourteen instructions, where forming 128 bits, folding them with two 64-bit
+// Shoup products and converting to double takes about seventy.
+constexpr uint32_t kFoldMaxTerms = 12;
+constexpr int kFoldShift = 25;
+
+// h < 2^50 split at bit 25: the upper half in the upper word
+__host__ __device__ __forceinline__ uint64_t fold_const(uint64_t h)
+{
+    return ((h >> kFoldShift) << 32) | (h & ((1ull << kFoldShift) - 1));
+}
+
+struct FoldSum {
+    uint64_t a, b;  // a is signed
+
+    // y < 2^62; c0 = fold_const(h), c1 = fold_const([2^32 h]_q)
+    __host__ __device__ __forceinline__ void add(uint64_t y, uint64_t c0, uint64_t c1)
+    {
+        const uint32_t y0 = (uint32_t)y, y1 = (uint32_t)(y >> 32);
+        const uint32_t b0 = (uint32_t)c0, a0 = (uint32_t)(c0 >> 32);
+        const uint32_t b1 = (uint32_t)c1, a1 = (uint32_t)(c1 >> 32);
+#if defined(__HIP_DEVICE_COMPILE__)
+        uint64_t k;
+        asm("v_mad_u64_u32 %[a], %[k], %[y0], %[a0], %[a]\n\t"
+            "v_mad_u64_u32 %[b], %[k], %[y0], %[b0], %[b]\n\t"
+            "v_mad_u64_u32 %[a], %[k], %[y1], %[a1], %[a]\n\t"
+            "v_mad_u64_u32 %[b], %[k], %[y1], %[b1], %[b]"
+            : [a] "+v"(a), [b] "+v"(b), [k] "=&s"(k)
+            : [y0] "v"(y0), [y1] "v"(y1), [a0] "s"(a0), [b0] "s"(b0), [a1] "s"(a1), [b1] "s"(b1));
+#else
+        a = mad32(y1, a1, mad32(y0, a0, a));
+        b = mad32(y1, b1, mad32(y0, b0, b));
+#endif
+    }
+    // |result| <= (1/2 + 2^-14) q + 2^32
+    __host__ __device__ __forceinline__ double residue(FpMod m) const
+    {
+        const uint64_t lo = b + (a << kFoldShift);
+        const int32_t hi = (int32_t)((int64_t)a >> (64 - kFoldShift)) + (lo < b ? 1 : 0);
+        const double s = fma((double)hi, 0x1p64, (double)(uint32_t)(lo >> 32) * 0x1p32);
+        const double k = rint(s * m.qinv);
+        return fma(-k, m.q, s) + (double)(uint32_t)lo;
+    }
+};
 __host__ __device__ __forceinline__ uint64_t submod(uint64_t a, uint64_t b, uint64_t q) { return a >= b ? a - b : a + q - b; }
 
 }  // namespace ckks

@@ -153,7 +153,7 @@ struct FpArith {
 // (ys_mode 2) each canonical y of the special limb p is stored as y + p when
 // y <= (p - 1)/2, else as y: the centred representative plus p, in
 // [(p + 1)/2, 3 (p - 1)/2], below 2^62, so the conversion's sums take no
-// per-term comparison (bconv_load removes the shift).
+// per-term comparison (their constant rows remove the shift).
 template <int NV, class A, class Idx>
 __device__ __forceinline__ void inv_store(uint64_t *dst, const typename A::V (&v)[NV], const A &ar, uint32_t ys_mode,
                                           Idx idx)
@@ -430,125 +430,99 @@ __device__ __forceinline__ FpArith inv_fp_arith(const NttArgs &a, const LimbPos 
 // Source of a base conversion computed in the first forward pass (PRO_BCONV).
 struct BcSrc {
     const uint64_t *y;   // ns scaled source rows, stride N
-    const uint64_t *hm;  // [B/b_i] mod the target prime, i < ns
+    const uint64_t *hm;  // the target prime's constant row (kConvRow)
     uint32_t ns;
-    const Prime *src;    // centred conversion (ModDown, inputs shifted by p_k): the source primes, else null
-    uint64_t bq;         // [B]_q of the target prime (centred conversion)
 };
 
-__device__ __forceinline__ BcSrc bc_source(const NttArgs &a, uint32_t poly, uint32_t prime, size_t N)
+__device__ __forceinline__ BcSrc bc_source(const NttArgs &a, uint32_t poly, uint32_t prime)
 {
     BcSrc b;
-    uint32_t set;
-    if (a.bc_mode == 1) {
-        const uint32_t lo = poly * a.alpha;
-        b.ns = min(a.alpha, a.nlev - lo);
-        set = poly * a.alpha + b.ns - 1;
-        b.y = a.bc_src + (size_t)lo * N;
-        b.src = nullptr;
-        b.bq = 0;
-    } else {
-        b.ns = a.nprimes - a.map.nq;
-        set = a.pset;
-        b.y = a.bc_src + (int64_t)poly * a.bc_poly_stride;
-        b.src = a.primes + a.map.nq;
-        b.bq = a.pmod[prime];
-    }
-    b.hm = a.hmod + ((size_t)set * a.nprimes + prime) * kMaxDigitPrimes;
+    b.ns = a.nprimes - a.map.nq;
+    b.y = a.bc_src + (int64_t)poly * a.bc_poly_stride;
+    b.hm = a.hmod + ((size_t)a.pset * a.nprimes + prime) * kConvRow;
     return b;
 }
 
-// v[i] = Conv(y)[pos(i)]: sum_k y_k[pos] [B/b_k]_q accumulated exactly, reduced
-// once.  Acc sums by 32-bit columns: MacSplit (four multiply-adds per term)
-// when the target prime, and so every constant, is below 2^50 (the table holds
-// those constants split), else MacCols
-// (four multiply-adds and three carry additions; the constants in scalar
-// registers either way).  Groups of four elements keep the column sums in few
-// registers.  The loads of source row k+1 are issued before the products of
-// row k, so the latency of the source rows overlaps the arithmetic.  For
-// ModDown's centred conversion the inverse NTT stored u_k = y_k + p_k with
-// y_k centred: sum_k p_k [P/p_k]_q = K [P]_q (mod q), which `corr` removes
-// after the reduction.
-template <class Acc, int NV, class A, class Pos>
-__device__ __forceinline__ void bconv_sum(typename A::V (&v)[NV], const A &ar, const BcSrc &b, const Prime &P,
-                                          size_t N, Pos pos, uint64_t corr)
-{
-    constexpr int G = 4;
-    static_assert(NV % G == 0, "groups of four elements");
-#pragma unroll
-    for (int grp = 0; grp < NV / G; ++grp) {
-        Acc acc[G];
-        uint64_t cur[G];
-#pragma unroll
-        for (int i = 0; i < G; ++i) cur[i] = b.y[pos(G * grp + i)];
-        for (uint32_t k = 0; k < b.ns; ++k) {
-            const bool more = k + 1 < b.ns;
-            uint64_t nxt[G];
-            if (more) {
-                const uint64_t *yn = b.y + (size_t)(k + 1) * N;
-#pragma unroll
-                for (int i = 0; i < G; ++i) nxt[i] = yn[pos(G * grp + i)];
-            }
-            const uint64_t h = ((const __attribute__((address_space(4))) uint64_t *)b.hm)[k];  // scalar cache
-#pragma unroll
-            for (int i = 0; i < G; ++i) acc[i].add(cur[i], h);
-            if (more) {
-#pragma unroll
-                for (int i = 0; i < G; ++i) cur[i] = nxt[i];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < G; ++i) v[G * grp + i] = ar.from_u64(submod(reduce128(acc[i].total(), P), corr, P.q));
-    }
-}
+typedef const __attribute__((address_space(4))) uint64_t ConvWord;  // constants through the scalar cache
 
-// The same for at most kConvBatch source rows: every load of a group is
-// issued before its first product, one wait per group instead of one per row.
+// Accumulator of one converted element: the sum of its terms, then its value
+// in the limb's arithmetic.  FoldAcc: targets below 2^50 with at most
+// kFoldMaxTerms source rows (four multiply-adds a term, fourteen instructions
+// for the residue, which is the FP64 element itself).  WideAcc: exact 128-bit
+// sums reduced once, by MacSplit's carry-free columns below 2^50 (more source
+// rows than FoldSum's columns hold) and by MacCols (carries counted) above.
+struct FoldAcc {
+    FoldSum s;
+    __device__ __forceinline__ void start(ConvWord *h) { s.a = h[kConvStart], s.b = h[kConvStart + 1]; }
+    __device__ __forceinline__ void add(uint64_t y, ConvWord *h, uint32_t k) { s.add(y, h[2 * k], h[2 * k + 1]); }
+    __device__ __forceinline__ double value(const FpArith &ar, ConvWord *, const Prime &) const { return s.residue(ar.m); }
+};
+template <class Acc>
+struct WideAcc {
+    Acc s;
+    __device__ __forceinline__ void start(ConvWord *) {}
+    __device__ __forceinline__ void add(uint64_t y, ConvWord *h, uint32_t k) { s.add(y, h[k]); }
+    template <class A>
+    __device__ __forceinline__ typename A::V value(const A &ar, ConvWord *h, const Prime &P) const
+    {
+        return ar.from_u64(addmod(reduce128(s.total(), P), h[kConvStart + 1], P.q));
+    }
+};
+
+// v[i] = Conv(y)[pos(i)]: sum_k y_k[pos] [B/b_k]_q, reduced once.  Groups of
+// four elements keep the column sums in few registers; a group's loads are
+// issued four source rows at a time, before the first of their products, so a
+// group waits once for every four rows.
 constexpr uint32_t kConvBatch = 4;
 
 template <class Acc, int NV, class A, class Pos>
-__device__ __forceinline__ void bconv_sum_few(typename A::V (&v)[NV], const A &ar, const BcSrc &b, const Prime &P,
-                                              size_t N, Pos pos, uint64_t corr)
+__device__ __forceinline__ void bconv_acc(typename A::V (&v)[NV], const A &ar, const BcSrc &b, const Prime &P,
+                                          size_t N, Pos pos)
 {
     constexpr int G = 4;
     static_assert(NV % G == 0, "groups of four elements");
+    ConvWord *h = (ConvWord *)b.hm;
 #pragma unroll
     for (int grp = 0; grp < NV / G; ++grp) {
-        uint64_t y[kConvBatch][G];
-#pragma unroll
-        for (uint32_t k = 0; k < kConvBatch; ++k)
-            if (k < b.ns) {
-#pragma unroll
-                for (int i = 0; i < G; ++i) y[k][i] = b.y[(size_t)k * N + pos(G * grp + i)];
-            }
         Acc acc[G];
 #pragma unroll
-        for (uint32_t k = 0; k < kConvBatch; ++k)
-            if (k < b.ns) {
-                const uint64_t h = ((const __attribute__((address_space(4))) uint64_t *)b.hm)[k];  // scalar cache
+        for (int i = 0; i < G; ++i) acc[i].start(h);
+        for (uint32_t k0 = 0; k0 < b.ns; k0 += kConvBatch) {
+            uint64_t y[kConvBatch][G];
 #pragma unroll
-                for (int i = 0; i < G; ++i) acc[i].add(y[k][i], h);
-            }
+            for (uint32_t t = 0; t < kConvBatch; ++t)
+                if (k0 + t < b.ns) {
+                    const uint64_t *row = b.y + (size_t)(k0 + t) * N;
 #pragma unroll
-        for (int i = 0; i < G; ++i) v[G * grp + i] = ar.from_u64(submod(reduce128(acc[i].total(), P), corr, P.q));
+                    for (int i = 0; i < G; ++i) y[t][i] = row[pos(G * grp + i)];
+                }
+#pragma unroll
+            for (uint32_t t = 0; t < kConvBatch; ++t)
+                if (k0 + t < b.ns) {
+#pragma unroll
+                    for (int i = 0; i < G; ++i) acc[i].add(y[t][i], h, k0 + t);
+                }
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i) v[G * grp + i] = acc[i].value(ar, h, P);
     }
 }
 
-template <int NV, class A, class Pos>
-__device__ __forceinline__ void bconv_load(typename A::V (&v)[NV], const A &ar, const BcSrc &b, const Prime &P,
+template <int NV, class Pos>
+__device__ __forceinline__ void bconv_load(double (&v)[NV], const FpArith &ar, const BcSrc &b, const Prime &P,
                                            size_t N, Pos pos)
 {
-    const uint64_t corr = b.src ? reduce128(mul_wide((uint64_t)b.ns, b.bq), P) : 0;
-    if (b.ns <= kConvBatch) {
-        if (P.q < kSplitMaxConst)
-            bconv_sum_few<MacSplit>(v, ar, b, P, N, pos, corr);
-        else
-            bconv_sum_few<MacColsAcc>(v, ar, b, P, N, pos, corr);
-    } else if (P.q < kSplitMaxConst) {
-        bconv_sum<MacSplit>(v, ar, b, P, N, pos, corr);
-    } else {
-        bconv_sum<MacColsAcc>(v, ar, b, P, N, pos, corr);
-    }
+    if (b.ns <= kFoldMaxTerms)
+        bconv_acc<FoldAcc>(v, ar, b, P, N, pos);
+    else
+        bconv_acc<WideAcc<MacSplit>>(v, ar, b, P, N, pos);
+}
+
+template <int NV, class Pos>
+__device__ __forceinline__ void bconv_load(uint64_t (&v)[NV], const IntArith &ar, const BcSrc &b, const Prime &P,
+                                           size_t N, Pos pos)
+{
+    bconv_acc<WideAcc<MacColsAcc>>(v, ar, b, P, N, pos);
 }
 
 // ------------------------------------------------------------------ N = 2^16
@@ -619,7 +593,7 @@ __device__ __forceinline__ void fwd_col_body(const NttArgs &a, const LimbPos &lp
     typename A::W wa[7], wb[7], wc[6];
     typename A::V v[8];
     if (PRO == PRO_BCONV) {  // the twiddles after the conversion: not live across its loop
-        bconv_load(v, ar, bc_source(a, lp.poly, lp.prime, 65536), P, 65536,
+        bconv_load(v, ar, bc_source(a, lp.poly, lp.prime), P, 65536,
                    [&](int i) { return pos_wide(s, i) * 256 + c; });
         tw_fwd<3, 256, 32>(wa, s, ar, 1);
     } else {
@@ -1006,7 +980,7 @@ __device__ __forceinline__ void fwd12_body(const NttArgs &a, const LimbPos &lp, 
     const uint64_t *src = a.src + (int64_t)lp.poly * a.map.src_poly_stride + (size_t)lp.row * 4096;
     typename A::V v[16];
     if (PRO == PRO_BCONV) {
-        bconv_load(v, ar, bc_source(a, lp.poly, lp.prime, 4096), P, 4096, [&](int i) { return t + 256 * i; });
+        bconv_load(v, ar, bc_source(a, lp.poly, lp.prime), P, 4096, [&](int i) { return t + 256 * i; });
     } else {
 #pragma unroll
         for (int i = 0; i < 16; ++i) v[i] = ar.from_u64(load_fwd<PRO>(a, lp, src, t + 256 * i, P));
@@ -1139,6 +1113,7 @@ constexpr int kLds12 = 4352;
 // (run_work_queue_uniform).  Those at N = 2^12 keep it in LDS: with 16
 // elements per thread they already need close to the scalar register file,
 // and a scalar copy would spill to scratch.
+#define QATTR(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 4 : 1)))
 #define NTT_KERNELS(NAME, LDS, THREADS, UNIFORM, GRID_ATTR, ...)                                \
     __global__ __launch_bounds__(THREADS) GRID_ATTR void k_##NAME(NttArgs a)                     \
     {                                                                                             \
@@ -1146,7 +1121,7 @@ constexpr int kLds12 = 4352;
         const UnitId u = grid_unit(a);                                                            \
         __VA_ARGS__(a, u.limb, u.tile, lds, threadIdx.x);                                         \
     }                                                                                             \
-    __global__ __launch_bounds__(THREADS) void q_##NAME(const NttArgs *insts, WorkQueue q)        \
+    __global__ __launch_bounds__(THREADS) QATTR(THREADS) void q_##NAME(const NttArgs *insts, WorkQueue q)        \
     {                                                                                             \
         __shared__ uint64_t lds[LDS];                                                             \
         __shared__ uint32_t claim;                                                                \
