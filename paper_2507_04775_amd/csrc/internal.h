@@ -103,7 +103,7 @@ struct NttArgs {
     // Grid launches at N = 2^16 place the limbs on the 64-bit integer path (primes of 2^50 and
     // above, about 2.4 times the work of an FP64 limb) apart from the others; see grid_unit.
     uint64_t int_primes;        // bit i: prime i is on the integer path
-    uint32_t n_heavy, heavy_pad;
+    uint32_t n_heavy, by_tile;  // by_tile: workgroups in plain (tile, limb) order
     uint8_t heavy[kMaxHeavy];   // launch limbs on the integer path, ascending (n_heavy of them)
     // PRO_TENSOR (first inverse pass): the input row is [src * src2]_q, HMult's d2 = a1 b1
     const uint64_t *src2;
