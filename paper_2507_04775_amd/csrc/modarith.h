@@ -161,6 +161,45 @@ __host__ __device__ __forceinline__ uint64_t shoup(uint64_t x, uint64_t w, uint6
     return csub(shoup_lazy(x, w, ws, q), q);
 }
 
+// a 2^SH + b modulo 2^64, SH <= 4: one v_lshl_add_u64
+template <int SH>
+__host__ __device__ __forceinline__ uint64_t shl_add(uint64_t a, uint64_t b)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint64_t r;
+    asm("v_lshl_add_u64 %0, %1, %3, %2" : "=v"(r) : "v"(a), "v"(b), "n"(SH));
+    return r;
+#else
+    return (a << SH) + b;
+#endif
+}
+
+// x - m if x >= m, else x, for |x - m| < 2^63 (nm = 2^64 - m): an add, a sign
+// test and the selects
+__host__ __device__ __forceinline__ uint64_t csub_sign(uint64_t x, uint64_t nm)
+{
+    const uint64_t t = shl_add<0>(x, nm);
+    return (int64_t)t < 0 ? x : t;
+}
+
+// Shoup with a quotient from the three upper partial products: floor(y ws /
+// 2^64) less at most 2 (the low product and two low halves are dropped, below
+// 3 in all), so acc + y w - k q lies in acc + [0, 4q), for any 64-bit y and ws =
+// floor(w 2^64 / q).  Sums wrap modulo 2^64; nq = 2^64 - q.  13 instructions
+// where shoup_lazy's exact quotient and separate sum take about 20.
+__host__ __device__ __forceinline__ uint64_t shoup_add(uint64_t acc, uint64_t y, uint64_t w, uint64_t ws, uint64_t nq)
+{
+    const uint32_t y0 = (uint32_t)y, y1 = (uint32_t)(y >> 32);
+    const uint32_t s0 = (uint32_t)ws, s1 = (uint32_t)(ws >> 32);
+    const uint64_t cross = (uint64_t)(uint32_t)(((uint64_t)y1 * s0) >> 32) + (uint32_t)(((uint64_t)y0 * s1) >> 32);
+    const uint64_t k = mad32(y1, s1, cross);
+    const uint32_t k0 = (uint32_t)k, k1 = (uint32_t)(k >> 32);
+    const uint64_t lo = mad32(k0, (uint32_t)nq, mad32(y0, (uint32_t)w, acc));
+    const uint32_t hi = (uint32_t)(lo >> 32) + y0 * (uint32_t)(w >> 32) + y1 * (uint32_t)w + k0 * (uint32_t)(nq >> 32) +
+                        k1 * (uint32_t)nq;
+    return ((uint64_t)hi << 32) | (uint32_t)lo;
+}
+
 // Per-prime constants needed by the reductions.
 struct Prime {
     uint64_t q;

@@ -25,8 +25,8 @@
 //   keeps |x| <= q/2 + 1, after which four forward stages stay below 5.3 q
 //   (7.1 q when a round starts from canonical input) and four inverse stages,
 //   with the sums of the third stage re-centred, below 4 q; all < 2^53.
-// - other primes (up to 2^61): 64-bit integers with Shoup twiddles and
-//   Harvey's lazy butterflies ([0, 4q) forward, [0, 2q) inverse).
+// - other primes (up to 2^61): 64-bit integers with Shoup twiddles and lazy
+//   butterflies after Harvey ([0, 8q) forward, [0, 4q) inverse).
 // Outputs of every transform are canonical.
 #include <atomic>
 
@@ -49,7 +49,7 @@ struct IntArith {
     typedef uint64_t V;
     typedef ulonglong2 W;
     const ulonglong2 *T;
-    uint64_t q, q2, fc, fc_s;  // fc: constant of the last inverse multiplication
+    uint64_t q, q4, nq, fc, fc_s;  // 4q, 2^64 - q; fc: constant of the last inverse multiplication
 
     __device__ __forceinline__ V from_u64(uint64_t x) const { return x; }
     __device__ __forceinline__ V from_bits(uint64_t x) const { return x; }
@@ -64,34 +64,30 @@ struct IntArith {
     }
     template <int NV>
     __device__ __forceinline__ void reduce_all(V (&)[NV]) const {}
-    // Harvey forward butterfly: x, y in [0, 4q) -> [0, 4q)
+    // Butterflies after Harvey, with shoup_add's products in [0, 4q): forward x, y in [0, 8q) ->
+    // [0, 8q) (x brought below 4q, x + t formed by the product's own multiply-adds), inverse x, y in
+    // [0, 4q) -> [0, 4q).  8q fits a word (q < 2^61).
     __device__ __forceinline__ void ct(V &x, V &y, W w) const
     {
-        uint64_t a = x >= q2 ? x - q2 : x;
-        uint64_t t = shoup_lazy(y, w.x, w.y, q);
-        x = a + t;
-        y = a - t + q2;
+        const uint64_t a = csub_sign(x, 4 * nq);
+        x = shoup_add(a, y, w.x, w.y, nq);
+        y = shl_add<1>(a, q4) - x;
     }
-    // Harvey inverse butterfly: x, y in [0, 2q) -> [0, 2q)
     __device__ __forceinline__ void gs(V &x, V &y, W w, int) const
     {
-        uint64_t s = x + y;
-        s = s >= q2 ? s - q2 : s;
-        uint64_t d = x - y + q2;
-        x = s;
-        y = shoup_lazy(d, w.x, w.y, q);
+        const uint64_t d = x + q4 - y;
+        x = csub_sign(x + y, 4 * nq);
+        y = shoup_add(0, d, w.x, w.y, nq);
     }
-    __device__ __forceinline__ uint64_t fwd_final(V x) const { return csub(csub(x, q2), q); }
-    __device__ __forceinline__ uint64_t inv_final(V x) const { return shoup(x, fc, fc_s, q); }
-    __device__ __forceinline__ uint64_t modulus() const { return q; }
-    // key inner product on canonical values
-    __device__ __forceinline__ V mac_in(V x) const { return fwd_final(x); }
-    __device__ __forceinline__ V own(uint64_t x) const { return x; }
-    __device__ __forceinline__ void mac(V &acc, V v, uint64_t k, const Prime &P) const
+    __device__ __forceinline__ uint64_t fwd_final(V x) const
     {
-        acc = addmod(acc, mulmod(v, k, P), q);
+        return csub_sign(csub_sign(csub_sign(x, 4 * nq), 2 * nq), nq);
     }
-    __device__ __forceinline__ uint64_t acc_final(V acc) const { return acc; }
+    __device__ __forceinline__ uint64_t inv_final(V x) const
+    {
+        return csub_sign(csub_sign(shoup_add(0, x, fc, fc_s, nq), 2 * nq), nq);
+    }
+    __device__ __forceinline__ uint64_t modulus() const { return q; }
 };
 
 // ----------------------------------------------------------- FP64 path
@@ -139,14 +135,6 @@ struct FpArith {
     __device__ __forceinline__ uint64_t fwd_final(V x) const { return fp_canonical(x, m); }
     __device__ __forceinline__ uint64_t inv_final(V x) const { return fp_canonical(fp_mulmod(x, fc, m), m); }
     __device__ __forceinline__ uint64_t modulus() const { return (uint64_t)m.q; }
-    // key inner product: |v| < 5.3 q from a forward round, the running sum re-centred each step
-    __device__ __forceinline__ V mac_in(V x) const { return x; }
-    __device__ __forceinline__ V own(uint64_t x) const { return (double)x; }
-    __device__ __forceinline__ void mac(V &acc, V v, uint64_t k, const Prime &) const
-    {
-        acc = fp_reduce(acc + fp_mulmod(v, (double)k, m), m);
-    }
-    __device__ __forceinline__ uint64_t acc_final(V acc) const { return fp_canonical(acc, m); }
 };
 
 // Stores the last inverse pass's outputs.  For ModDown's centred conversion
@@ -371,7 +359,8 @@ __device__ __forceinline__ IntArith int_arith(const ulonglong2 *tw, const Prime 
     IntArith r;
     r.T = tw + (size_t)prime * N;
     r.q = P.q;
-    r.q2 = P.two_q;
+    r.q4 = 2 * P.two_q;
+    r.nq = 0 - P.q;
     r.fc = P.ninv;
     r.fc_s = P.ninv_s;
     return r;
