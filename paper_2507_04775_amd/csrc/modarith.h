@@ -262,12 +262,25 @@ __host__ __device__ __forceinline__ double fp_reduce(double x, FpMod m)
     return fma(-k, m.q, x);
 }
 
+// Exact integers below 2^52 between words and doubles through the mantissa of
+// 2^52 + x: an or and an add, an add and a mask, where the conversions of
+// 64-bit integers take four and six instructions.
+__host__ __device__ __forceinline__ double fp_from_word(uint64_t x)
+{
+    return __builtin_bit_cast(double, x | 0x4330000000000000ull) - 0x1p52;
+}
+
+__host__ __device__ __forceinline__ uint64_t fp_to_word(double r)
+{
+    return __builtin_bit_cast(uint64_t, r + 0x1p52) & 0x000FFFFFFFFFFFFFull;
+}
+
 // canonical residue in [0, q) of an exact integer |x| < 2^53
 __host__ __device__ __forceinline__ uint64_t fp_canonical(double x, FpMod m)
 {
     double r = fp_reduce(x, m);
     r = r < 0.0 ? r + m.q : r;
-    return (uint64_t)r;
+    return fp_to_word(r);
 }
 
 // ------------------------------------ base conversion into primes below 2^50

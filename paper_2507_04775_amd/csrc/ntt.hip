@@ -43,6 +43,13 @@ constexpr int kThreads = 256;
 __device__ __forceinline__ uint32_t pad(uint32_t x) { return x + (x >> 4); }
 
 
+// SwitchModulo of the rescale: u in [0, q_l) lifted centred and reduced mod q
+__device__ __forceinline__ uint64_t switch_modulo(uint64_t u, uint64_t half, uint64_t qlmod, const Prime &P)
+{
+    uint64_t um = csub(u - mul_hi(u, P.one_s) * P.q, P.q);
+    return u <= half ? um : submod(um, qlmod, P.q);
+}
+
 // ----------------------------------------------------------- integer path
 
 struct IntArith {
@@ -88,6 +95,18 @@ struct IntArith {
         return csub_sign(csub_sign(shoup_add(0, x, fc, fc_s, nq), 2 * nq), nq);
     }
     __device__ __forceinline__ uint64_t modulus() const { return q; }
+    // c (aux - x) + add for a forward output x and canonical aux, add: P^-1 (acc - Conv) + add of
+    // ModDown, q_l^-1 (c - .) of Rescale
+    __device__ __forceinline__ uint64_t scaled_difference(V x, uint64_t aux, uint64_t add, ulonglong2 c) const
+    {
+        const uint64_t r = shoup_add(add, aux + q - fwd_final(x), c.x, c.y, nq);  // below 5q
+        return csub_sign(csub_sign(csub_sign(r, 4 * nq), 2 * nq), nq);
+    }
+    // SwitchModulo of the rescale: u in [0, q_l) lifted centred and reduced
+    __device__ __forceinline__ V lift(uint64_t u, uint64_t ql, uint64_t qlmod, const Prime &P) const
+    {
+        return switch_modulo(u, (ql - 1) >> 1, qlmod, P);
+    }
 };
 
 // ----------------------------------------------------------- FP64 path
@@ -99,7 +118,7 @@ struct FpArith {
     FpMod m;
     double fc;  // constant of the last inverse multiplication
 
-    __device__ __forceinline__ V from_u64(uint64_t x) const { return (double)x; }
+    __device__ __forceinline__ V from_u64(uint64_t x) const { return fp_from_word(x); }
     __device__ __forceinline__ V from_bits(uint64_t x) const { return __longlong_as_double((long long)x); }
     __device__ __forceinline__ uint64_t to_bits(V x) const { return (uint64_t)__double_as_longlong(x); }
     __device__ __forceinline__ W tw(uint32_t i) const { return T[i]; }
@@ -110,7 +129,7 @@ struct FpArith {
     // [x y]_q of two canonical residues below 2^50, a centred representative
     __device__ __forceinline__ V product(uint64_t x, uint64_t y, const Prime &) const
     {
-        return fp_mulmod((double)x, (double)y, m);
+        return fp_mulmod(fp_from_word(x), fp_from_word(y), m);
     }
     template <int NV>
     __device__ __forceinline__ void reduce_all(V (&v)[NV]) const
@@ -135,6 +154,19 @@ struct FpArith {
     __device__ __forceinline__ uint64_t fwd_final(V x) const { return fp_canonical(x, m); }
     __device__ __forceinline__ uint64_t inv_final(V x) const { return fp_canonical(fp_mulmod(x, fc, m), m); }
     __device__ __forceinline__ uint64_t modulus() const { return (uint64_t)m.q; }
+    // as IntArith's; |x| < 5.3 q leaves the difference below 2^53 and the product below 2.9 q
+    __device__ __forceinline__ uint64_t scaled_difference(V x, uint64_t aux, uint64_t add, ulonglong2 c) const
+    {
+        return fp_canonical(fp_mulmod(fp_from_word(aux) - x, (double)c.x, m) + fp_from_word(add), m);
+    }
+    __device__ __forceinline__ V lift(uint64_t u, uint64_t ql, uint64_t qlmod, const Prime &P) const
+    {
+        if (ql < kFpMaxPrime) {  // the centred lift itself, below 2^49
+            const double d = fp_from_word(u), l = (double)ql;
+            return d > 0.5 * l ? d - l : d;
+        }
+        return from_u64(switch_modulo(u, (ql - 1) >> 1, qlmod, P));
+    }
 };
 
 // Stores the last inverse pass's outputs.  For ModDown's centred conversion
@@ -319,38 +351,33 @@ __host__ __device__ __forceinline__ LimbPos limb_pos(const LimbMap &m, uint32_t 
     return p;
 }
 
-// SwitchModulo of the rescale: u in [0, q_l) lifted centred and reduced mod q
-__device__ __forceinline__ uint64_t switch_modulo(uint64_t u, uint64_t half, uint64_t qlmod, const Prime &P)
+template <int PRO, class A>
+__device__ __forceinline__ typename A::V load_fwd(const NttArgs &a, const LimbPos &lp, const A &ar, const uint64_t *src,
+                                                  uint32_t e, const Prime &P)
 {
-    uint64_t um = csub(u - mul_hi(u, P.one_s) * P.q, P.q);
-    return u <= half ? um : submod(um, qlmod, P.q);
+    if (PRO == PRO_RESCALE) return ar.lift(pick(a.rs_src, lp.poly)[e], a.rs_ql, a.rs_qlmod[lp.prime], P);
+    return ar.from_u64(src[e]);
 }
 
-template <int PRO>
-__device__ __forceinline__ uint64_t load_fwd(const NttArgs &a, const LimbPos &lp, const uint64_t *src, uint32_t e,
-                                             const Prime &P)
+// What a forward pass leaves for its store: the canonical residue, or the value
+// itself where an epilogue goes on with it.
+template <int EPI, class A>
+__device__ __forceinline__ uint64_t fwd_out(const A &ar, typename A::V v)
 {
-    if (PRO == PRO_RESCALE) {
-        return switch_modulo(pick(a.rs_src, lp.poly)[e], (a.rs_ql - 1) >> 1, a.rs_qlmod[lp.prime], P);
-    } else {
-        return src[e];
-    }
+    return EPI == EPI_PLAIN ? ar.fwd_final(v) : ar.to_bits(v);
 }
 
-// Final forward value x (canonical) at element e of the limb; `addv` is the
+// Final forward value (fwd_out's x) at element e of the limb; `addv` is the
 // addend of the ModDown epilogue (already gathered, 0 without addend).
-template <int EPI>
-__device__ __forceinline__ void store_fwd(const NttArgs &a, const LimbPos &lp, uint64_t *dst, uint32_t e, uint64_t x,
-                                          uint64_t addv, uint64_t auxv, const Prime &P, size_t N)
+template <int EPI, class A>
+__device__ __forceinline__ void store_fwd(const NttArgs &a, const LimbPos &lp, const A &ar, uint64_t *dst, uint32_t e,
+                                          uint64_t x, uint64_t addv, uint64_t auxv, size_t N)
 {
     if (EPI == EPI_PLAIN) {
         dst[e] = x;
     } else {
-        const size_t off = (size_t)lp.row * N;
-        const ulonglong2 c = a.cst[lp.prime];
-        uint64_t r = shoup(submod(auxv, x, P.q), c.x, c.y, P.q);
-        if (EPI == EPI_MODDOWN) r = addmod(r, addv, P.q);
-        pick(a.out, lp.poly)[off + e] = r;
+        pick(a.out, lp.poly)[(size_t)lp.row * N + e] =
+            ar.scaled_difference(ar.from_bits(x), auxv, EPI == EPI_MODDOWN ? addv : 0, a.cst[lp.prime]);
     }
 }
 
@@ -588,7 +615,7 @@ __device__ __forceinline__ void fwd_col_body(const NttArgs &a, const LimbPos &lp
     } else {
         tw_fwd<3, 256, 32>(wa, s, ar, 1);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = ar.from_u64(load_fwd<PRO>(a, lp, src, pos_wide(s, i) * 256 + c, P));
+        for (int i = 0; i < 8; ++i) v[i] = load_fwd<PRO>(a, lp, ar, src, pos_wide(s, i) * 256 + c, P);
     }
     fwd_rw<3>(v, wa, ar);
     tw_fwd<3, 256, 4>(wb, pos_mid(s, 0), ar, 1);  // in flight across the exchange
@@ -679,7 +706,7 @@ __device__ __forceinline__ void fwd_row_body(const NttArgs &a, const LimbPos &lp
     fwd_rw<2>(v, wc, ar);
     fwd_rw<2>(v + 4, wc + 3, ar);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) L[row_slot(pos_narrow(s, i))] = ar.fwd_final(v[i]);
+    for (int i = 0; i < 8; ++i) L[row_slot(pos_narrow(s, i))] = fwd_out<EPI>(ar, v[i]);
     wave_sync();
     uint64_t x[8];
 #pragma unroll
@@ -695,7 +722,7 @@ __device__ __forceinline__ void fwd_row_body(const NttArgs &a, const LimbPos &lp
     uint64_t *dst = a.dst + (int64_t)lp.poly * a.map.dst_poly_stride + (size_t)lp.row * 65536;
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-        store_fwd<EPI>(a, lp, dst, b * 256 + pos_wide(s, i), x[i], addv[i], auxv[i], P, 65536);
+        store_fwd<EPI>(a, lp, ar, dst, b * 256 + pos_wide(s, i), x[i], addv[i], auxv[i], 65536);
 }
 
 template <int EPI, int TW = 16>
@@ -972,7 +999,7 @@ __device__ __forceinline__ void fwd12_body(const NttArgs &a, const LimbPos &lp, 
         bconv_load(v, ar, bc_source(a, lp.poly, lp.prime), P, 4096, [&](int i) { return t + 256 * i; });
     } else {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = ar.from_u64(load_fwd<PRO>(a, lp, src, t + 256 * i, P));
+        for (int i = 0; i < 16; ++i) v[i] = load_fwd<PRO>(a, lp, ar, src, t + 256 * i, P);
     }
     fwd16<4096, 256>(v, t, ar, 1);
 #pragma unroll
@@ -990,7 +1017,7 @@ __device__ __forceinline__ void fwd12_body(const NttArgs &a, const LimbPos &lp, 
     ar.reduce_all(v);
     fwd16<4096, 1>(v, 16 * t, ar, 1);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) lds[pad(16 * t + i)] = ar.fwd_final(v[i]);
+    for (int i = 0; i < 16; ++i) lds[pad(16 * t + i)] = fwd_out<EPI>(ar, v[i]);
     __syncthreads();
     uint64_t x[16], addv[16];
 #pragma unroll
@@ -1017,7 +1044,7 @@ __device__ __forceinline__ void fwd12_body(const NttArgs &a, const LimbPos &lp, 
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const uint64_t auxv = EPI == EPI_PLAIN ? 0 : pick(a.aux, lp.poly)[(size_t)lp.row * 4096 + t + 256 * i];
-        store_fwd<EPI>(a, lp, dst, t + 256 * i, x[i], addv[i], auxv, P, 4096);
+        store_fwd<EPI>(a, lp, ar, dst, t + 256 * i, x[i], addv[i], auxv, 4096);
     }
 }
 
