@@ -455,7 +455,11 @@ ckks_status plan_batch(ckks_ctx *ctx, const ckks_work *items, uint32_t n, char *
         b->q[qi].pass = spec[qi].pass;
         b->q[qi].set = spec[qi].set;
         b->q[qi].tiles = spec[qi].k == Q_NTT ? nt : ctx->N / (256 * kQueueBlocks);
-        b->q[qi].grid_mult = 2;
+        // persistent workgroups per CU: two of the 512-thread passes are resident at once; the
+        // 256-thread inner product and conversion stream rows, and want as many waves as their
+        // registers allow (measured on batches of 4, 12 and 32 items: the inner product at 6 instead
+        // of 2 takes 9, 8 and 6 % off the whole batch, higher is no faster)
+        b->q[qi].grid_mult = qi == QI_IP ? 6 : qi == QI_UP_BCONV ? 4 : 2;
     }
     char *w = ws;
     uint32_t max_rows = 0;

@@ -28,8 +28,8 @@ typedef const __attribute__((address_space(4))) uint64_t ConstU64;
 // [sum_i y_i [B/b_i]_c]_c, reduced once (as the paper does): by FoldSum when
 // the row's prime is below 2^50 and the sources are at most kFoldMaxTerms,
 // else exactly in 128 bits (MacSplit's columns below 2^50, mac_cols above).
-// `job` selects the digit (or polynomial), `bz` a group of kBconvRowGroup
-// output rows.  The source count NS is a template parameter (no predicated
+// `J` is the digit (or polynomial), `bz` a group of kBconvRowGroup output
+// rows.  The source count NS is a template parameter (no predicated
 // iterations), and the constant rows and the prime's constants, uniform over
 // the workgroup, come through the scalar cache.
 template <class Acc, int NS>
@@ -66,7 +66,7 @@ __device__ __forceinline__ Prime uniform_prime(const Prime *primes, uint32_t pi)
 }
 
 template <int NS>
-__device__ __forceinline__ void bconv_rows(const BconvArgs &a, const BconvJob &J, uint32_t n, uint32_t r0,
+__device__ __forceinline__ void bconv_rows(const BconvCommon &a, const BconvJob &J, uint32_t n, uint32_t r0,
                                            uint32_t r1)
 {
     const uint32_t N = a.N;
@@ -99,9 +99,9 @@ __device__ __forceinline__ void bconv_rows(const BconvArgs &a, const BconvJob &J
     }
 }
 
-__device__ __forceinline__ void bconv_unit(const BconvArgs &a, uint32_t job, uint32_t bx, uint32_t bz, uint32_t tid)
+__device__ __forceinline__ void bconv_unit(const BconvCommon &a, const BconvJob &J, uint32_t bx, uint32_t bz,
+                                           uint32_t tid)
 {
-    const BconvJob &J = a.job[job];
     const uint32_t n = bx * kCoefThreads + tid;
     const uint32_t r0 = bz * kBconvRowGroup;
     if (r0 >= a.nrows) return;

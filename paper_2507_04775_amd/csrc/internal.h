@@ -124,73 +124,6 @@ struct WorkQueue {
     uint32_t *counter;
 };
 
-// Persistent work-queue loop shared by every stage kernel: units are claimed
-// from q.counter (the next claim is issued while the current unit runs), the
-// unit's argument block is copied into LDS (`sa`) whenever the instance
-// changes, and body(sa, limb, tile) processes the unit with the whole block.
-template <class Args, class Body>
-__device__ __forceinline__ void run_work_queue(const Args *insts, const WorkQueue &q, Args &sa, uint32_t *claim,
-                                               Body body)
-{
-    static_assert(sizeof(Args) % 8 == 0, "argument blocks are copied as 8-byte words");
-    const uint32_t total = q.nrecs * q.tiles;
-    if (threadIdx.x == 0) *claim = atomicAdd(q.counter, 1u);
-    __syncthreads();
-    uint32_t u = *claim;
-    uint32_t have = 0xFFFFFFFFu;
-    while (u < total) {
-        const UnitRec rec = q.recs[u / q.tiles];
-        __syncthreads();  // every thread has read *claim and is done with sa and the unit's LDS
-        if (threadIdx.x == 0) *claim = atomicAdd(q.counter, 1u);
-        if (rec.inst != have) {
-            const uint64_t *src = (const uint64_t *)(insts + rec.inst);
-            uint64_t *dst = (uint64_t *)&sa;
-            for (uint32_t i = threadIdx.x; i < sizeof(Args) / 8; i += blockDim.x) dst[i] = src[i];
-            have = rec.inst;
-        }
-        __syncthreads();
-        body(sa, rec.limb, u % q.tiles);
-        __syncthreads();
-        u = *claim;
-    }
-}
-
-// The same loop for argument blocks without dynamically indexed fields (the
-// NTT passes): the claim is made wave-uniform and the unit record and the
-// argument block are read through the constant address space, so they come in
-// with scalar loads into scalar registers, as a grid kernel receives its
-// arguments.  An argument block in LDS occupies vector registers instead,
-// 8 to 14 more per thread in these passes, which put the Rescale prologue
-// pass and the first inverse pass above the 128 that two 512-thread
-// workgroups per CU allow.  Both blocks are written before the launch and
-// only read here.
-template <class Args, class Body>
-__device__ __forceinline__ void run_work_queue_uniform(const Args *insts, const WorkQueue &q, uint32_t *claim,
-                                                       Body body)
-{
-    static_assert(sizeof(Args) % 4 == 0, "argument blocks are read as 4-byte words");
-    typedef const __attribute__((address_space(4))) uint32_t ConstWord;
-    const uint32_t total = q.nrecs * q.tiles;
-    if (threadIdx.x == 0) *claim = atomicAdd(q.counter, 1u);
-    __syncthreads();
-    uint32_t u = __builtin_amdgcn_readfirstlane(*claim);
-    while (u < total) {
-        const uint32_t ri = __builtin_amdgcn_readfirstlane(u / q.tiles);
-        ConstWord *rec = (ConstWord *)((uintptr_t)q.recs + (uintptr_t)ri * sizeof(UnitRec));
-        const uint32_t inst = __builtin_amdgcn_readfirstlane(rec[0]);  // UnitRec::inst
-        const uint32_t limb = __builtin_amdgcn_readfirstlane(rec[1]);  // UnitRec::limb
-        __syncthreads();  // every thread has read *claim and is done with the unit's LDS
-        if (threadIdx.x == 0) *claim = atomicAdd(q.counter, 1u);
-        Args a;
-        ConstWord *src = (ConstWord *)((uintptr_t)insts + (uintptr_t)inst * sizeof(Args));
-#pragma unroll
-        for (uint32_t i = 0; i < sizeof(Args) / 4; ++i) ((uint32_t *)&a)[i] = src[i];
-        body(a, limb, u - ri * q.tiles);
-        __syncthreads();
-        u = __builtin_amdgcn_readfirstlane(*claim);
-    }
-}
-
 // The steps of a batch of key switches, in the order of their dependencies
 // (one persistent launch each, or one unit kind each of the one-launch batch
 // kernel).
@@ -218,9 +151,6 @@ enum BatchStep {
 // for, and claimed in that order, so the wait of the earliest unfinished unit
 // is always satisfied and the launch cannot deadlock.
 constexpr uint32_t kNoGroup = 0xFFFFFFFFu;
-struct BconvArgs;
-struct IpArgs;
-struct TensorArgs;
 struct FusedUnit {
     uint32_t inst;
     uint32_t code;              // limb | tile << 16 | step << 28
@@ -229,6 +159,9 @@ struct FusedUnit {
 };
 static_assert(sizeof(FusedUnit) == 16, "a fused unit is four words");
 
+struct BconvArgs;
+struct IpArgs;
+struct TensorArgs;
 struct FusedArgs {
     const FusedUnit *units;
     const uint32_t *target;     // per group: its number of units
@@ -265,14 +198,20 @@ struct BconvJob {
     uint32_t lo, hi;            // output rows not converted
 };
 
-struct BconvArgs {
-    BconvJob job[kMaxDigits];
+// What the jobs of one conversion share.
+struct BconvCommon {
     const Prime *primes;
     uint32_t nrows;             // output rows 0..nrows-1
     uint32_t level, nq;         // row -> prime map as in LimbMap
     uint32_t N, logn;
     uint32_t copy_galois;       // copied rows are gathered through X -> X^g (1 = plain copy)
     uint32_t prescaled;         // sources already hold y_i (the iNTT folded the scaling in)
+    uint32_t pad;
+};
+
+struct BconvArgs {
+    BconvJob job[kMaxDigits];
+    BconvCommon c;
 };
 
 constexpr uint32_t kBconvRowGroup = 8;  // output rows per workgroup (grid z splits the rows)
@@ -332,6 +271,112 @@ struct TensorArgs {
     const Prime *primes;
     uint32_t logn, pad;
 };
+
+// A pointer read from an argument block in memory, known to point to global
+// memory: without this its accesses are flat ones, which wait on the LDS
+// counter as well and serialise with the passes' exchanges.
+template <class T>
+__device__ __forceinline__ void global_ptr(T *&p)
+{
+    p = (T *)(__attribute__((address_space(1))) T *)(uintptr_t)p;
+}
+__device__ __forceinline__ void global_ptrs(NttArgs &a)
+{
+    global_ptr(a.dst), global_ptr(a.src), global_ptr(a.mid), global_ptr(a.primes), global_ptr(a.tw), global_ptr(a.twd);
+    global_ptr(a.aux[0]), global_ptr(a.aux[1]), global_ptr(a.add[0]), global_ptr(a.add[1]);
+    global_ptr(a.out[0]), global_ptr(a.out[1]), global_ptr(a.cst), global_ptr(a.rs_src[0]), global_ptr(a.rs_src[1]);
+    global_ptr(a.rs_qlmod), global_ptr(a.ys), global_ptr(a.ysd), global_ptr(a.bc_src), global_ptr(a.hmod), global_ptr(a.src2);
+}
+__device__ __forceinline__ void global_ptrs(IpArgs &a)
+{
+    global_ptr(a.ext), global_ptr(a.key), global_ptr(a.acc), global_ptr(a.primes), global_ptr(a.own), global_ptr(a.pmod);
+    global_ptr(a.ta0), global_ptr(a.ta1), global_ptr(a.tb0), global_ptr(a.tb1), global_ptr(a.fold_c0), global_ptr(a.fold_tot);
+}
+__device__ __forceinline__ void global_ptrs(TensorArgs &a)
+{
+    global_ptr(a.a0), global_ptr(a.a1), global_ptr(a.b0), global_ptr(a.b1);
+    global_ptr(a.d0), global_ptr(a.d1), global_ptr(a.d2), global_ptr(a.primes);
+}
+__device__ __forceinline__ void global_ptrs(BconvJob &j)
+{
+    global_ptr(j.src), global_ptr(j.dst), global_ptr(j.copy_src), global_ptr(j.hinv), global_ptr(j.hmod);
+}
+__device__ __forceinline__ void global_ptrs(BconvCommon &c) { global_ptr(c.primes); }
+
+// The whole argument block, read through the constant address space with a
+// wave-uniform address: it comes in with scalar loads into scalar registers, as
+// a grid kernel's arguments do.  A block in LDS occupies vector registers
+// instead, 8 to 14 more per thread in the NTT passes, which put the Rescale
+// prologue pass and the first inverse pass above the 128 that two 512-thread
+// workgroups per CU allow.  The blocks are written before the launch.
+template <class Args>
+__device__ __forceinline__ Args uniform_args(const Args *p)
+{
+    typedef const __attribute__((address_space(4))) uint32_t ConstWord;
+    static_assert(sizeof(Args) % 4 == 0, "argument blocks are read as 4-byte words");
+    ConstWord *src = (ConstWord *)(uintptr_t)p;
+    Args a;
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(Args) / 4; ++i) ((uint32_t *)&a)[i] = src[i];
+    global_ptrs(a);
+    return a;
+}
+
+// Persistent work-queue loop: units are claimed from q.counter (the next claim
+// is issued while the current unit runs), the unit's record is read with scalar
+// loads, and body(inst, limb, tile) processes it.
+template <class Body>
+__device__ __forceinline__ void run_work_queue_units(const WorkQueue &q, uint32_t *claim, Body body)
+{
+    typedef const __attribute__((address_space(4))) uint32_t ConstWord;
+    const uint32_t total = q.nrecs * q.tiles;
+    if (threadIdx.x == 0) *claim = atomicAdd(q.counter, 1u);
+    __syncthreads();
+    uint32_t u = __builtin_amdgcn_readfirstlane(*claim);
+    while (u < total) {
+        const uint32_t ri = __builtin_amdgcn_readfirstlane(u / q.tiles);
+        ConstWord *rec = (ConstWord *)((uintptr_t)q.recs + (uintptr_t)ri * sizeof(UnitRec));
+        const uint32_t inst = __builtin_amdgcn_readfirstlane(rec[0]);  // UnitRec::inst
+        const uint32_t limb = __builtin_amdgcn_readfirstlane(rec[1]);  // UnitRec::limb
+        __syncthreads();  // every thread has read *claim and is done with the unit's LDS
+        if (threadIdx.x == 0) *claim = atomicAdd(q.counter, 1u);
+        body(inst, limb, u - ri * q.tiles);
+        __syncthreads();
+        u = __builtin_amdgcn_readfirstlane(*claim);
+    }
+}
+
+// The same with the instance's argument block in scalar registers:
+// body(args, limb, tile).
+template <class Args, class Body>
+__device__ __forceinline__ void run_work_queue_uniform(const Args *insts, const WorkQueue &q, uint32_t *claim,
+                                                       Body body)
+{
+    run_work_queue_units(q, claim, [&](uint32_t inst, uint32_t limb, uint32_t tile) {
+        body(uniform_args(insts + inst), limb, tile);
+    });
+}
+
+// The same with the argument block copied into LDS (`sa`) whenever the instance
+// changes, for the N = 2^12 passes: their scalar registers are nearly full, and
+// a scalar copy would spill to scratch.
+template <class Args, class Body>
+__device__ __forceinline__ void run_work_queue(const Args *insts, const WorkQueue &q, Args &sa, uint32_t *claim,
+                                               Body body)
+{
+    static_assert(sizeof(Args) % 8 == 0, "argument blocks are copied as 8-byte words");
+    uint32_t have = 0xFFFFFFFFu;
+    run_work_queue_units(q, claim, [&](uint32_t inst, uint32_t limb, uint32_t tile) {
+        if (inst != have) {
+            const uint64_t *src = (const uint64_t *)(insts + inst);
+            uint64_t *dst = (uint64_t *)&sa;
+            for (uint32_t i = threadIdx.x; i < sizeof(Args) / 8; i += blockDim.x) dst[i] = src[i];
+            have = inst;
+        }
+        __syncthreads();
+        body(sa, limb, tile);
+    });
+}
 
 // Linear combinations of ciphertexts with plaintexts (the baby-step sums of
 // the bootstrap's linear transforms): for each output o < nout (1 or 2),

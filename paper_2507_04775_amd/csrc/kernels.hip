@@ -16,18 +16,19 @@ using namespace coef;
 
 __global__ __launch_bounds__(kThreads) void k_bconv(BconvArgs a)
 {
-    bconv_unit(a, blockIdx.y, blockIdx.x, blockIdx.z, threadIdx.x);
+    bconv_unit(a.c, a.job[blockIdx.y], blockIdx.x, blockIdx.z, threadIdx.x);
 }
 
 // persistent: tile t of record (inst, job) covers kQueueBlocks coefficient blocks
 // ((t % (N / (256 kQueueBlocks))) kQueueBlocks ..) of row group t / (N / (256 kQueueBlocks))
 __global__ __launch_bounds__(kThreads) void q_bconv(const BconvArgs *insts, WorkQueue q)
 {
-    __shared__ BconvArgs sa;
     __shared__ uint32_t claim;
-    run_work_queue(insts, q, sa, &claim, [&](const BconvArgs &a, uint32_t job, uint32_t t) {
+    run_work_queue_units(q, &claim, [&](uint32_t inst, uint32_t job, uint32_t t) {
+        const BconvCommon a = uniform_args(&insts[inst].c);
+        const BconvJob J = uniform_args(&insts[inst].job[job]);
         const uint32_t nb = a.N / (kThreads * kQueueBlocks);
-        for (uint32_t i = 0; i < kQueueBlocks; ++i) bconv_unit(a, job, (t % nb) * kQueueBlocks + i, t / nb, threadIdx.x);
+        for (uint32_t i = 0; i < kQueueBlocks; ++i) bconv_unit(a, J, (t % nb) * kQueueBlocks + i, t / nb, threadIdx.x);
     });
 }
 
@@ -45,9 +46,8 @@ __global__ __launch_bounds__(kThreads) void k_inner_product_tensor(IpArgs a)
 __global__ __launch_bounds__(kThreads) void q_inner_product(const IpArgs *insts, WorkQueue q)
 {
     __shared__ uint64_t stage[kIpStage * kThreads];
-    __shared__ IpArgs sa;
     __shared__ uint32_t claim;
-    run_work_queue(insts, q, sa, &claim, [&](const IpArgs &a, uint32_t row, uint32_t t) {
+    run_work_queue_uniform(insts, q, &claim, [&](const IpArgs &a, uint32_t row, uint32_t t) {
         ip_blocks(a, row, t * kQueueBlocks, kQueueBlocks, stage, threadIdx.x);
     });
 }
@@ -56,9 +56,8 @@ __global__ __launch_bounds__(kThreads) void k_tensor(TensorArgs a) { tensor_unit
 
 __global__ __launch_bounds__(kThreads) void q_tensor(const TensorArgs *insts, WorkQueue q)
 {
-    __shared__ TensorArgs sa;
     __shared__ uint32_t claim;
-    run_work_queue(insts, q, sa, &claim, [&](const TensorArgs &a, uint32_t limb, uint32_t t) {
+    run_work_queue_uniform(insts, q, &claim, [&](const TensorArgs &a, uint32_t limb, uint32_t t) {
         for (uint32_t i = 0; i < kQueueBlocks; ++i) tensor_unit(a, limb, t * kQueueBlocks + i, threadIdx.x);
     });
 }
@@ -283,7 +282,7 @@ hipError_t launch_half_monomial(uint64_t *out, uint32_t nlimbs, uint32_t logn, h
 hipError_t launch_bconv(const BconvArgs &a, uint32_t njobs, hipStream_t stream)
 {
     if (njobs == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bconv, dim3(a.N / kThreads, njobs, (a.nrows + kBconvRowGroup - 1) / kBconvRowGroup),
+    hipLaunchKernelGGL(k_bconv, dim3(a.c.N / kThreads, njobs, (a.c.nrows + kBconvRowGroup - 1) / kBconvRowGroup),
                        dim3(kThreads), 0, stream, a);
     return hipGetLastError();
 }

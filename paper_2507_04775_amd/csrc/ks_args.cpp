@@ -89,14 +89,14 @@ BconvArgs args_modup_bconv(const ckks_ctx *c, const uint64_t *d, uint32_t g, uin
         J.lo = lo;
         J.hi = hi;
     }
-    b.primes = c->d_primes;
-    b.nrows = s.rows;
-    b.level = level;
-    b.nq = c->nq;
-    b.N = c->N;
-    b.logn = c->logn;
-    b.copy_galois = g;
-    b.prescaled = 1;
+    b.c.primes = c->d_primes;
+    b.c.nrows = s.rows;
+    b.c.level = level;
+    b.c.nq = c->nq;
+    b.c.N = c->N;
+    b.c.logn = c->logn;
+    b.c.copy_galois = g;
+    b.c.prescaled = 1;
     return b;
 }
 

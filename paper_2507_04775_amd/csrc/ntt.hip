@@ -1262,7 +1262,6 @@ constexpr int kFusedLds = kLds16 > (int)kFusedIpStage ? kLds16 : (int)kFusedIpSt
 static_assert(kQueueBlocks % 2 == 0, "the two halves take half of a unit's blocks each");
 
 __shared__ uint64_t g_fused_lds[kFusedLds];
-__shared__ BconvArgs g_fused_bc;
 
 // Completions a workgroup has not yet published: up to f.publish_every
 // (at most kFusedPending) groups with their unit counts, kept by thread 0.
@@ -1328,18 +1327,6 @@ __device__ __forceinline__ void fused_wait(const FusedArgs &f, Pending &p, uint3
     p.seen_next = (p.seen_next + 1) % kFusedSeen;
 }
 
-template <class Args>
-__device__ __forceinline__ Args uniform_args(const Args *base, uint32_t inst)
-{
-    typedef const __attribute__((address_space(4))) uint32_t ConstWord;
-    static_assert(sizeof(Args) % 4 == 0, "argument blocks are read as 4-byte words");
-    ConstWord *src = (ConstWord *)((uintptr_t)base + (uintptr_t)inst * sizeof(Args));
-    Args a;
-#pragma unroll
-    for (uint32_t i = 0; i < sizeof(Args) / 4; ++i) ((uint32_t *)&a)[i] = src[i];
-    return a;
-}
-
 // The argument block of the unit's step: the pointer passes through an empty
 // asm statement, so that the scalar loads of one step's block are not
 // hoisted above the switch (speculated for every step, the blocks of all
@@ -1349,7 +1336,7 @@ __device__ __forceinline__ Args step_args(const Args *base, uint32_t inst)
 {
     uint64_t p = (uint64_t)(uintptr_t)base;
     asm volatile("" : "+s"(p));
-    return uniform_args((const Args *)(uintptr_t)p, inst);
+    return uniform_args((const Args *)(uintptr_t)p + inst);
 }
 
 __global__ __launch_bounds__(kThreads16) __attribute__((amdgpu_waves_per_eu(4))) void q_fused16(FusedArgs f)
@@ -1365,7 +1352,6 @@ __global__ __launch_bounds__(kThreads16) __attribute__((amdgpu_waves_per_eu(4)))
     }
     __syncthreads();
     uint32_t u = __builtin_amdgcn_readfirstlane(claim);
-    uint32_t have_bc = 0xFFFFFFFFu;
     while (u < f.nunits) {
         ConstWord *w = (ConstWord *)((uintptr_t)f.units + (uintptr_t)u * sizeof(FusedUnit));
         const uint32_t inst = __builtin_amdgcn_readfirstlane(w[0]);
@@ -1393,16 +1379,11 @@ __global__ __launch_bounds__(kThreads16) __attribute__((amdgpu_waves_per_eu(4)))
         case QI_UP_INTT0_GALOIS: inv_row_unit<PRO_GALOIS>(step_args(f.ntt[0], inst), limb, tile, g_fused_lds, tx); break;
         case QI_UP_INTT1: inv_col_unit(step_args(f.ntt[0], inst), limb, tile, g_fused_lds, tx); break;
         case QI_UP_BCONV: {
-            if (inst != have_bc) {  // its job fields are indexed per thread: the block goes through LDS
-                const uint64_t *src = (const uint64_t *)(f.bconv + inst);
-                uint64_t *dst = (uint64_t *)&g_fused_bc;
-                for (uint32_t i = threadIdx.x; i < sizeof(BconvArgs) / 8; i += blockDim.x) dst[i] = src[i];
-                have_bc = inst;
-                __syncthreads();
-            }
-            const uint32_t nb = g_fused_bc.N / (coef::kCoefThreads * kQueueBlocks);
+            const BconvCommon c = uniform_args(&f.bconv[inst].c);
+            const BconvJob J = uniform_args(&f.bconv[inst].job[limb]);
+            const uint32_t nb = c.N / (coef::kCoefThreads * kQueueBlocks);
             for (uint32_t i = tx / coef::kCoefThreads; i < kQueueBlocks; i += 2)
-                coef::bconv_unit(g_fused_bc, limb, (tile % nb) * kQueueBlocks + i, tile / nb, tx % coef::kCoefThreads);
+                coef::bconv_unit(c, J, (tile % nb) * kQueueBlocks + i, tile / nb, tx % coef::kCoefThreads);
             break;
         }
         case QI_UP_NTT0: fwd_col_unit<PRO_PLAIN>(step_args(f.ntt[1], inst), limb, tile, g_fused_lds, tx); break;
