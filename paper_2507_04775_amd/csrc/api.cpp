@@ -66,6 +66,29 @@ hipError_t modup_from_coeffs(const ckks_ctx *c, const uint64_t *d, uint32_t g, u
     return launch_ntt_stage(STAGE_FWD_PLAIN, a, s.beta * s.rows - s.n, st);
 }
 
+// ModUp of phi_g(d) (of a1 b1 with tin) into ext, the digits' own rows left out.  finish: false leaves
+// the last forward pass to the inner product (N = 2^12, where the transforms run in their two passes
+// and the conversion inside the column launch).
+hipError_t modup(const ckks_ctx *c, const uint64_t *d, uint32_t g, uint32_t level, const KsWs &w, const TensorIn *tin,
+                 bool finish, hipStream_t st)
+{
+    const KsSizes s = ks_sizes(c, level);
+    NttArgs ia = args_modup_intt(c, tin ? tin->a1 : d, g, level, w.dc);
+    if (tin) ia.src2 = tin->b1;
+    const NttStage first = tin ? STAGE_INV_TENSOR : g == 1 ? STAGE_INV_PLAIN : STAGE_INV_GALOIS;
+    if (c->logn != 12) {
+        hipError_t e = launch_ntt_stage(first, ia, s.n, st);
+        return e == hipSuccess ? modup_from_coeffs(c, d, g, level, w.dc, w.ext, false, st) : e;
+    }
+    hipError_t e = launch_split12_inv_rows(first, ia, s.n, st);
+    if (e == hipSuccess)
+        e = launch_split12_cols(COLS_MODUP, args_cols(c, level, w.dc, 0, w.ext, (int64_t)s.rows * s.N), s.beta, st);
+    if (e != hipSuccess || !finish) return e;
+    NttArgs fa = args_modup_ntt(c, level, w.ext);
+    fa.map.dense = 1;
+    return launch_split12_fwd_rows(EPI_PLAIN, fa, s.beta * s.rows - s.n, st);
+}
+
 hipError_t inner_product(const ckks_ctx *c, const uint64_t *ext, uint32_t level, const uint64_t *key, uint32_t g,
                          uint64_t *acc, hipStream_t st, const uint64_t *own = nullptr, uint32_t own_galois = 1)
 {
@@ -78,17 +101,37 @@ hipError_t inner_product(const ckks_ctx *c, const uint64_t *ext, uint32_t level,
 // conversion inputs y_k = [a_k (P/p_k)^-1] (N^-1 folded into the same
 // constant); the forward NTT computes the conversion in its first pass and the
 // P^-1 (x - .) + add sequence in its last (III-F.5 ModDown fusion).
-// row_done: the inner product already ran the INTT's first pass (launch_inner_product_rowpass).
+// row_done: the inner product already ran the INTT's first pass.
 hipError_t moddown(const ckks_ctx *c, const uint64_t *acc, int64_t acc_stride, uint32_t npoly, uint32_t level,
                    uint64_t *const *out, const uint64_t *const *add, uint32_t g, uint64_t *pc, uint64_t *conv,
                    hipStream_t st, bool row_done = false)
 {
     KsSizes s = ks_sizes(c, level);
-    hipError_t e = launch_ntt_stage(STAGE_INV_PLAIN, args_moddown_intt(c, acc, acc_stride, level, pc), npoly * c->np, st,
-                                    row_done ? 1 : 0);
-    if (e != hipSuccess) return e;
-    return launch_ntt_stage(STAGE_FWD_BCONV_MODDOWN,
-                            args_moddown_ntt(c, acc, acc_stride, npoly, level, out, add, g, pc, conv), npoly * s.n, st);
+    const NttArgs ia = args_moddown_intt(c, acc, acc_stride, level, pc);
+    const NttArgs fa = args_moddown_ntt(c, acc, acc_stride, npoly, level, out, add, g, pc, conv);
+    hipError_t e = hipSuccess;
+    if (c->logn == 12) {
+        if (!row_done) e = launch_split12_inv_rows(STAGE_INV_PLAIN, ia, npoly * c->np, st);
+        if (e == hipSuccess)
+            e = launch_split12_cols(COLS_MODDOWN, args_cols(c, level, pc, ia.mid_stride, conv, fa.mid_stride), npoly, st);
+        return e == hipSuccess ? launch_split12_fwd_rows(EPI_MODDOWN, fa, npoly * s.n, st) : e;
+    }
+    e = launch_ntt_stage(STAGE_INV_PLAIN, ia, npoly * c->np, st, row_done ? 1 : 0);
+    return e == hipSuccess ? launch_ntt_stage(STAGE_FWD_BCONV_MODDOWN, fa, npoly * s.n, st) : e;
+}
+
+// The inner product ip, with the first pass of ModDown's INTT on the special rows in its launch, and
+// the ModDown of its two accumulators (in w) into out.  ready: ip.ext holds finished transforms (see
+// modup; always so at N = 2^16).
+hipError_t ip_moddown(const ckks_ctx *c, const IpArgs &ip, bool ready, uint32_t level, uint64_t *const *out,
+                      const uint64_t *const *add, uint32_t g, const KsWs &w, hipStream_t st)
+{
+    const KsSizes s = ks_sizes(c, level);
+    const int64_t acc_stride = (int64_t)s.rows * s.N;
+    const NttArgs ia = args_moddown_intt(c, w.acc, acc_stride, level, w.pc);
+    hipError_t e = c->logn == 12 ? launch_split12_ip(ip, ia, base_args(c, false), ready, st)
+                                 : launch_inner_product_rowpass(ip, ia, st);
+    return e == hipSuccess ? moddown(c, w.acc, acc_stride, 2, level, out, add, g, w.pc, w.conv, st, true) : e;
 }
 
 }  // namespace
@@ -98,7 +141,7 @@ namespace ckks {
 // Full key switch of d (gathered through g_in) with `key`; outputs
 // out_t = KS_t + add_t (add gathered through g_add).  The digits' own rows are
 // never copied: the inner product reads them from d directly.
-// tin (N = 2^16, d, add0, add1 null, g_in = g_add = 1): HMult's relinearisation
+// tin (d, add0, add1 null, g_in = g_add = 1): HMult's relinearisation
 // of a x b with the tensor folded in.  d2 = a1 b1 is formed by ModUp's first
 // inverse pass and by the inner product (its digit-own rows), and the inner
 // product adds [P]_q d0 and [P]_q d1 to the accumulators over q_0..q_l, so
@@ -108,18 +151,9 @@ hipError_t keyswitch_core(const ckks_ctx *c, const uint64_t *d, uint32_t g_in, u
                           uint64_t *out0, uint64_t *out1, const uint64_t *add0, const uint64_t *add1, uint32_t g_add,
                           void *ws, hipStream_t st, const TensorIn *tin)
 {
-    KsSizes s = ks_sizes(c, level);
     KsWs w = ks_ws(c, level, ws);
-    hipError_t e;
-    if (tin) {
-        if (c->logn != 16 || d || add0 || add1 || g_in != 1 || g_add != 1) return hipErrorInvalidValue;
-        NttArgs ia = args_modup_intt(c, tin->a1, 1, level, w.dc);
-        ia.src2 = tin->b1;
-        e = launch_ntt_stage(STAGE_INV_TENSOR, ia, level + 1, st);
-    } else {
-        e = modup_intt(c, d, g_in, level, w.dc, st);
-    }
-    if (e == hipSuccess) e = modup_from_coeffs(c, d, g_in, level, w.dc, w.ext, false, st);
+    if (tin && (d || add0 || add1 || g_in != 1 || g_add != 1)) return hipErrorInvalidValue;
+    hipError_t e = modup(c, d, g_in, level, w, tin, false, st);
     if (e != hipSuccess) return e;
     IpArgs ip = args_ip(c, w.ext, level, key, 1, w.acc, d, g_in);
     if (tin) {
@@ -129,15 +163,9 @@ hipError_t keyswitch_core(const ckks_ctx *c, const uint64_t *d, uint32_t g_in, u
         ip.tb0 = tin->b0;
         ip.tb1 = tin->b1;
     }
-    // at N = 2^16 the inner product also runs the first pass of ModDown's INTT on the special rows
-    const int64_t acc_stride = (int64_t)s.rows * s.N;
-    const bool rowpass = c->logn == 16;
-    e = rowpass ? launch_inner_product_rowpass(ip, args_moddown_intt(c, w.acc, acc_stride, level, w.pc), st)
-                : launch_inner_product(ip, st);
-    if (e != hipSuccess) return e;
     uint64_t *outs[2] = {out0, out1};
     const uint64_t *adds[2] = {add0, add1};
-    return moddown(c, w.acc, acc_stride, 2, level, outs, adds, g_add, w.pc, w.conv, st, rowpass);
+    return ip_moddown(c, ip, c->logn != 12, level, outs, adds, g_add, w, st);
 }
 
 }  // namespace ckks
@@ -208,8 +236,7 @@ hipError_t keyswitch_extended(ckks_ctx *c, const uint64_t *d, uint32_t g, uint32
 {
     KsWs w = ks_ws(c, level, ws);
     *acc = w.acc;
-    hipError_t e = modup_intt(c, d, g, level, w.dc, st);
-    if (e == hipSuccess) e = modup_from_coeffs(c, d, g, level, w.dc, w.ext, false, st);
+    hipError_t e = modup(c, d, g, level, w, nullptr, true, st);
     if (e == hipSuccess) e = inner_product(c, w.ext, level, key, 1, w.acc, st, d, g);
     return e;
 }
@@ -218,8 +245,7 @@ hipError_t keyswitch_extended_fold(ckks_ctx *c, const uint64_t *d, uint32_t g, u
                                    void *ws, hipStream_t st, const uint64_t *c0, uint64_t *tot, bool first)
 {
     KsWs w = ks_ws(c, level, ws);
-    hipError_t e = modup_intt(c, d, g, level, w.dc, st);
-    if (e == hipSuccess) e = modup_from_coeffs(c, d, g, level, w.dc, w.ext, false, st);
+    hipError_t e = modup(c, d, g, level, w, nullptr, true, st);
     if (e != hipSuccess) return e;
     IpArgs ip = args_ip(c, w.ext, level, key, 1, w.acc, d, g);
     ip.fold_c0 = c0;
@@ -276,8 +302,8 @@ static ckks_status ntt_common(ckks_ctx *ctx, uint64_t *poly, uint32_t limb0, uin
     a.dst = poly;
     a.map.rows = n_limbs;
     a.map.prime0 = limb0;
-    hipError_t e = inverse ? launch_ntt_inv(a, n_limbs, PRO_PLAIN, S(stream), poly, 0)
-                           : launch_ntt_fwd(a, n_limbs, PRO_PLAIN, EPI_PLAIN, S(stream), poly, 0);
+    hipError_t e = inverse ? launch_ntt_inv(a, n_limbs, S(stream), poly, 0)
+                           : launch_ntt_fwd(a, n_limbs, PRO_PLAIN, S(stream), poly, 0);
     return dev(e, inverse ? "ckks_intt" : "ckks_ntt");
 }
 
@@ -422,18 +448,11 @@ extern "C" ckks_status ckks_hmult_relin(ckks_ctx *ctx, const ckks_ct *a, const c
     const void *all[6] = {a->c0, a->c1, b->c0, b->c1, o.c0, o.c1};
     for (int i = 0; i < 6; ++i)
         if (overlap(ws, wb, all[i], pb)) return fail(CKKS_E_ARG, "ckks_hmult_relin: workspace overlaps a polynomial");
-    const size_t N = ctx->N;
-    uint64_t *d2 = (uint64_t *)ws;
-    void *ks_ws = d2 + (size_t)(level + 1) * N;
-    hipError_t e;
-    if (ctx->logn == 16) {
-        const TensorIn tin = {a->c0, a->c1, b->c0, b->c1};
-        e = keyswitch_core(ctx, nullptr, 1, level, rlk->data, o.c0, o.c1, nullptr, nullptr, 1, ks_ws, S(stream), &tin);
-    } else {
-        e = launch_tensor(a->c0, a->c1, b->c0, b->c1, o.c0, o.c1, d2, ctx->d_primes, level + 1, ctx->logn, S(stream));
-        if (e == hipSuccess)
-            e = keyswitch_core(ctx, d2, 1, level, rlk->data, o.c0, o.c1, o.c0, o.c1, 1, ks_ws, S(stream));
-    }
+    // (the workspace's first level + 1 rows are kept free: callers size it by ckks_workspace_bytes)
+    void *ks_ws = (uint64_t *)ws + (size_t)(level + 1) * ctx->N;
+    const TensorIn tin = {a->c0, a->c1, b->c0, b->c1};
+    const hipError_t e =
+        keyswitch_core(ctx, nullptr, 1, level, rlk->data, o.c0, o.c1, nullptr, nullptr, 1, ks_ws, S(stream), &tin);
     TRY(dev(e, "ckks_hmult_relin"));
     out->level = level;
     out->scale = a->scale * b->scale;
@@ -470,7 +489,13 @@ extern "C" ckks_status ckks_rescale(ckks_ctx *ctx, const ckks_ct *in, ckks_ct *o
     ia.map.prime0 = l;
     ia.map.src_poly_stride = (int64_t)(in->c1 - in->c0);
     ia.map.dst_poly_stride = (int64_t)N;
-    hipError_t e = launch_ntt_inv(ia, 2, PRO_PLAIN, S(stream), v, (int64_t)N);
+    ia.mid = v;
+    ia.mid_stride = (int64_t)N;
+    const bool split = ctx->logn == 12;  // the transforms in their two passes, the lift in the column launch
+    hipError_t e = split ? launch_split12_inv_rows(STAGE_INV_PLAIN, ia, 2, S(stream))
+                         : launch_ntt_stage(STAGE_INV_PLAIN, ia, 2, S(stream));
+    if (e == hipSuccess && split)
+        e = launch_split12_cols(COLS_RESCALE, args_cols(ctx, l, v, (int64_t)N, mid, (int64_t)l * N), 2, S(stream));
     if (e == hipSuccess) {
         NttArgs a = base_args(ctx, false);
         a.src = v;
@@ -488,7 +513,10 @@ extern "C" ckks_status ckks_rescale(ckks_ctx *ctx, const ckks_ct *in, ckks_ct *o
         a.aux[1] = in->c1;
         a.out[0] = o.c0;
         a.out[1] = o.c1;
-        e = launch_ntt_fwd(a, 2 * l, PRO_RESCALE, EPI_RESCALE, S(stream), mid, (int64_t)l * N);
+        a.mid = mid;
+        a.mid_stride = (int64_t)l * N;
+        e = split ? launch_split12_fwd_rows(EPI_RESCALE, a, 2 * l, S(stream))
+                  : launch_ntt_stage(STAGE_FWD_RESCALE, a, 2 * l, S(stream));
     }
     TRY(dev(e, "ckks_rescale"));
     out->level = l - 1;
@@ -571,20 +599,13 @@ extern "C" ckks_status ckks_hrotate_hoisted(ckks_ctx *ctx, const ckks_ct *in, ui
     }
     if (overlap(ws, wb, in->c0, pb) || overlap(ws, wb, in->c1, pb))
         return fail(CKKS_E_ARG, "ckks_hrotate_hoisted: workspace overlaps the input");
-    KsSizes s = ks_sizes(ctx, level);
     KsWs w = ks_ws(ctx, level, ws);
-    hipError_t e = modup_intt(ctx, in->c1, 1, level, w.dc, S(stream));
-    if (e == hipSuccess) e = modup_from_coeffs(ctx, in->c1, 1, level, w.dc, w.ext, false, S(stream));
-    const int64_t acc_stride = (int64_t)s.rows * s.N;
-    const bool rowpass = ctx->logn == 16;  // the inner product runs the special rows' first INTT pass
+    hipError_t e = modup(ctx, in->c1, 1, level, w, nullptr, true, S(stream));
     for (uint32_t i = 0; i < n && e == hipSuccess; ++i) {
         const IpArgs ip = args_ip(ctx, w.ext, level, keys[i]->data, gs[i], w.acc, in->c1, gs[i]);
-        e = rowpass ? launch_inner_product_rowpass(ip, args_moddown_intt(ctx, w.acc, acc_stride, level, w.pc), S(stream))
-                    : launch_inner_product(ip, S(stream));
-        if (e != hipSuccess) break;
         uint64_t *outs[2] = {out[i].c0, out[i].c1};
         const uint64_t *adds[2] = {in->c0, nullptr};
-        e = moddown(ctx, w.acc, acc_stride, 2, level, outs, adds, gs[i], w.pc, w.conv, S(stream), rowpass);
+        e = ip_moddown(ctx, ip, true, level, outs, adds, gs[i], w, S(stream));
     }
     TRY(dev(e, "ckks_hrotate_hoisted"));
     for (uint32_t i = 0; i < n; ++i) {

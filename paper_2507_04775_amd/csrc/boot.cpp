@@ -642,7 +642,7 @@ struct Runner {
         ia.map.prime0 = 0;
         ia.map.src_poly_stride = (int64_t)(in.c1 - in.c0);
         ia.map.dst_poly_stride = (int64_t)N;
-        TRY(dev(launch_ntt_inv(ia, 2, PRO_PLAIN, st, v, (int64_t)N), "ckks_bootstrap modraise"));
+        TRY(dev(launch_ntt_inv(ia, 2, st, v, (int64_t)N), "ckks_bootstrap modraise"));
         NttArgs a = base_args(c, false);
         a.src = v;
         a.dst = x.c0;
@@ -654,7 +654,7 @@ struct Runner {
         a.rs_src[1] = v + N;
         a.rs_qlmod = c->d_rs_mod;  // row 0: q_0 mod q_i
         a.rs_ql = c->primes[0];
-        return dev(launch_ntt_fwd(a, 2 * (b->L + 1), PRO_RESCALE, EPI_PLAIN, st, x.c0, (int64_t)(x.c1 - x.c0)),
+        return dev(launch_ntt_fwd(a, 2 * (b->L + 1), PRO_RESCALE, st, x.c0, (int64_t)(x.c1 - x.c0)),
                    "ckks_bootstrap modraise");
     }
 
@@ -1047,7 +1047,7 @@ static ckks_status boot_create(ckks_ctx *ctx, const ckks_boot_desc *desc, ckks_b
                 a.map.rows = g.level + 1;
                 a.map.prime0 = 0;
                 a.map.src_poly_stride = a.map.dst_poly_stride = (int64_t)(g.level + 1) * N;
-                e = launch_ntt_fwd(a, g.lay.count * (g.level + 1), PRO_PLAIN, EPI_PLAIN, 0, g.pt,
+                e = launch_ntt_fwd(a, g.lay.count * (g.level + 1), PRO_PLAIN, 0, g.pt,
                                    (int64_t)(g.level + 1) * N);
             }
             if (e == hipSuccess) e = hipStreamSynchronize(0);  // the staging buffer is reused
@@ -1063,7 +1063,7 @@ static ckks_status boot_create(ckks_ctx *ctx, const ckks_boot_desc *desc, ckks_b
         a.map.rows = L + 1;
         a.map.prime0 = 0;
         a.map.src_poly_stride = a.map.dst_poly_stride = 0;
-        e = launch_ntt_fwd(a, L + 1, PRO_PLAIN, EPI_PLAIN, 0, b->mono, 0);
+        e = launch_ntt_fwd(a, L + 1, PRO_PLAIN, 0, b->mono, 0);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(0);
     if (e != hipSuccess) return bail(CKKS_E_DEVICE, std::string("plaintext upload: ") + hipGetErrorString(e));

@@ -178,13 +178,12 @@ struct FusedArgs {
 
 enum NttStage {
     STAGE_FWD_PLAIN = 0,
-    STAGE_FWD_MODDOWN,
     STAGE_FWD_RESCALE,
     STAGE_FWD_BCONV_MODDOWN,
     STAGE_INV_PLAIN,
     STAGE_INV_GALOIS,
     STAGE_FWD_LIFT,             // centred lift of one source limb into every row, then forward NTT
-    STAGE_INV_TENSOR            // inverse NTT of the product of two polynomials (N = 2^16)
+    STAGE_INV_TENSOR            // inverse NTT of the product of two polynomials (grid launches)
 };
 
 struct BconvJob {
@@ -357,27 +356,6 @@ __device__ __forceinline__ void run_work_queue_uniform(const Args *insts, const 
     });
 }
 
-// The same with the argument block copied into LDS (`sa`) whenever the instance
-// changes, for the N = 2^12 passes: their scalar registers are nearly full, and
-// a scalar copy would spill to scratch.
-template <class Args, class Body>
-__device__ __forceinline__ void run_work_queue(const Args *insts, const WorkQueue &q, Args &sa, uint32_t *claim,
-                                               Body body)
-{
-    static_assert(sizeof(Args) % 8 == 0, "argument blocks are copied as 8-byte words");
-    uint32_t have = 0xFFFFFFFFu;
-    run_work_queue_units(q, claim, [&](uint32_t inst, uint32_t limb, uint32_t tile) {
-        if (inst != have) {
-            const uint64_t *src = (const uint64_t *)(insts + inst);
-            uint64_t *dst = (uint64_t *)&sa;
-            for (uint32_t i = threadIdx.x; i < sizeof(Args) / 8; i += blockDim.x) dst[i] = src[i];
-            have = inst;
-        }
-        __syncthreads();
-        body(sa, limb, tile);
-    });
-}
-
 // Linear combinations of ciphertexts with plaintexts (the baby-step sums of
 // the bootstrap's linear transforms): for each output o < nout (1 or 2),
 // out_t[o] = sum_b a_t[b] * pt[o][b], t = 0, 1.  Two outputs (two giant steps
@@ -413,10 +391,9 @@ uint64_t smallest_2n_root(uint64_t q, uint64_t two_n);
 uint32_t reverse_bits(uint32_t x, uint32_t bits);
 
 // Launchers (all asynchronous on `stream`).
-hipError_t launch_ntt_fwd(const NttArgs &a, uint32_t nlimbs, NttPro pro, NttEpi epi, hipStream_t stream,
-                          uint64_t *mid, int64_t mid_poly_stride);
-hipError_t launch_ntt_inv(const NttArgs &a, uint32_t nlimbs, NttPro pro, hipStream_t stream, uint64_t *mid,
+hipError_t launch_ntt_fwd(const NttArgs &a, uint32_t nlimbs, NttPro pro, hipStream_t stream, uint64_t *mid,
                           int64_t mid_poly_stride);
+hipError_t launch_ntt_inv(const NttArgs &a, uint32_t nlimbs, hipStream_t stream, uint64_t *mid, int64_t mid_poly_stride);
 uint32_t ntt_passes(uint32_t logn);
 uint32_t ntt_tiles(uint32_t logn);  // tiles per limb of the persistent passes
 // Tile width (16, 8 or 4 columns / rows per workgroup) of the N = 2^16 grid
@@ -441,9 +418,33 @@ hipError_t launch_inner_product(const IpArgs &a, hipStream_t stream);  // ta0 se
 // same accumulators), with that INTT's first pass on the special rows run by the same launch; the
 // INTT then runs with first_pass 1.  The special rows of ip.acc are not written.
 hipError_t launch_inner_product_rowpass(const IpArgs &ip, const NttArgs &ia, hipStream_t stream);
-hipError_t launch_tensor(const uint64_t *a0, const uint64_t *a1, const uint64_t *b0, const uint64_t *b1,
-                         uint64_t *d0, uint64_t *d1, uint64_t *d2, const Prime *primes, uint32_t nlimbs,
-                         uint32_t logn, hipStream_t stream);
+// ---- N = 2^12 in split transforms (64 x 64, a wave per 8 columns or rows of a limb)
+// The column launch of a conversion: job j takes its ns source rows through the second inverse pass
+// (times the conversion scale), converts them to its target rows and runs those through the first
+// forward pass.  COLS_MODUP: job j is digit j, targets every extended row but its own.  COLS_MODDOWN:
+// job t is polynomial t, sources the K special rows, targets q_0..q_l.  COLS_RESCALE: job t is
+// polynomial t, source its row q_l, targets q_0..q_{l-1} (SwitchModulo in place of a conversion).
+enum ColsMode { COLS_MODUP = 0, COLS_MODDOWN = 1, COLS_RESCALE = 2 };
+struct ColsArgs {
+    const uint64_t *src;        // output of the first inverse pass; job j's rows at src + j src_stride
+    uint64_t *dst;              // input of the last forward pass; job j's row r at dst + j dst_stride + r N
+    int64_t src_stride, dst_stride;
+    const Prime *primes;
+    const ulonglong2 *twf, *twi;
+    const double *twdf, *twdi;
+    const ulonglong2 *ys;
+    const double *ysd;
+    const uint64_t *hmod;       // [nsets][n_primes][kConvRow]
+    const uint64_t *rs_qlmod;   // COLS_RESCALE: q_l mod q_i
+    uint32_t level, nq, np, alpha, pset, pad;
+};
+hipError_t launch_split12_inv_rows(NttStage st, const NttArgs &a, uint32_t nlimbs, hipStream_t stream);
+hipError_t launch_split12_cols(ColsMode mode, const ColsArgs &a, uint32_t njobs, hipStream_t stream);
+hipError_t launch_split12_fwd_rows(NttEpi epi, const NttArgs &a, uint32_t nlimbs, hipStream_t stream);
+// The key inner product: rows q_0..q_l of both halves to ip.acc, the special rows through ModDown's
+// first inverse pass (ia: args_moddown_intt) to ia.mid.  ready: ip.ext holds finished transforms, else
+// the column launch's output, whose last forward pass runs here.
+hipError_t launch_split12_ip(const IpArgs &ip, const NttArgs &ia, const NttArgs &fa, bool ready, hipStream_t stream);
 // op: 0 add, 1 sub, 2 mul, 3 mul-add (a*b+c), 4 scalar mul (host_scalars[limb]), 5 scalar add
 hipError_t launch_elementwise(int op, const uint64_t *a, const uint64_t *b, const uint64_t *c, uint64_t *out,
                               const uint64_t *host_scalars, const Prime *primes, uint32_t nlimbs, uint32_t logn,

@@ -52,8 +52,6 @@ __global__ __launch_bounds__(kThreads) void q_inner_product(const IpArgs *insts,
     });
 }
 
-__global__ __launch_bounds__(kThreads) void k_tensor(TensorArgs a) { tensor_unit(a, blockIdx.y, blockIdx.x, threadIdx.x); }
-
 __global__ __launch_bounds__(kThreads) void q_tensor(const TensorArgs *insts, WorkQueue q)
 {
     __shared__ uint32_t claim;
@@ -296,15 +294,6 @@ hipError_t launch_inner_product(const IpArgs &a, hipStream_t stream)
     } else {
         hipLaunchKernelGGL(k_inner_product, dim3((1u << a.logn) / kThreads, a.rows), dim3(kThreads), 0, stream, a);
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_tensor(const uint64_t *a0, const uint64_t *a1, const uint64_t *b0, const uint64_t *b1, uint64_t *d0,
-                         uint64_t *d1, uint64_t *d2, const Prime *primes, uint32_t nlimbs, uint32_t logn,
-                         hipStream_t stream)
-{
-    TensorArgs a = {a0, a1, b0, b1, d0, d1, d2, primes, logn, 0};
-    hipLaunchKernelGGL(k_tensor, dim3((1u << logn) / kThreads, nlimbs), dim3(kThreads), 0, stream, a);
     return hipGetLastError();
 }
 

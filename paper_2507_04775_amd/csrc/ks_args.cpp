@@ -115,6 +115,32 @@ NttArgs args_modup_ntt(const ckks_ctx *c, uint32_t level, uint64_t *ext)
     return a;
 }
 
+ColsArgs args_cols(const ckks_ctx *c, uint32_t level, const uint64_t *src, int64_t src_stride, uint64_t *dst,
+                   int64_t dst_stride)
+{
+    ColsArgs a;
+    memset(&a, 0, sizeof(a));
+    a.src = src;
+    a.dst = dst;
+    a.src_stride = src_stride;
+    a.dst_stride = dst_stride;
+    a.primes = c->d_primes;
+    a.twf = c->d_tw_fwd;
+    a.twi = c->d_tw_inv;
+    a.twdf = c->d_twd_fwd;
+    a.twdi = c->d_twd_inv;
+    a.ys = c->d_bc_ys;
+    a.ysd = c->d_bc_ysd;
+    a.hmod = c->d_bc_hmod;
+    a.rs_qlmod = c->d_rs_mod + (size_t)level * c->nq;
+    a.level = level;
+    a.nq = c->nq;
+    a.np = c->np;
+    a.alpha = c->alpha;
+    a.pset = c->pset_index();
+    return a;
+}
+
 IpArgs args_ip(const ckks_ctx *c, const uint64_t *ext, uint32_t level, const uint64_t *key, uint32_t g,
                uint64_t *acc, const uint64_t *own, uint32_t own_galois)
 {

@@ -38,11 +38,6 @@ namespace ckks {
 
 namespace {
 
-constexpr int kThreads = 256;
-
-__device__ __forceinline__ uint32_t pad(uint32_t x) { return x + (x >> 4); }
-
-
 // SwitchModulo of the rescale: u in [0, q_l) lifted centred and reduced mod q
 __device__ __forceinline__ uint64_t switch_modulo(uint64_t u, uint64_t half, uint64_t qlmod, const Prime &P)
 {
@@ -95,9 +90,15 @@ struct IntArith {
         return csub_sign(csub_sign(shoup_add(0, x, fc, fc_s, nq), 2 * nq), nq);
     }
     __device__ __forceinline__ uint64_t modulus() const { return q; }
+    // exact sums of products with canonical residues k, reduced once (at most kMaxDigits + 2 terms)
+    typedef u128 Sum;
+    __device__ __forceinline__ void sum_start(Sum &s) const { s = {0, 0}; }
+    __device__ __forceinline__ void sum_add(Sum &s, V x, uint64_t k) const { s = add128(s, mul_wide(x, k)); }
+    __device__ __forceinline__ V sum_value(const Sum &s, const Prime &P) const { return reduce128(s, P); }
+    __device__ __forceinline__ V sum_input(V x) const { return fwd_final(x); }  // of a forward output
     // c (aux - x) + add for a forward output x and canonical aux, add: P^-1 (acc - Conv) + add of
     // ModDown, q_l^-1 (c - .) of Rescale
-    __device__ __forceinline__ uint64_t scaled_difference(V x, uint64_t aux, uint64_t add, ulonglong2 c) const
+    __device__ __forceinline__ uint64_t scaled_difference(V x, V aux, uint64_t add, ulonglong2 c) const
     {
         const uint64_t r = shoup_add(add, aux + q - fwd_final(x), c.x, c.y, nq);  // below 5q
         return csub_sign(csub_sign(csub_sign(r, 4 * nq), 2 * nq), nq);
@@ -154,10 +155,19 @@ struct FpArith {
     __device__ __forceinline__ uint64_t fwd_final(V x) const { return fp_canonical(x, m); }
     __device__ __forceinline__ uint64_t inv_final(V x) const { return fp_canonical(fp_mulmod(x, fc, m), m); }
     __device__ __forceinline__ uint64_t modulus() const { return (uint64_t)m.q; }
-    // as IntArith's; |x| < 5.3 q leaves the difference below 2^53 and the product below 2.9 q
-    __device__ __forceinline__ uint64_t scaled_difference(V x, uint64_t aux, uint64_t add, ulonglong2 c) const
+    // sums of products re-centred term by term
+    typedef double Sum;
+    __device__ __forceinline__ void sum_start(Sum &s) const { s = 0.0; }
+    __device__ __forceinline__ void sum_add(Sum &s, V x, uint64_t k) const
     {
-        return fp_canonical(fp_mulmod(fp_from_word(aux) - x, (double)c.x, m) + fp_from_word(add), m);
+        s = fp_reduce(s + fp_mulmod(x, fp_from_word(k), m), m);
+    }
+    __device__ __forceinline__ V sum_value(const Sum &s, const Prime &) const { return s; }
+    __device__ __forceinline__ V sum_input(V x) const { return x; }
+    // as IntArith's; |x| < 5.3 q, |aux| <= q leave the difference below 2^53 and the product below 2.9 q
+    __device__ __forceinline__ uint64_t scaled_difference(V x, V aux, uint64_t add, ulonglong2 c) const
+    {
+        return fp_canonical(fp_mulmod(aux - x, (double)c.x, m) + fp_from_word(add), m);
     }
     __device__ __forceinline__ V lift(uint64_t u, uint64_t ql, uint64_t qlmod, const Prime &P) const
     {
@@ -234,14 +244,6 @@ __device__ __forceinline__ void fwd_rw(typename A::V *v, const typename A::W *w,
     }
 }
 
-template <int LOG, int NS, int STRIDE, class A>
-__device__ __forceinline__ void fwd_r(typename A::V *v, uint32_t base, const A &ar, uint32_t B)
-{
-    typename A::W w[(1 << LOG) - 1];
-    tw_fwd<LOG, NS, STRIDE>(w, base, ar, B);
-    fwd_rw<LOG>(v, w, ar);
-}
-
 // LOG inverse stages: t = STRIDE, 2 STRIDE, ..., 2^(LOG-1) STRIDE.  Rounds
 // of four stages re-centre the sums of their third stage (FP64 path); three
 // stages from a centred start stay below 4 q + 8 without it.
@@ -273,26 +275,6 @@ __device__ __forceinline__ void inv_rw(typename A::V *v, const typename A::W *w,
             for (int kk = 0; kk < h; ++kk) ar.gs(v[g * 2 * h + kk], v[g * 2 * h + kk + h], ww, LOG == 4 ? st : -1);
         }
     }
-}
-
-template <int LOG, int NS, int STRIDE, class A>
-__device__ __forceinline__ void inv_r(typename A::V *v, uint32_t base, const A &ar, uint32_t B)
-{
-    typename A::W w[(1 << LOG) - 1];
-    tw_inv<LOG, NS, STRIDE>(w, base, ar, B);
-    inv_rw<LOG>(v, w, ar);
-}
-
-template <int NS, int STRIDE, class A>
-__device__ __forceinline__ void fwd16(typename A::V (&v)[16], uint32_t base, const A &ar, uint32_t B)
-{
-    fwd_r<4, NS, STRIDE>(v, base, ar, B);
-}
-
-template <int NS, int STRIDE, class A>
-__device__ __forceinline__ void inv16(typename A::V (&v)[16], uint32_t base, const A &ar, uint32_t B)
-{
-    inv_r<4, NS, STRIDE>(v, base, ar, B);
 }
 
 // The thread's index, opaque to loop-invariant code motion, for the pass
@@ -377,7 +359,7 @@ __device__ __forceinline__ void store_fwd(const NttArgs &a, const LimbPos &lp, c
         dst[e] = x;
     } else {
         pick(a.out, lp.poly)[(size_t)lp.row * N + e] =
-            ar.scaled_difference(ar.from_bits(x), auxv, EPI == EPI_MODDOWN ? addv : 0, a.cst[lp.prime]);
+            ar.scaled_difference(ar.from_bits(x), ar.from_u64(auxv), EPI == EPI_MODDOWN ? addv : 0, a.cst[lp.prime]);
     }
 }
 
@@ -987,123 +969,519 @@ __device__ __forceinline__ void inv_col4_unit(const NttArgs &a, uint32_t limb, u
 }
 
 // ------------------------------------------------------------------ N = 2^12
+// One workgroup of 512 threads per limb, 8 elements per thread, four rounds of
+// three stages in the layouts
+//   0: t + 512 i,  1: 512 (t/64) + t%64 + 64 i,  2: 64 (t/8) + t%8 + 8 i,  3: 8 t + i.
+// Layouts 1, 2 and 3 of a wave cover the same 512 elements, so only the exchange
+// with layout 0 takes a workgroup barrier; layout 3 reads and writes 64
+// consecutive bytes per thread.  A launch has as many workgroups as limbs, far
+// fewer than CUs, so a limb's own time is all that counts: two waves per SIMD
+// with four independent butterflies each, and the twiddles of a round loaded
+// before the exchange that precedes it.  (256 threads with 16 elements, one
+// wave per SIMD and three rounds with a barrier each: 9.3 us for the four limbs
+// of the small set, 7.7 us this way.)
+constexpr int kThreads12 = 512;
+constexpr int kLds12 = 4096;
+
+__device__ __forceinline__ uint32_t p12a(uint32_t t, int i) { return t + 512 * i; }
+__device__ __forceinline__ uint32_t p12b(uint32_t t, int i) { return 512 * (t >> 6) + (t & 63) + 64 * i; }
+__device__ __forceinline__ uint32_t p12c(uint32_t t, int i) { return 64 * (t >> 3) + (t & 7) + 8 * i; }
+__device__ __forceinline__ uint32_t p12d(uint32_t t, int i) { return 8 * t + i; }
+
+// LDS slot of element e: its low five bits XOR-ed with bits 5 to 7, so that
+// each half-wave hits 32 distinct 8-byte banks in all four layouts (bits 3, 4
+// identify a thread's group in layout 3, bits 6, 7 in layout 2).
+__device__ __forceinline__ uint32_t slot12(uint32_t e)
+{
+    const uint32_t h = (e >> 5) & 7;
+    return e ^ h ^ ((h >> 1) << 3);
+}
 
 template <int PRO, int EPI, class A>
 __device__ __forceinline__ void fwd12_body(const NttArgs &a, const LimbPos &lp, const Prime &P, const A &ar,
-                                           uint64_t *lds)
+                                           uint64_t *lds, uint32_t t)
 {
-    const uint32_t t = threadIdx.x, base2 = (t >> 4) * 256 + (t & 15);
-    const uint64_t *src = a.src + (int64_t)lp.poly * a.map.src_poly_stride + (size_t)lp.row * 4096;
-    typename A::V v[16];
+    const size_t off = (size_t)lp.row * 4096;
+    typename A::W wa[7], wb[7];
+    typename A::V v[8], aux[8];
+    tw_fwd<3, 4096, 512>(wa, 0, ar, 1);
     if (PRO == PRO_BCONV) {
-        bconv_load(v, ar, bc_source(a, lp.poly, lp.prime), P, 4096, [&](int i) { return t + 256 * i; });
+        bconv_load(v, ar, bc_source(a, lp.poly, lp.prime), P, 4096, [&](int i) { return p12a(t, i); });
     } else {
+        const uint64_t *src = a.src + (int64_t)lp.poly * a.map.src_poly_stride + off;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = load_fwd<PRO>(a, lp, ar, src, t + 256 * i, P);
+        for (int i = 0; i < 8; ++i) v[i] = load_fwd<PRO>(a, lp, ar, src, p12a(t, i), P);
     }
-    fwd16<4096, 256>(v, t, ar, 1);
+    fwd_rw<3>(v, wa, ar);
+    tw_fwd<3, 4096, 64>(wb, p12b(t, 0), ar, 1);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) lds[pad(t + 256 * i)] = ar.to_bits(v[i]);
+    for (int i = 0; i < 8; ++i) lds[slot12(p12a(t, i))] = ar.to_bits(v[i]);
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = ar.from_bits(lds[pad(base2 + 16 * i)]);
+    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(lds[slot12(p12b(t, i))]);
     ar.reduce_all(v);
-    fwd16<4096, 16>(v, base2, ar, 1);
+    fwd_rw<3>(v, wb, ar);
+    tw_fwd<3, 4096, 8>(wa, p12c(t, 0), ar, 1);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) lds[pad(base2 + 16 * i)] = ar.to_bits(v[i]);
-    __syncthreads();
+    for (int i = 0; i < 8; ++i) lds[slot12(p12b(t, i))] = ar.to_bits(v[i]);
+    wave_sync();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = ar.from_bits(lds[pad(16 * t + i)]);
+    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(lds[slot12(p12c(t, i))]);
     ar.reduce_all(v);
-    fwd16<4096, 1>(v, 16 * t, ar, 1);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) lds[pad(16 * t + i)] = fwd_out<EPI>(ar, v[i]);
-    __syncthreads();
-    uint64_t x[16], addv[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        x[i] = lds[pad(t + 256 * i)];
-        addv[i] = 0;
-    }
+    fwd_rw<3>(v, wa, ar);
+    // the epilogue's operands, in flight across the last round
+    uint64_t addv[8];
     const uint64_t *add = EPI == EPI_MODDOWN ? pick(a.add, lp.poly) : nullptr;
-    if (add) {
-        add += (size_t)lp.row * 4096;
-        if (a.galois == 1) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) addv[i] = add[t + 256 * i];
-        } else {  // the whole limb's addend through LDS, then permuted
-            __syncthreads();
+    for (int i = 0; i < 8; ++i) addv[i] = 0;
+    if (EPI != EPI_PLAIN) {
+        const uint64_t *ax = pick(a.aux, lp.poly) + off;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) lds[pad(t + 256 * i)] = add[t + 256 * i];
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 16; ++i) addv[i] = lds[pad(galois_src(t + 256 * i, a.galois, 12))];
-        }
+        for (int i = 0; i < 8; ++i) aux[i] = ar.from_u64(ax[p12d(t, i)]);
     }
-    uint64_t *dst = a.dst + (int64_t)lp.poly * a.map.dst_poly_stride + (size_t)lp.row * 4096;
+    if (add) {
+        add += off;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const uint64_t auxv = EPI == EPI_PLAIN ? 0 : pick(a.aux, lp.poly)[(size_t)lp.row * 4096 + t + 256 * i];
-        store_fwd<EPI>(a, lp, ar, dst, t + 256 * i, x[i], addv[i], auxv, 4096);
+        for (int i = 0; i < 8; ++i) addv[i] = add[a.galois == 1 ? p12d(t, i) : galois_src(p12d(t, i), a.galois, 12)];
+    }
+    tw_fwd<3, 4096, 1>(wb, 8 * t, ar, 1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) lds[slot12(p12c(t, i))] = ar.to_bits(v[i]);
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(lds[slot12(p12d(t, i))]);
+    ar.reduce_all(v);
+    fwd_rw<3>(v, wb, ar);
+    if (EPI == EPI_PLAIN) {
+        uint64_t *dst = a.dst + (int64_t)lp.poly * a.map.dst_poly_stride + off;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) dst[p12d(t, i)] = ar.fwd_final(v[i]);
+    } else {
+        const ulonglong2 c = a.cst[lp.prime];
+        uint64_t *out = pick(a.out, lp.poly) + off;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) out[p12d(t, i)] = ar.scaled_difference(v[i], aux[i], addv[i], c);
     }
 }
 
 template <int PRO, int EPI>
-__device__ __forceinline__ void fwd12_unit(const NttArgs &a, uint32_t limb, uint32_t, uint64_t *lds, uint32_t)
+__device__ __forceinline__ void fwd12_unit(const NttArgs &a, uint32_t limb, uint32_t, uint64_t *lds, uint32_t tx)
 {
     const LimbPos lp = limb_pos(a.map, limb);
     if (lp.skip) return;
     const Prime P = a.primes[lp.prime];
     if (P.q < kFpMaxPrime)
-        fwd12_body<PRO, EPI>(a, lp, P, fp_arith(a, P, lp.prime, 4096), lds);
+        fwd12_body<PRO, EPI>(a, lp, P, fp_arith(a, P, lp.prime, 4096), lds, tx);
     else
-        fwd12_body<PRO, EPI>(a, lp, P, int_arith(a, P, lp.prime, 4096), lds);
+        fwd12_body<PRO, EPI>(a, lp, P, int_arith(a, P, lp.prime, 4096), lds, tx);
 }
 
 template <int PRO, class A>
-__device__ __forceinline__ void inv12_body(const NttArgs &a, const LimbPos &lp, const A &ar, uint64_t *lds)
+__device__ __forceinline__ void inv12_body(const NttArgs &a, const LimbPos &lp, const A &ar, uint64_t *lds, uint32_t t)
 {
-    const uint32_t t = threadIdx.x, base2 = (t >> 4) * 256 + (t & 15);
     const uint64_t *src = a.src + (int64_t)lp.poly * a.map.src_poly_stride + (size_t)lp.row * 4096;
+    typename A::W wa[7], wb[7];
+    typename A::V v[8];
+    tw_inv<3, 4096, 1>(wa, 8 * t, ar, 1);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        uint32_t e = t + 256 * i;
-        lds[pad(e)] = src[PRO == PRO_GALOIS ? galois_src(e, a.galois, 12) : e];
-    }
-    __syncthreads();
-    typename A::V v[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = ar.from_u64(lds[pad(16 * t + i)]);
+    for (int i = 0; i < 8; ++i)
+        v[i] = ar.from_u64(src[PRO == PRO_GALOIS ? galois_src(p12d(t, i), a.galois, 12) : p12d(t, i)]);
     ar.reduce_all(v);
-    inv16<4096, 1>(v, 16 * t, ar, 1);
+    inv_rw<3>(v, wa, ar);
+    tw_inv<3, 4096, 8>(wb, p12c(t, 0), ar, 1);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) lds[pad(16 * t + i)] = ar.to_bits(v[i]);
+    for (int i = 0; i < 8; ++i) lds[slot12(p12d(t, i))] = ar.to_bits(v[i]);
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(lds[slot12(p12c(t, i))]);
+    ar.reduce_all(v);
+    inv_rw<3>(v, wb, ar);
+    tw_inv<3, 4096, 64>(wa, p12b(t, 0), ar, 1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) lds[slot12(p12c(t, i))] = ar.to_bits(v[i]);
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(lds[slot12(p12b(t, i))]);
+    ar.reduce_all(v);
+    inv_rw<3>(v, wa, ar);
+    tw_inv<3, 4096, 512>(wb, 0, ar, 1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) lds[slot12(p12b(t, i))] = ar.to_bits(v[i]);
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = ar.from_bits(lds[pad(base2 + 16 * i)]);
+    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(lds[slot12(p12a(t, i))]);
     ar.reduce_all(v);
-    inv16<4096, 16>(v, base2, ar, 1);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) lds[pad(base2 + 16 * i)] = ar.to_bits(v[i]);
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = ar.from_bits(lds[pad(t + 256 * i)]);
-    ar.reduce_all(v);
-    inv16<4096, 256>(v, t, ar, 1);
+    inv_rw<3>(v, wb, ar);
     uint64_t *dst = a.dst + (int64_t)lp.poly * a.map.dst_poly_stride + (size_t)lp.row * 4096;
-    inv_store(dst, v, ar, a.ys_mode, [&](int i) { return t + 256 * i; });
+    inv_store(dst, v, ar, a.ys_mode, [&](int i) { return p12a(t, i); });
 }
 
 template <int PRO>
-__device__ __forceinline__ void inv12_unit(const NttArgs &a, uint32_t limb, uint32_t, uint64_t *lds, uint32_t)
+__device__ __forceinline__ void inv12_unit(const NttArgs &a, uint32_t limb, uint32_t, uint64_t *lds, uint32_t tx)
 {
     const LimbPos lp = limb_pos(a.map, limb);
     if (lp.skip) return;
     const Prime P = a.primes[lp.prime];
     if (P.q < kFpMaxPrime)
-        inv12_body<PRO>(a, lp, inv_fp_arith(a, lp, P, 4096), lds);
+        inv12_body<PRO>(a, lp, inv_fp_arith(a, lp, P, 4096), lds, tx);
     else
-        inv12_body<PRO>(a, lp, inv_int_arith(a, lp, P, 4096), lds);
+        inv12_body<PRO>(a, lp, inv_int_arith(a, lp, P, 4096), lds, tx);
+}
+
+// ------------------------------------- N = 2^12, transforms in two launches
+// The single key switch, ModDown and Rescale at N = 2^12 are latency-bound: a
+// whole limb per workgroup (above) leaves most CUs idle and takes 7 to 20 us
+// on one of them.  Here a limb is a 64 x 64 matrix and a wave owns 8 columns
+// (or 8 rows) of it, 8 elements per lane, two rounds of three stages with one
+// exchange inside the wave.  What is local to columns shares a launch, and so
+// does what is local to rows:
+//   inverse rows | inverse columns, conversion, forward columns |
+//   forward rows, inner product, inverse rows of the special rows |
+//   inverse columns, conversion, forward columns | forward rows, P^-1 (x - .) + add
+// (Rescale: inverse rows | inverse columns, lift, forward columns | forward
+// rows, q_l^-1 (x - .)).  HMult of the small set (four limbs) went from 58 us
+// in seven launches to 32 us in these five, a rotation at K = 2 from 62 to 28 us.
+// Lane layouts (s = 0..7 along the 64-point problem): A: s + 8 i, B: 8 s + i.
+// Columns: col = lane % 8, s = lane / 8, element e = 8 row + col of the tile;
+// rows: row = lane / 8, s = lane % 8, e = 64 row + position.  slot12 keeps the
+// exchanges conflict-free in all of them.
+constexpr uint32_t kTile12 = 512;  // elements of a wave's tile
+
+// exchange of a wave's tile: v[i] at element from(i) becomes the one at to(i)
+template <class A, class From, class To>
+__device__ __forceinline__ void exchange12(const A &ar, typename A::V (&v)[8], uint64_t *L, From from, To to)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) L[slot12(from(i))] = ar.to_bits(v[i]);
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(L[slot12(to(i))]);
+    ar.reduce_all(v);
+}
+
+// 64-point transforms over layout s; e(p) is the tile element of position p of
+// the lane's problem, B the twiddle block (1 for columns, 64 + row for rows).
+// Forward A -> B, inverse B -> A; the caller has centred the inverse's input.
+template <class A, class E>
+__device__ __forceinline__ void fwd64(const A &ar, typename A::V (&v)[8], uint64_t *L, uint32_t s, uint32_t B, E e)
+{
+    typename A::W wa[7], wb[7];
+    tw_fwd<3, 64, 8>(wa, s, ar, B);
+    tw_fwd<3, 64, 1>(wb, 8 * s, ar, B);
+    fwd_rw<3>(v, wa, ar);
+    exchange12(ar, v, L, [&](int i) { return e(s + 8 * i); }, [&](int i) { return e(8 * s + i); });
+    fwd_rw<3>(v, wb, ar);
+}
+
+template <class A, class E>
+__device__ __forceinline__ void inv64(const A &ar, typename A::V (&v)[8], uint64_t *L, uint32_t s, uint32_t B, E e)
+{
+    typename A::W wa[7], wb[7];
+    tw_inv<3, 64, 1>(wb, 8 * s, ar, B);
+    tw_inv<3, 64, 8>(wa, s, ar, B);
+    inv_rw<3>(v, wb, ar);
+    exchange12(ar, v, L, [&](int i) { return e(8 * s + i); }, [&](int i) { return e(s + 8 * i); });
+    inv_rw<3>(v, wa, ar);
+}
+
+// Inverse rows: 8 rows of a limb (tile) from its evaluations to a.mid.
+template <int PRO, class A>
+__device__ __forceinline__ void inv_rows12(const NttArgs &a, const LimbPos &lp, const Prime &P, const A &ar, uint64_t *L,
+                                           uint32_t tile, uint32_t lane)
+{
+    const size_t row_off = (int64_t)lp.poly * a.map.src_poly_stride + (size_t)lp.row * 4096;
+    const uint64_t *src = a.src + row_off;
+    const uint32_t row = lane >> 3, s = lane & 7, e0 = tile * kTile12 + 64 * row + 8 * s;
+    typename A::V v[8];
+    uint64_t x[8], y[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = src[PRO == PRO_GALOIS ? galois_src(e0 + i, a.galois, 12) : e0 + i];
+    if (PRO == PRO_TENSOR) {  // HMult's d2 = a1 b1
+#pragma unroll
+        for (int i = 0; i < 8; ++i) y[i] = a.src2[row_off + e0 + i];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = PRO == PRO_TENSOR ? ar.product(x[i], y[i], P) : ar.from_u64(x[i]);
+    ar.reduce_all(v);
+    inv64(ar, v, L, s, 64 + 8 * tile + row, [&](uint32_t p) { return 64 * row + p; });
+    uint64_t *m = a.mid + (int64_t)lp.poly * a.mid_stride + (size_t)lp.row * 4096 + tile * kTile12;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m[64 * row + s + 8 * i] = ar.to_bits(v[i]);
+}
+
+template <int PRO>
+__global__ __launch_bounds__(64) void k12_inv_rows(NttArgs a)
+{
+    __shared__ uint64_t L[kTile12];
+    const LimbPos lp = limb_pos(a.map, blockIdx.y);
+    const Prime P = a.primes[lp.prime];
+    if (P.q < kFpMaxPrime)
+        inv_rows12<PRO>(a, lp, P, fp_arith(a, P, lp.prime, 4096), L, blockIdx.x, threadIdx.x);
+    else
+        inv_rows12<PRO>(a, lp, P, int_arith(a, P, lp.prime, 4096), L, blockIdx.x, threadIdx.x);
+}
+
+// Forward rows: 8 rows of a limb from a.mid to its evaluations, with the epilogue.
+template <int EPI, class A>
+__device__ __forceinline__ void fwd_rows12(const NttArgs &a, const LimbPos &lp, const A &ar, uint64_t *L, uint32_t tile,
+                                           uint32_t lane)
+{
+    const uint32_t row = lane >> 3, s = lane & 7, e0 = tile * kTile12 + 64 * row + 8 * s;
+    const size_t off = (size_t)lp.row * 4096;
+    const uint64_t *m = a.mid + (int64_t)lp.poly * a.mid_stride + off + tile * kTile12;
+    typename A::V v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(m[64 * row + s + 8 * i]);
+    // the epilogue's operands, in flight across the rounds
+    uint64_t auxv[8], addv[8];
+    const uint64_t *add = EPI == EPI_MODDOWN ? pick(a.add, lp.poly) : nullptr;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) auxv[i] = EPI != EPI_PLAIN ? pick(a.aux, lp.poly)[off + e0 + i] : 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        addv[i] = add ? add[off + (a.galois == 1 ? e0 + i : galois_src(e0 + i, a.galois, 12))] : 0;
+    ar.reduce_all(v);
+    fwd64(ar, v, L, s, 64 + 8 * tile + row, [&](uint32_t p) { return 64 * row + p; });
+    if (EPI == EPI_PLAIN) {
+        uint64_t *dst = a.dst + (int64_t)lp.poly * a.map.dst_poly_stride + off;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) dst[e0 + i] = ar.fwd_final(v[i]);
+    } else {
+        const ulonglong2 c = a.cst[lp.prime];
+        uint64_t *out = pick(a.out, lp.poly) + off;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) out[e0 + i] = ar.scaled_difference(v[i], ar.from_u64(auxv[i]), addv[i], c);
+    }
+}
+
+template <int EPI>
+__global__ __launch_bounds__(64) void k12_fwd_rows(NttArgs a)
+{
+    __shared__ uint64_t L[kTile12];
+    const LimbPos lp = limb_pos(a.map, blockIdx.y);
+    const Prime P = a.primes[lp.prime];
+    if (P.q < kFpMaxPrime)
+        fwd_rows12<EPI>(a, lp, fp_arith(a, P, lp.prime, 4096), L, blockIdx.x, threadIdx.x);
+    else
+        fwd_rows12<EPI>(a, lp, int_arith(a, P, lp.prime, 4096), L, blockIdx.x, threadIdx.x);
+}
+
+// Second inverse pass of a source row's 8 columns, scaled: canonical inputs of
+// the conversion (shifted for ModDown) to the tile y, element lane + 64 i.
+template <int MODE, class A>
+__device__ __forceinline__ void source_cols12(const A &ar, const uint64_t *m, uint64_t *y, uint32_t tile, uint32_t lane)
+{
+    const uint32_t col = lane & 7, s = lane >> 3, c = 8 * tile + col;
+    typename A::V v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(m[64 * (8 * s + i) + c]);
+    ar.reduce_all(v);
+    inv64(ar, v, y, s, 1, [&](uint32_t p) { return 8 * p + col; });
+    wave_sync();  // the exchange's reads are done: the tile takes the result
+    inv_store(y, v, ar, MODE == COLS_MODDOWN ? 2 : 1, [&](int i) { return lane + 64 * i; });
+}
+
+// v[i] = Conv(y)[lane + 64 i] from the source tiles in LDS.
+template <class Acc, class A>
+__device__ __forceinline__ void conv12_acc(typename A::V (&v)[8], const A &ar, const uint64_t *y, uint32_t ns,
+                                           ConvWord *h, const Prime &P, uint32_t lane)
+{
+    Acc acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i].start(h);
+    for (uint32_t k = 0; k < ns; ++k) {
+        uint64_t x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = y[k * kTile12 + lane + 64 * i];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i].add(x[i], h, k);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = acc[i].value(ar, h, P);
+}
+__device__ __forceinline__ void conv12(double (&v)[8], const FpArith &ar, const uint64_t *y, uint32_t ns, ConvWord *h,
+                                       const Prime &P, uint32_t lane)
+{
+    if (ns <= kFoldMaxTerms)
+        conv12_acc<FoldAcc>(v, ar, y, ns, h, P, lane);
+    else
+        conv12_acc<WideAcc<MacSplit>>(v, ar, y, ns, h, P, lane);
+}
+__device__ __forceinline__ void conv12(uint64_t (&v)[8], const IntArith &ar, const uint64_t *y, uint32_t ns, ConvWord *h,
+                                       const Prime &P, uint32_t lane)
+{
+    conv12_acc<WideAcc<MacColsAcc>>(v, ar, y, ns, h, P, lane);
+}
+
+// First forward pass of a target row's 8 columns, converted from the sources.
+template <int MODE, class A>
+__device__ __forceinline__ void target_cols12(const A &ar, const Prime &P, const uint64_t *y, uint32_t ns, ConvWord *h,
+                                              uint64_t qlmod, uint64_t ql, uint64_t *L, uint64_t *m, uint32_t tile,
+                                              uint32_t lane)
+{
+    const uint32_t col = lane & 7, s = lane >> 3, c = 8 * tile + col;
+    typename A::V v[8];
+    if (MODE == COLS_RESCALE) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = ar.lift(y[lane + 64 * i], ql, qlmod, P);
+    } else {
+        conv12(v, ar, y, ns, h, P, lane);
+    }
+    fwd64(ar, v, L, s, 1, [&](uint32_t p) { return 8 * p + col; });
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m[64 * (8 * s + i) + c] = ar.to_bits(v[i]);
+}
+
+// A workgroup of 8 waves: a job's sources for one tile (each wave a row, two
+// when there are more than eight), then one target row per wave.  A job with
+// more than eight targets takes several workgroups, which all form the sources:
+// that costs no time, since they do it side by side.
+constexpr uint32_t kColsWaves = 8;
+
+template <int MODE>
+__global__ __launch_bounds__(64 * kColsWaves) void k12_cols(ColsArgs a)
+{
+    extern __shared__ uint64_t lds12[];  // ns source tiles, then a tile per wave
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const uint32_t tile = blockIdx.x, job = blockIdx.y, n = a.level + 1;
+    uint32_t lo = 0, ns = 1, set = a.pset, prime0 = a.level, ntgt = a.level;
+    if (MODE == COLS_MODUP) {
+        lo = job * a.alpha;
+        ns = min(a.alpha, n - lo);
+        set = job * a.alpha + ns - 1;
+        prime0 = lo;
+        ntgt = n + a.np - ns;
+    } else if (MODE == COLS_MODDOWN) {
+        ns = a.np;
+        prime0 = a.nq;
+        ntgt = n;
+    }
+    const uint64_t *src = a.src + (MODE == COLS_MODUP ? (int64_t)lo * 4096 : (int64_t)job * a.src_stride);
+    for (uint32_t k = w; k < ns; k += kColsWaves) {
+        const uint32_t pi = prime0 + k;
+        const Prime P = a.primes[pi];
+        uint64_t *y = lds12 + k * kTile12;
+        if (P.q < kFpMaxPrime) {
+            FpArith ar = fp_arith(a.twdi, P, pi, 4096);
+            if (MODE != COLS_RESCALE) ar.fc = a.ysd[set * kMaxDigitPrimes + k];
+            source_cols12<MODE>(ar, src + (size_t)k * 4096, y, tile, lane);
+        } else {
+            IntArith ar = int_arith(a.twi, P, pi, 4096);
+            if (MODE != COLS_RESCALE) {
+                const ulonglong2 f = a.ys[set * kMaxDigitPrimes + k];
+                ar.fc = f.x;
+                ar.fc_s = f.y;
+            }
+            source_cols12<MODE>(ar, src + (size_t)k * 4096, y, tile, lane);
+        }
+    }
+    __syncthreads();
+    const uint32_t idx = blockIdx.z * kColsWaves + w;
+    if (idx >= ntgt) return;
+    const uint32_t r = MODE == COLS_MODUP && idx >= lo ? idx + ns : idx;
+    const uint32_t pi = coef::row_prime(r, a.level, a.nq);
+    const Prime P = a.primes[pi];
+    ConvWord *h = (ConvWord *)(a.hmod + ((size_t)set * (a.nq + a.np) + pi) * kConvRow);
+    const uint64_t qlmod = MODE == COLS_RESCALE ? a.rs_qlmod[pi] : 0, ql = MODE == COLS_RESCALE ? a.primes[a.level].q : 0;
+    uint64_t *L = lds12 + (ns + w) * kTile12, *m = a.dst + (int64_t)job * a.dst_stride + (size_t)r * 4096;
+    if (P.q < kFpMaxPrime)
+        target_cols12<MODE>(fp_arith(a.twdf, P, pi, 4096), P, lds12, ns, h, qlmod, ql, L, m, tile, lane);
+    else
+        target_cols12<MODE>(int_arith(a.twf, P, pi, 4096), P, lds12, ns, h, qlmod, ql, L, m, tile, lane);
+}
+
+// Half `half` of the inner product of extended row r on 8 rows of its matrix
+// (layout B: eight consecutive positions per lane): sum_j x_j[r] key[j][half][r],
+// x_j the digit's row (READY: finished, gathered through ip.galois; else its
+// last forward pass runs here), its own row of ip.own (gathered through
+// ip.own_galois) or, with a tensor, the product a1 b1; rows q_0..q_l of a
+// tensor also take [P]_q d_half (see IpArgs).  A special row goes on to
+// ModDown's first inverse pass.  fwd, inv: the row's two directions.
+template <bool READY, class A>
+__device__ __forceinline__ void ip_rows12(const IpArgs &ip, const NttArgs &ia, const A &fwd, const A &inv, const Prime &P,
+                                          uint32_t half, uint32_t r, uint32_t pi, uint64_t *L, uint32_t tile,
+                                          uint32_t lane)
+{
+    const bool qrow = r <= ip.level;
+    const uint32_t row = lane >> 3, s = lane & 7, e0 = tile * kTile12 + 64 * row + 8 * s;
+    const size_t krows = ip.nq + ip.np, off = (size_t)r * 4096;
+    auto elem = [&](uint32_t p) { return 64 * row + p; };
+    typename A::Sum sum[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) fwd.sum_start(sum[i]);
+    for (uint32_t j = 0; j < ip.beta; ++j) {
+        const uint64_t *key = ip.key + (((size_t)j * 2 + half) * krows + pi) * 4096 + e0;
+        const bool own = qrow && r >= j * ip.alpha && r < j * ip.alpha + ip.alpha && (ip.own || ip.ta0);
+        uint64_t k[8], x[8];
+        typename A::V v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) k[i] = key[i];
+        if (own && ip.ta0) {
+            uint64_t y[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = ip.ta1[off + e0 + i], y[i] = ip.tb1[off + e0 + i];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = fwd.product(x[i], y[i], P);
+        } else if (own || READY) {
+            const uint64_t *xr = own ? ip.own + off : ip.ext + ((size_t)j * ip.rows + r) * 4096;
+            const uint32_t g = own ? ip.own_galois : ip.galois;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = fwd.from_u64(xr[g == 1 ? e0 + i : galois_src(e0 + i, g, 12)]);
+        } else {
+            const uint64_t *m = ip.ext + ((size_t)j * ip.rows + r) * 4096 + tile * kTile12;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = fwd.from_bits(m[64 * row + s + 8 * i]);
+            fwd.reduce_all(v);
+            wave_sync();  // the previous digit's exchange is read
+            fwd64(fwd, v, L, s, 64 + 8 * tile + row, elem);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = fwd.sum_input(v[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) fwd.sum_add(sum[i], v[i], k[i]);
+    }
+    if (qrow && ip.ta0) {
+        const uint64_t pm = ip.pmod[pi];
+        uint64_t x[8], y[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = ip.ta0[off + e0 + i], y[i] = (half ? ip.tb1 : ip.tb0)[off + e0 + i];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) fwd.sum_add(sum[i], fwd.product(x[i], y[i], P), pm);
+        if (half) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = ip.ta1[off + e0 + i], y[i] = ip.tb0[off + e0 + i];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) fwd.sum_add(sum[i], fwd.product(x[i], y[i], P), pm);
+        }
+    }
+    typename A::V v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = fwd.sum_value(sum[i], P);
+    if (qrow) {
+        uint64_t *acc = ip.acc + ((size_t)half * ip.rows + r) * 4096 + e0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = fwd.fwd_final(v[i]);
+        return;
+    }
+    wave_sync();
+    inv64(inv, v, L, s, 64 + 8 * tile + row, elem);
+    uint64_t *m = ia.mid + (int64_t)half * ia.mid_stride + (size_t)(r - ip.level - 1) * 4096 + tile * kTile12;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m[64 * row + s + 8 * i] = inv.to_bits(v[i]);
+}
+
+template <bool READY>
+__global__ __launch_bounds__(64) void k12_ip_rows(IpArgs ip, NttArgs ia, const ulonglong2 *twf, const double *twdf)
+{
+    __shared__ uint64_t L[kTile12];
+    const uint32_t half = blockIdx.z, r = blockIdx.y, pi = coef::row_prime(r, ip.level, ip.nq);
+    const Prime P = ip.primes[pi];
+    if (P.q < kFpMaxPrime)
+        ip_rows12<READY>(ip, ia, fp_arith(twdf, P, pi, 4096), fp_arith(ia.twd, P, pi, 4096), P, half, r, pi, L, blockIdx.x,
+                         threadIdx.x);
+    else
+        ip_rows12<READY>(ip, ia, int_arith(twf, P, pi, 4096), int_arith(ia.tw, P, pi, 4096), P, half, r, pi, L, blockIdx.x,
+                         threadIdx.x);
 }
 
 // ---------------------------------------------------- kernels: grid and queue
@@ -1123,34 +1501,27 @@ __device__ __forceinline__ UnitId grid_unit(const NttArgs &a)
     return unit_of(blockIdx.y * 16 + blockIdx.x, gridDim.y, a.n_heavy, a.heavy);
 }
 
-constexpr int kLds12 = 4352;
-
-// Persistent kernels at N = 2^16 read their argument block with scalar loads
-// (run_work_queue_uniform).  Those at N = 2^12 keep it in LDS: with 16
-// elements per thread they already need close to the scalar register file,
-// and a scalar copy would spill to scratch.
-#define QATTR(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 4 : 1)))
-#define NTT_KERNELS(NAME, LDS, THREADS, UNIFORM, GRID_ATTR, ...)                                \
-    __global__ __launch_bounds__(THREADS) GRID_ATTR void k_##NAME(NttArgs a)                     \
+#define NTT_GRID(NAME, LDS, THREADS, ATTR, ...)                                                  \
+    __global__ __launch_bounds__(THREADS) ATTR void k_##NAME(NttArgs a)                          \
     {                                                                                             \
         __shared__ uint64_t lds[LDS];                                                             \
         const UnitId u = grid_unit(a);                                                            \
         __VA_ARGS__(a, u.limb, u.tile, lds, threadIdx.x);                                         \
-    }                                                                                             \
-    __global__ __launch_bounds__(THREADS) QATTR(THREADS) void q_##NAME(const NttArgs *insts, WorkQueue q)        \
+    }
+// two workgroups per CU: at most 128 VGPRs
+#define NTT_QUEUE(NAME, LDS, THREADS, ...)                                                       \
+    __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) void           \
+        q_##NAME(const NttArgs *insts, WorkQueue q)                                              \
     {                                                                                             \
         __shared__ uint64_t lds[LDS];                                                             \
         __shared__ uint32_t claim;                                                                \
-        auto body = [&](const NttArgs &a, uint32_t limb, uint32_t tile) {                        \
-            __VA_ARGS__(a, limb, tile, lds, UNIFORM ? thread_index() : threadIdx.x);              \
-        };                                                                                        \
-        if constexpr (UNIFORM) {                                                                  \
-            run_work_queue_uniform(insts, q, &claim, body);                                       \
-        } else {                                                                                  \
-            __shared__ NttArgs sa;                                                                \
-            run_work_queue(insts, q, sa, &claim, body);                                           \
-        }                                                                                         \
+        run_work_queue_uniform(insts, q, &claim, [&](const NttArgs &a, uint32_t limb, uint32_t tile) { \
+            __VA_ARGS__(a, limb, tile, lds, thread_index());                                      \
+        });                                                                                       \
     }
+#define NTT_KERNELS(NAME, LDS, THREADS, ATTR, ...)                                               \
+    NTT_GRID(NAME, LDS, THREADS, ATTR, __VA_ARGS__)                                               \
+    NTT_QUEUE(NAME, LDS, THREADS, __VA_ARGS__)
 
 // Three 512-thread workgroups per CU for the plain passes: the column passes
 // fit in 72 VGPRs; the row passes spill 12 to 16 bytes per lane and still gain
@@ -1158,16 +1529,16 @@ constexpr int kLds12 = 4352;
 // keeps two workgroups per CU).
 #define OCC6 __attribute__((amdgpu_waves_per_eu(6)))
 
-NTT_KERNELS(fwd_col_plain, kLds16, kThreads16, true, OCC6, fwd_col_unit<PRO_PLAIN>)
-NTT_KERNELS(fwd_col_rescale, kLds16, kThreads16, true, , fwd_col_unit<PRO_RESCALE>)
-NTT_KERNELS(fwd_col_bconv, kLds16, kThreads16, true, , fwd_col_unit<PRO_BCONV>)
-NTT_KERNELS(fwd_row_plain, kLds16, kThreads16, true, OCC6, fwd_row_unit<EPI_PLAIN>)
-NTT_KERNELS(fwd_row_moddown, kLds16, kThreads16, true, , fwd_row_unit<EPI_MODDOWN>)
-NTT_KERNELS(fwd_row_rescale, kLds16, kThreads16, true, , fwd_row_unit<EPI_RESCALE>)
-NTT_KERNELS(inv_row_plain, kLds16, kThreads16, true, OCC6, inv_row_unit<PRO_PLAIN>)
-NTT_KERNELS(inv_row_galois, kLds16, kThreads16, true, , inv_row_unit<PRO_GALOIS>)
-NTT_KERNELS(inv_row_tensor, kLds16, kThreads16, true, , inv_row_unit<PRO_TENSOR>)
-NTT_KERNELS(inv_col, kLds16, kThreads16, true, OCC6, inv_col_unit)
+NTT_KERNELS(fwd_col_plain, kLds16, kThreads16, OCC6, fwd_col_unit<PRO_PLAIN>)
+NTT_GRID(fwd_col_rescale, kLds16, kThreads16, , fwd_col_unit<PRO_RESCALE>)
+NTT_KERNELS(fwd_col_bconv, kLds16, kThreads16, , fwd_col_unit<PRO_BCONV>)
+NTT_KERNELS(fwd_row_plain, kLds16, kThreads16, OCC6, fwd_row_unit<EPI_PLAIN>)
+NTT_KERNELS(fwd_row_moddown, kLds16, kThreads16, , fwd_row_unit<EPI_MODDOWN>)
+NTT_GRID(fwd_row_rescale, kLds16, kThreads16, , fwd_row_unit<EPI_RESCALE>)
+NTT_KERNELS(inv_row_plain, kLds16, kThreads16, OCC6, inv_row_unit<PRO_PLAIN>)
+NTT_KERNELS(inv_row_galois, kLds16, kThreads16, , inv_row_unit<PRO_GALOIS>)
+NTT_GRID(inv_row_tensor, kLds16, kThreads16, , inv_row_unit<PRO_TENSOR>)
+NTT_KERNELS(inv_col, kLds16, kThreads16, OCC6, inv_col_unit)
 // Grid kernels with narrower tiles (TW = 8, 4 columns or rows per workgroup of
 // 32 TW threads), for launches over few limbs; unit = (blockIdx.x, blockIdx.y).
 #define NTT_NARROW(NAME, UNIT_T)                                                                    \
@@ -1225,23 +1596,19 @@ NTT_NARROW(inv_col, U_IC)
 #undef NTT_NARROW
 
 #define FWD12_PP fwd12_unit<PRO_PLAIN, EPI_PLAIN>
-#define FWD12_PM fwd12_unit<PRO_PLAIN, EPI_MODDOWN>
-#define FWD12_RR fwd12_unit<PRO_RESCALE, EPI_RESCALE>
 #define FWD12_RP fwd12_unit<PRO_RESCALE, EPI_PLAIN>
 #define FWD12_BM fwd12_unit<PRO_BCONV, EPI_MODDOWN>
-NTT_KERNELS(fwd12_plain, kLds12, kThreads, false, , FWD12_PP)
-NTT_KERNELS(fwd12_moddown, kLds12, kThreads, false, , FWD12_PM)
-NTT_KERNELS(fwd12_rescale, kLds12, kThreads, false, , FWD12_RR)
-NTT_KERNELS(fwd12_lift, kLds12, kThreads, false, , FWD12_RP)
-NTT_KERNELS(fwd12_bconv_moddown, kLds12, kThreads, false, , FWD12_BM)
-NTT_KERNELS(inv12_plain, kLds12, kThreads, false, , inv12_unit<PRO_PLAIN>)
-NTT_KERNELS(inv12_galois, kLds12, kThreads, false, , inv12_unit<PRO_GALOIS>)
+NTT_KERNELS(fwd12_plain, kLds12, kThreads12, , FWD12_PP)
+NTT_GRID(fwd12_lift, kLds12, kThreads12, , FWD12_RP)
+NTT_QUEUE(fwd12_bconv_moddown, kLds12, kThreads12, FWD12_BM)
+NTT_KERNELS(inv12_plain, kLds12, kThreads12, , inv12_unit<PRO_PLAIN>)
+NTT_QUEUE(inv12_galois, kLds12, kThreads12, inv12_unit<PRO_GALOIS>)
 #undef FWD12_PP
-#undef FWD12_PM
-#undef FWD12_RR
 #undef FWD12_RP
 #undef FWD12_BM
 #undef NTT_KERNELS
+#undef NTT_GRID
+#undef NTT_QUEUE
 #undef OCC6
 
 // ------------------------------------------- one launch for a whole batch
@@ -1491,24 +1858,21 @@ __global__ __launch_bounds__(coef::kCoefThreads) void k_inner_product_tensor_row
 // 2^16) with tiles of tw columns (rows); the narrow tiles have grid kernels only.
 bool stage_kernels(NttStage st, uint32_t logn, int pass, StageKernels &k, uint32_t tw = 16)
 {
-#define SK(G) \
-    k.grid = tw == 8 ? k_##G##_w8 : tw == 4 ? k_##G##_w4 : k_##G; \
-    k.queue = tw == 16 ? q_##G : nullptr; \
+#define SK(GRID, QUEUE) \
+    k.grid = GRID; \
+    k.queue = QUEUE; \
     return true;
-#define SK12(G) \
-    k.grid = k_##G; \
-    k.queue = q_##G; \
-    return true;
-    if (logn == 12) {
+#define SK_TILES(G) tw == 8 ? k_##G##_w8 : tw == 4 ? k_##G##_w4 : k_##G
+#define SK16(G) SK(SK_TILES(G), tw == 16 ? q_##G : nullptr)
+#define SK16_GRID(G) SK(SK_TILES(G), nullptr)
+    if (logn == 12) {  // whole limbs; the split transforms have launches of their own
         if (pass != 0) return false;
         switch (st) {
-        case STAGE_FWD_PLAIN: SK12(fwd12_plain)
-        case STAGE_FWD_MODDOWN: SK12(fwd12_moddown)
-        case STAGE_FWD_RESCALE: SK12(fwd12_rescale)
-        case STAGE_FWD_LIFT: SK12(fwd12_lift)
-        case STAGE_FWD_BCONV_MODDOWN: SK12(fwd12_bconv_moddown)
-        case STAGE_INV_PLAIN: SK12(inv12_plain)
-        case STAGE_INV_GALOIS: SK12(inv12_galois)
+        case STAGE_FWD_PLAIN: SK(k_fwd12_plain, q_fwd12_plain)
+        case STAGE_FWD_LIFT: SK(k_fwd12_lift, nullptr)
+        case STAGE_FWD_BCONV_MODDOWN: SK(nullptr, q_fwd12_bconv_moddown)
+        case STAGE_INV_PLAIN: SK(k_inv12_plain, q_inv12_plain)
+        case STAGE_INV_GALOIS: SK(nullptr, q_inv12_galois)
         default: return false;
         }
     }
@@ -1523,32 +1887,32 @@ bool stage_kernels(NttStage st, uint32_t logn, int pass, StageKernels &k, uint32
     }
     switch (st) {
     case STAGE_FWD_PLAIN:
-        if (pass == 0) { SK(fwd_col_plain) } else { SK(fwd_row_plain) }
-    case STAGE_FWD_MODDOWN:
-        if (pass == 0) { SK(fwd_col_plain) } else { SK(fwd_row_moddown) }
+        if (pass == 0) { SK16(fwd_col_plain) } else { SK16(fwd_row_plain) }
     case STAGE_FWD_RESCALE:
-        if (pass == 0) { SK(fwd_col_rescale) } else { SK(fwd_row_rescale) }
+        if (pass == 0) { SK16_GRID(fwd_col_rescale) } else { SK16_GRID(fwd_row_rescale) }
     case STAGE_FWD_LIFT:
-        if (pass == 0) { SK(fwd_col_rescale) } else { SK(fwd_row_plain) }
+        if (pass == 0) { SK16_GRID(fwd_col_rescale) } else { SK16(fwd_row_plain) }
     case STAGE_FWD_BCONV_MODDOWN:
-        if (pass == 0) { SK(fwd_col_bconv) } else { SK(fwd_row_moddown) }
+        if (pass == 0) { SK16(fwd_col_bconv) } else { SK16(fwd_row_moddown) }
     case STAGE_INV_PLAIN:
-        if (pass == 0) { SK(inv_row_plain) } else { SK(inv_col) }
+        if (pass == 0) { SK16(inv_row_plain) } else { SK16(inv_col) }
     case STAGE_INV_GALOIS:
-        if (pass == 0) { SK(inv_row_galois) } else { SK(inv_col) }
+        if (pass == 0) { SK16(inv_row_galois) } else { SK16(inv_col) }
     case STAGE_INV_TENSOR:
-        if (pass == 0) { SK(inv_row_tensor) } else { SK(inv_col) }
+        if (pass == 0) { SK16_GRID(inv_row_tensor) } else { SK16(inv_col) }
     default: return false;
     }
 #undef SK
-#undef SK12
+#undef SK_TILES
+#undef SK16
+#undef SK16_GRID
 }
 
 }  // namespace
 
 uint32_t ntt_passes(uint32_t logn) { return logn == 12 ? 1 : 2; }
 uint32_t ntt_tiles(uint32_t logn) { return logn == 12 ? 1 : 16; }
-static uint32_t ntt_threads(uint32_t logn) { return logn == 12 ? kThreads : kThreads16; }
+static uint32_t ntt_threads(uint32_t logn) { return logn == 12 ? kThreads12 : kThreads16; }
 
 // Fills a.heavy with the launch limbs on the integer path.  It leaves none when
 // they do not fit the list, when every limb is on that path, or in launches of
@@ -1615,11 +1979,11 @@ hipError_t launch_ntt_stage(NttStage st, const NttArgs &a0, uint32_t nlimbs, hip
     else a.n_heavy = 0;
     for (uint32_t pass = first_pass; pass < ntt_passes(a.logn); ++pass) {
         StageKernels k;
-        if (!stage_kernels(st, a.logn, pass, k, tw)) return hipErrorInvalidValue;
+        if (!stage_kernels(st, a.logn, pass, k, tw) || !k.grid) return hipErrorInvalidValue;
         const bool four = a.logn == 16 && four_element_pass(st, pass, tw);
         const uint32_t pw = tw == 2 ? 8 : tw;  // rows or columns per workgroup
         const uint32_t tiles = a.logn == 12 ? 1 : 256 / pw;
-        const uint32_t threads = a.logn == 12 ? kThreads : four ? 512 : 32 * pw;
+        const uint32_t threads = a.logn == 12 ? kThreads12 : four ? 512 : 32 * pw;
         // ModDown's conversion reads the same K source rows for every limb: workgroups in (tile, limb)
         // order send a column tile of every limb to one XCD, whose L2 then holds that tile of the
         // sources (whole limbs per XCD read all K rows, 5 MB at K = 10, against 4 MB of L2).  Over 48
@@ -1627,6 +1991,63 @@ hipError_t launch_ntt_stage(NttStage st, const NttArgs &a0, uint32_t nlimbs, hip
         a.by_tile = st == STAGE_FWD_BCONV_MODDOWN && pass == 0;
         hipLaunchKernelGGL(k.grid, dim3(tiles, nlimbs), dim3(threads), 0, stream, a);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_split12_inv_rows(NttStage st, const NttArgs &a, uint32_t nlimbs, hipStream_t stream)
+{
+    if (a.logn != 12 || !a.mid) return hipErrorInvalidValue;
+    const dim3 grid(8, nlimbs), block(64);
+    switch (st) {
+    case STAGE_INV_PLAIN: hipLaunchKernelGGL(k12_inv_rows<PRO_PLAIN>, grid, block, 0, stream, a); break;
+    case STAGE_INV_GALOIS: hipLaunchKernelGGL(k12_inv_rows<PRO_GALOIS>, grid, block, 0, stream, a); break;
+    case STAGE_INV_TENSOR: hipLaunchKernelGGL(k12_inv_rows<PRO_TENSOR>, grid, block, 0, stream, a); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_split12_cols(ColsMode mode, const ColsArgs &a, uint32_t njobs, hipStream_t stream)
+{
+    const uint32_t n = a.level + 1;
+    // the most sources and targets of a job; LDS holds a tile per source and per wave (96 KB at most)
+    const uint32_t ns = mode == COLS_MODUP ? (a.alpha < n ? a.alpha : n) : mode == COLS_MODDOWN ? a.np : 1;
+    const uint32_t least = mode == COLS_MODUP ? (n % a.alpha ? n % a.alpha : ns) : 0;
+    const uint32_t targets = mode == COLS_MODUP ? n + a.np - least : mode == COLS_MODDOWN ? n : a.level;
+    if (targets == 0 || njobs == 0) return hipSuccess;
+    const dim3 grid(8, njobs, (targets + kColsWaves - 1) / kColsWaves), block(64 * kColsWaves);
+    const size_t lds = (size_t)(ns + kColsWaves) * kTile12 * 8;
+    switch (mode) {
+    case COLS_MODUP: hipLaunchKernelGGL(k12_cols<COLS_MODUP>, grid, block, lds, stream, a); break;
+    case COLS_MODDOWN: hipLaunchKernelGGL(k12_cols<COLS_MODDOWN>, grid, block, lds, stream, a); break;
+    case COLS_RESCALE: hipLaunchKernelGGL(k12_cols<COLS_RESCALE>, grid, block, lds, stream, a); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_split12_fwd_rows(NttEpi epi, const NttArgs &a, uint32_t nlimbs, hipStream_t stream)
+{
+    if (a.logn != 12 || !a.mid || (a.map.skip_alpha && !a.map.dense)) return hipErrorInvalidValue;
+    const dim3 grid(8, nlimbs), block(64);
+    switch (epi) {
+    case EPI_PLAIN: hipLaunchKernelGGL(k12_fwd_rows<EPI_PLAIN>, grid, block, 0, stream, a); break;
+    case EPI_MODDOWN: hipLaunchKernelGGL(k12_fwd_rows<EPI_MODDOWN>, grid, block, 0, stream, a); break;
+    case EPI_RESCALE: hipLaunchKernelGGL(k12_fwd_rows<EPI_RESCALE>, grid, block, 0, stream, a); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_split12_ip(const IpArgs &ip, const NttArgs &ia, const NttArgs &fa, bool ready, hipStream_t stream)
+{
+    if (ip.logn != 12 || ia.logn != 12 || ip.fold_tot || ip.rows != ip.level + 1 + ip.np || ia.map.rows != ip.np ||
+        !ia.mid || (!ready && ip.galois != 1) ||
+        (ip.ta0 && (ip.galois != 1 || !ip.ta1 || !ip.tb0 || !ip.tb1 || !ip.pmod)))
+        return hipErrorInvalidValue;
+    const dim3 grid(8, ip.rows, 2), block(64);
+    if (ready)
+        hipLaunchKernelGGL(k12_ip_rows<true>, grid, block, 0, stream, ip, ia, fa.tw, fa.twd);
+    else
+        hipLaunchKernelGGL(k12_ip_rows<false>, grid, block, 0, stream, ip, ia, fa.tw, fa.twd);
     return hipGetLastError();
 }
 
@@ -1663,7 +2084,7 @@ hipError_t launch_ntt_stage_queue(NttStage st, uint32_t logn, uint32_t pass, con
                                   const WorkQueue &q, uint32_t grid, hipStream_t stream)
 {
     StageKernels k;
-    if (!stage_kernels(st, logn, pass, k)) return hipErrorInvalidValue;
+    if (!stage_kernels(st, logn, pass, k) || !k.queue) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k.queue, dim3(grid), dim3(ntt_threads(logn)), 0, stream, insts, q);
     return hipGetLastError();
 }
@@ -1675,30 +2096,23 @@ hipError_t launch_fused_batch(const FusedArgs &f, uint32_t grid, hipStream_t str
     return hipGetLastError();
 }
 
-// Compatibility wrappers used by the single-operation paths.
-hipError_t launch_ntt_fwd(const NttArgs &a0, uint32_t nlimbs, NttPro pro, NttEpi epi, hipStream_t stream,
-                          uint64_t *mid, int64_t mid_poly_stride)
-{
-    NttArgs a = a0;
-    a.mid = mid;
-    a.mid_stride = mid_poly_stride;
-    NttStage st;
-    if (pro == PRO_PLAIN && epi == EPI_PLAIN) st = STAGE_FWD_PLAIN;
-    else if (pro == PRO_PLAIN && epi == EPI_MODDOWN) st = STAGE_FWD_MODDOWN;
-    else if (pro == PRO_RESCALE && epi == EPI_RESCALE) st = STAGE_FWD_RESCALE;
-    else if (pro == PRO_RESCALE && epi == EPI_PLAIN) st = STAGE_FWD_LIFT;
-    else if (pro == PRO_BCONV && epi == EPI_MODDOWN) st = STAGE_FWD_BCONV_MODDOWN;
-    else return hipErrorInvalidValue;
-    return launch_ntt_stage(st, a, nlimbs, stream);
-}
-
-hipError_t launch_ntt_inv(const NttArgs &a0, uint32_t nlimbs, NttPro pro, hipStream_t stream, uint64_t *mid,
+// Whole transforms between limbs in one buffer each: plain, or of the centred lift (PRO_RESCALE).
+hipError_t launch_ntt_fwd(const NttArgs &a0, uint32_t nlimbs, NttPro pro, hipStream_t stream, uint64_t *mid,
                           int64_t mid_poly_stride)
 {
     NttArgs a = a0;
     a.mid = mid;
     a.mid_stride = mid_poly_stride;
-    return launch_ntt_stage(pro == PRO_GALOIS ? STAGE_INV_GALOIS : STAGE_INV_PLAIN, a, nlimbs, stream);
+    if (pro != PRO_PLAIN && pro != PRO_RESCALE) return hipErrorInvalidValue;
+    return launch_ntt_stage(pro == PRO_PLAIN ? STAGE_FWD_PLAIN : STAGE_FWD_LIFT, a, nlimbs, stream);
+}
+
+hipError_t launch_ntt_inv(const NttArgs &a0, uint32_t nlimbs, hipStream_t stream, uint64_t *mid, int64_t mid_poly_stride)
+{
+    NttArgs a = a0;
+    a.mid = mid;
+    a.mid_stride = mid_poly_stride;
+    return launch_ntt_stage(STAGE_INV_PLAIN, a, nlimbs, stream);
 }
 
 }  // namespace ckks
