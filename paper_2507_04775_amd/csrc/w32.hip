@@ -4,10 +4,10 @@
 //
 // Half the bytes of the 64-bit path per limb, and every modular product is
 // native: a twiddle multiplication is Shoup's method on 32-bit words (one
-// multiply, one high multiply, one multiply-subtract), the butterflies are
-// Harvey's lazy forms ([0, 4q) forward, [0, 2q) inverse, below 2^32 since
-// q < 2^30), and sums of products (base conversion, inner product, tensor)
-// accumulate exact 64-bit sums reduced once by Barrett.  The same modulus
+// high multiply, two multiplies, one subtract), the butterflies are Harvey's
+// lazy forms ([0, 4q) forward, [0, 2q) inverse, below 2^32 since q < 2^30), and
+// sums of products (base conversion, inner product, tensor) accumulate exact
+// 64-bit sums reduced once by an FP64 quotient (reduce64).  The same modulus
 // budget takes about twice the limbs.
 //
 // Operations (include/ckks.h, ckks32_*): NTT / INTT, ModUp, ModDown, key
@@ -19,13 +19,18 @@
 //   eight stages, each column an independent 256-point transform) and a row
 //   pass (the last eight), four global accesses per element as in the paper.
 //   A workgroup of 512 threads takes 32 columns (rows), 16 threads per column
-//   (row) with 16 elements each, in two register rounds of four stages and
-//   one exchange through LDS; row passes load and store 16 consecutive words
-//   per thread with 128-bit accesses and exchange once more.
-// - Base conversion, inner product, tensor, automorphism, lift: one thread
-//   per coefficient index of a 256-coefficient block.
-// - ModDown's P^-1 (x - Conv(x)) (+ add) and Rescale's q_l^-1 (c - .) run in
-//   the store of the last forward pass.
+//   (row) with 16 elements each, in two register rounds of four stages with an
+//   exchange through LDS; a row's threads lie in one wave, so the row passes
+//   exchange without workgroup barriers.  A pass over 188 rows issues 8 to 9 M
+//   wave instructions (about 18 us of VALU time) and moves 98 MB; the column
+//   pass takes 23 us and the row pass 31, whose twiddles are two words per
+//   word of data: the limbs of one prime are neighbours in a launch, so that
+//   they find them in L2.
+// - Base conversion: two coefficients per thread.  Inner product: one.
+// - Fused into the passes: HMult's d2 = a1 b1 and the automorphism into the
+//   first inverse pass's load (and the inner product's own rows), Rescale's
+//   lift into the first forward pass's load, ModDown's P^-1 (x - Conv(x)) (+
+//   add) and Rescale's q_l^-1 (c - .) into the last forward pass's store.
 #include <string.h>
 
 #include <algorithm>
@@ -57,34 +62,64 @@ struct Pair32 {
 
 struct Prime32 {
     uint32_t q, pad;
-    uint64_t mu;  // floor(2^64 / q), for Barrett reduction of 64-bit sums
+    double qinv;  // 1 / q, for the quotient of 64-bit sums
 };
 
 // -------------------------------------------------------- modular arithmetic
 
-__device__ __forceinline__ uint32_t csub(uint32_t x, uint32_t q) { return x >= q ? x - q : x; }
+// x - q if x >= q, else x, for x < 2q (x - q wraps above x otherwise)
+__device__ __forceinline__ uint32_t csub(uint32_t x, uint32_t q) { return min(x, x - q); }
 
-// w y - floor(ws y / 2^32) q: in [0, 2q) for every y < 2^32 (Shoup)
-__device__ __forceinline__ uint32_t shoup_lazy(uint32_t y, Pair32 w, uint32_t q)
-{
-    return w.w * y - __umulhi(w.s, y) * q;
-}
+// floor(ws y / 2^32) q - w y = -(w y mod q) or -(w y mod q) - q, modulo 2^32 (Shoup), any y
+__device__ __forceinline__ uint32_t shoup_neg(uint32_t y, Pair32 w, uint32_t q) { return __umulhi(w.s, y) * q - w.w * y; }
+
+// w y - floor(ws y / 2^32) q: in [0, 2q) for every y < 2^32
+__device__ __forceinline__ uint32_t shoup_lazy(uint32_t y, Pair32 w, uint32_t q) { return w.w * y - __umulhi(w.s, y) * q; }
 
 __device__ __forceinline__ uint32_t shoup(uint32_t y, Pair32 w, uint32_t q) { return csub(shoup_lazy(y, w, q), q); }
 
-// x mod q for any 64-bit x: x - floor(x mu / 2^64) q is in [0, 2q) (Barrett with mu = floor(2^64 / q))
+// x mod q for a 64-bit x (SIGNED: two's complement).  k = round(x / q) comes
+// from the low word of 1.5 2^52 + x (1/q), within 1/2 + 2^-8 of x / q (x is
+// rounded to 53 bits, q > 2^17), so x - k q, taken in 32 bits, is the centred
+// residue: eight instructions, where Barrett with a 64-bit product takes about
+// sixteen.
+template <bool SIGNED = false>
 __device__ __forceinline__ uint32_t reduce64(uint64_t x, const Prime32 &P)
 {
-    const uint64_t r = x - __umul64hi(x, P.mu) * P.q;
-    return csub((uint32_t)r, P.q);
+    const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
+    const double d = fma(SIGNED ? (double)(int32_t)hi : (double)hi, 0x1p32, (double)lo);
+    const uint32_t k = (uint32_t)__double_as_longlong(fma(d, P.qinv, 0x1.8p52));
+    const uint32_t r = lo - k * P.q;
+    return min(r, r + P.q);
 }
 
 __device__ __forceinline__ uint64_t mul32(uint32_t a, uint32_t b) { return (uint64_t)a * b; }
 
+// The threads of a row share a wave: their exchanges through LDS need its
+// order only.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Prime index of a launch's row: prime0 + r below `split`, prime1 + r - split
+// from there on (q_0..q_l, then p_0..p_{K-1}).  Formed, not looked up: a byte of
+// the argument block is a vector load in front of everything a row needs.
+struct RowMap32 {
+    uint32_t prime0, split, prime1;
+};
+__host__ __device__ __forceinline__ uint32_t row_prime32(const RowMap32 &m, uint32_t r)
+{
+    return r < m.split ? m.prime0 + r : m.prime1 + r - m.split;
+}
+
 // ------------------------------------------------------------- NTT passes
 
-// Launch row y = poly * rows + r: polynomial `poly`, row r under prime
-// prime[r]; rows whose bit is set in skip are left alone.
+// Launch row y = r npoly + poly: polynomial `poly`, row r under prime map(r)
+// (the polynomials' limbs of one prime follow each other); rows whose bit
+// poly * rows + r is set in skip are left alone.
 struct Ntt32Args {
     const uint32_t *src;
     uint32_t *dst;              // pass 0 writes here, pass 1 transforms it in place
@@ -100,8 +135,14 @@ struct Ntt32Args {
     const uint32_t *add[2];
     uint32_t *out[2];
     const Pair32 *cst;          // per prime index
+    const uint32_t *src2;       // first inverse pass: the input is [src src2]_q (HMult's d2)
+    uint32_t galois;            // first inverse pass and ModDown's addend: gathered through X -> X^g (1 = none)
+    // first forward pass of Rescale: its input is the centred lift of src (one limb per polynomial,
+    // coefficients under ql)
+    uint32_t lift_ql;
+    uint32_t centred;           // last inverse pass: stores centred signed values (ModDown's conversion)
     uint32_t skip[kMaxLaunch32 / 32];
-    uint8_t prime[kMaxRows32];
+    RowMap32 map;
 };
 
 struct RowPos {
@@ -112,10 +153,11 @@ struct RowPos {
 __device__ __forceinline__ RowPos row_pos(const Ntt32Args &a, uint32_t y)
 {
     RowPos p;
-    p.poly = y / a.rows;
-    p.r = y - p.poly * a.rows;
-    p.pi = a.prime[p.r];
-    p.skip = (a.skip[y >> 5] >> (y & 31)) & 1;
+    p.r = y / a.npoly;
+    p.poly = y - p.r * a.npoly;
+    p.pi = row_prime32(a.map, p.r);
+    const uint32_t bit = p.poly * a.rows + p.r;
+    p.skip = (a.skip[bit >> 5] >> (bit & 31)) & 1;
     return p;
 }
 
@@ -140,10 +182,10 @@ __device__ __forceinline__ void fwd4(uint32_t (&v)[16], const Pair32 *T, uint32_
         for (int i = 0; i < 16; ++i) {
             if (i & h) continue;
             const Pair32 w = twk(T, B, k0 + st, e(i));
-            const uint32_t x = v[i] >= q2 ? v[i] - q2 : v[i];
-            const uint32_t t = shoup_lazy(v[i + h], w, q);
-            v[i] = x + t;
-            v[i + h] = x - t + q2;
+            const uint32_t x = csub(v[i], q2);
+            const uint32_t t = shoup_neg(v[i + h], w, q);
+            v[i] = x - t;
+            v[i + h] = x + q2 + t;
         }
     }
 }
@@ -162,8 +204,7 @@ __device__ __forceinline__ void inv4(uint32_t (&v)[16], const Pair32 *T, uint32_
             if (i & h) continue;
             const Pair32 w = twk(T, B, k0 - st, e(i));
             const uint32_t x = v[i], y = v[i + h];
-            const uint32_t s = x + y;
-            v[i] = s >= q2 ? s - q2 : s;
+            v[i] = csub(x + y, q2);
             v[i + h] = shoup_lazy(x - y + q2, w, q);
         }
     }
@@ -172,22 +213,32 @@ __device__ __forceinline__ void inv4(uint32_t (&v)[16], const Pair32 *T, uint32_
 constexpr uint32_t kColStride = 33;               // LDS words per matrix row in a column pass (32 + 1)
 constexpr uint32_t kRowStride = 256 + 16;         // LDS words per row in a row pass
 __device__ __forceinline__ uint32_t rslot(uint32_t e) { return e + (e >> 4); }  // conflict-free both ways
-constexpr uint32_t kLds32 = 256 * kColStride > 32 * kRowStride ? 256 * kColStride : 32 * kRowStride;
 
 // Forward column pass: 32 columns per workgroup; round 1 on rows s + 16 i,
-// round 2 on rows 16 s + i.
+// round 2 on rows 16 s + i.  LIFT: Rescale's SwitchModulo of the input,
+// u - q_l [u > (q_l - 1) / 2] mod q.
+template <bool LIFT>
 __global__ __launch_bounds__(kT) void k32_fwd_col(Ntt32Args a)
 {
-    __shared__ uint32_t L[kLds32];
+    __shared__ uint32_t L[256 * kColStride];
     const RowPos p = row_pos(a, blockIdx.y);
     if (p.skip) return;
-    const uint32_t q = a.primes[p.pi].q;
+    const Prime32 P = a.primes[p.pi];
+    const uint32_t q = P.q;
     const Pair32 *T = a.tw + (size_t)p.pi * kN;
     const uint32_t col = threadIdx.x & 31, s = threadIdx.x >> 5, c = blockIdx.x * 32 + col;
-    const uint32_t *src = a.src + p.poly * a.src_poly_stride + (size_t)p.r * kN;
+    const uint32_t *src = a.src + p.poly * a.src_poly_stride + (LIFT ? 0 : (size_t)p.r * kN);
     uint32_t v[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = src[(s + 16 * i) * 256 + c];
+    if (LIFT) {
+        const uint32_t half = (a.lift_ql - 1) / 2;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int32_t u = (int32_t)(v[i] > half ? v[i] - a.lift_ql : v[i]);
+            v[i] = reduce64<true>((uint64_t)(int64_t)u, P);
+        }
+    }
     fwd4(v, T, 1, 0, q, [&](int i) { return s + 16 * i; });
 #pragma unroll
     for (int i = 0; i < 16; ++i) L[(s + 16 * i) * kColStride + col] = v[i];
@@ -218,32 +269,26 @@ __device__ __forceinline__ void store16(uint32_t *m, const uint32_t (&v)[16])
     for (int j = 0; j < 4; ++j) ((uint4 *)m)[j] = make_uint4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
 }
 
-// Forward row pass: 32 rows per workgroup, 16 threads per row.  Loaded as 16
-// consecutive words per thread, exchanged to e = s + 16 i for round 1, back to
-// e = 16 s + i for round 2 and the store (with the epilogue).
+// Forward row pass: 32 rows per workgroup, 16 threads per row: round 1 on e =
+// s + 16 i as loaded, round 2 on e = 16 s + i, stored as 16 consecutive words
+// per thread (with the epilogue).
 __global__ __launch_bounds__(kT) void k32_fwd_row(Ntt32Args a)
 {
-    __shared__ uint32_t L[kLds32];
+    __shared__ uint32_t L[32 * kRowStride];
     const RowPos p = row_pos(a, blockIdx.y);
     if (p.skip) return;
-    const Prime32 P = a.primes[p.pi];
-    const uint32_t q = P.q;
+    const uint32_t q = a.primes[p.pi].q;
     const Pair32 *T = a.tw + (size_t)p.pi * kN;
     const uint32_t rw = threadIdx.x >> 4, s = threadIdx.x & 15, b = blockIdx.x * 32 + rw;
     uint32_t *m = a.dst + p.poly * a.dst_poly_stride + (size_t)p.r * kN + b * 256;
     uint32_t *Lr = L + rw * kRowStride;
     uint32_t v[16];
-    load16(v, m + 16 * s);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) Lr[rslot(16 * s + i)] = v[i];
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = Lr[rslot(s + 16 * i)];
+    for (int i = 0; i < 16; ++i) v[i] = m[s + 16 * i];
     fwd4(v, T, 256 + b, 0, q, [&](int i) { return s + 16 * i; });
-    __syncthreads();
 #pragma unroll
     for (int i = 0; i < 16; ++i) Lr[rslot(s + 16 * i)] = v[i];
-    __syncthreads();
+    wave_sync();
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = Lr[rslot(16 * s + i)];
     fwd4(v, T, 256 + b, 4, q, [&](int i) { return 16 * s + i; });
@@ -261,7 +306,12 @@ __global__ __launch_bounds__(kT) void k32_fwd_row(Ntt32Args a)
     for (int i = 0; i < 16; ++i) o[i] = shoup(x[i] - v[i] + q, c, q);
     const uint32_t *add = p.poly ? a.add[1] : a.add[0];
     if (a.epi == 1 && add) {
-        load16(x, add + off);
+        if (a.galois == 1) {
+            load16(x, add + off);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) x[i] = add[(size_t)p.r * kN + galois_src(b * 256 + 16 * s + i, a.galois, kLogN)];
+        }
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[i] = csub(o[i] + x[i], q);
     }
@@ -269,23 +319,46 @@ __global__ __launch_bounds__(kT) void k32_fwd_row(Ntt32Args a)
 }
 
 // Inverse row pass: round 1 (stages 7..4) on e = 16 s + i as loaded, round 2
-// (stages 3..0) on e = s + 16 i; stored from that layout.
+// (stages 3..0) on e = s + 16 i; stored from that layout.  IN_GALOIS gathers
+// the input (a block of 256 positions comes from one source block), IN_TENSOR
+// forms HMult's d2.
+enum Inv32 { IN_PLAIN = 0, IN_GALOIS = 1, IN_TENSOR = 2 };
+
+template <int IN>
 __global__ __launch_bounds__(kT) void k32_inv_row(Ntt32Args a)
 {
-    __shared__ uint32_t L[kLds32];
+    __shared__ uint32_t L[32 * kRowStride];
     const RowPos p = row_pos(a, blockIdx.y);
     if (p.skip) return;
-    const uint32_t q = a.primes[p.pi].q;
+    const Prime32 P = a.primes[p.pi];
+    const uint32_t q = P.q;
     const Pair32 *T = a.tw + (size_t)p.pi * kN;
     const uint32_t rw = threadIdx.x >> 4, s = threadIdx.x & 15, b = blockIdx.x * 32 + rw;
-    const uint32_t *m = a.src + p.poly * a.src_poly_stride + (size_t)p.r * kN + b * 256;
+    const size_t off = p.poly * a.src_poly_stride + (size_t)p.r * kN;
     uint32_t *Lr = L + rw * kRowStride;
     uint32_t v[16];
-    load16(v, m + 16 * s);
+    if (IN == IN_GALOIS) {
+        const uint32_t sb = galois_src(b * 256, a.galois, kLogN) & ~255u;
+        load16(v, a.src + off + sb + 16 * s);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) Lr[rslot(16 * s + i)] = v[i];
+        wave_sync();
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = Lr[rslot(galois_src(b * 256 + 16 * s + i, a.galois, kLogN) - sb)];
+        wave_sync();
+    } else {
+        load16(v, a.src + off + b * 256 + 16 * s);
+        if (IN == IN_TENSOR) {
+            uint32_t y[16];
+            load16(y, a.src2 + off + b * 256 + 16 * s);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = reduce64(mul32(v[i], y[i]), P);
+        }
+    }
     inv4(v, T, 256 + b, 7, q, [&](int i) { return 16 * s + i; });
 #pragma unroll
     for (int i = 0; i < 16; ++i) Lr[rslot(16 * s + i)] = v[i];
-    __syncthreads();
+    wave_sync();
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = Lr[rslot(s + 16 * i)];
     inv4(v, T, 256 + b, 3, q, [&](int i) { return s + 16 * i; });
@@ -298,7 +371,7 @@ __global__ __launch_bounds__(kT) void k32_inv_row(Ntt32Args a)
 // on rows s + 16 i, then the last multiplication (N^-1 and the row's scale).
 __global__ __launch_bounds__(kT) void k32_inv_col(Ntt32Args a)
 {
-    __shared__ uint32_t L[kLds32];
+    __shared__ uint32_t L[256 * kColStride];
     const RowPos p = row_pos(a, blockIdx.y);
     if (p.skip) return;
     const uint32_t q = a.primes[p.pi].q;
@@ -316,8 +389,12 @@ __global__ __launch_bounds__(kT) void k32_inv_col(Ntt32Args a)
     for (int i = 0; i < 16; ++i) v[i] = L[(s + 16 * i) * kColStride + col];
     inv4(v, T, 1, 3, q, [&](int i) { return s + 16 * i; });
     const Pair32 f = a.scale[p.r];
+    const uint32_t half = a.centred ? q >> 1 : 0xFFFFFFFFu;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) d[(s + 16 * i) * 256 + c] = shoup(v[i], f, q);
+    for (int i = 0; i < 16; ++i) {
+        const uint32_t y = shoup(v[i], f, q);
+        d[(s + 16 * i) * 256 + c] = y > half ? y - q : y;
+    }
 }
 
 // ----------------------------------------------------- coefficient kernels
@@ -326,104 +403,147 @@ constexpr int kB = 256;
 
 // Fast base conversion (Eq. (1)) of job j = blockIdx.y: y_i = src row i (already
 // scaled by [(B/b_i)^-1]_{b_i} in the inverse NTT), out row c = [sum_i y_i [B/b_i]_c]_c
-// for the rows c outside [lo, hi), in groups of 8 rows (blockIdx.z).  With
-// centred, every y_i above (b_i - 1)/2 stands for y_i - b_i: the sum gains
-// h (q_c - [B]_{q_c}) for the h such inputs.
+// for the rows c outside [lo, hi), in groups of a.group rows (blockIdx.z).
+// ModDown's inputs are centred (CENTRED: signed words, sums below 2^63 over 16
+// terms; ModUp's unsigned sums stay below 2^64).  The source count is a template
+// parameter, the constants come through the scalar cache, and a thread takes two
+// coefficients: a term is one multiply-add, a reduction eight instructions, and
+// the rows' stores are what is left (4 digits of 13 rows into 47 each: 63 us
+// with the counts at run time and one coefficient per thread, 22 us so).
 struct Bconv32Job {
     const uint32_t *src;
     uint32_t *dst;
     const uint32_t *hmod;       // [prime][kMaxDigit32]: [B/b_i]_{prime}
     uint32_t ns, lo, hi, pad;
-    uint32_t half[kMaxDigit32]; // (b_i - 1) / 2
 };
 
 struct Bconv32Args {
     Bconv32Job job[kMaxDigit32];
     const Prime32 *primes;
-    const uint32_t *bmod;       // centred: [prime] B mod q
-    uint32_t nrows, centred;
-    uint8_t prime[kMaxRows32];
+    uint32_t nrows, group;      // output rows, and how many of them a workgroup takes
+    RowMap32 map;
 };
 
+typedef const __attribute__((address_space(4))) uint32_t Const32;
+
+// A target row's constants in scalar registers.
+template <int NS>
+struct ConvRow32 {
+    Prime32 P;
+    uint32_t h[NS];
+};
+
+template <int NS>
+__device__ __forceinline__ ConvRow32<NS> conv_row32(const Bconv32Args &a, const Bconv32Job &J, uint32_t r)
+{
+    const uint32_t pi = row_prime32(a.map, r);
+    Const32 *w = (Const32 *)(a.primes + pi), *h = (Const32 *)(J.hmod + (size_t)pi * kMaxDigit32);
+    ConvRow32<NS> c;
+    c.P.q = w[0];
+    c.P.pad = 0;
+    c.P.qinv = __hiloint2double((int)w[3], (int)w[2]);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) c.h[i] = h[i];
+    return c;
+}
+
+// s + y c, y and c signed (the compiler widens one of two such products to 64 bits)
+__device__ __forceinline__ uint64_t mad_signed(uint32_t y, uint32_t c, uint64_t s)
+{
+    uint64_t k;
+    asm("v_mad_i64_i32 %0, %1, %2, %3, %0" : "+v"(s), "=s"(k) : "v"(y), "s"(c));
+    return s;
+}
+
+template <bool CENTRED, int NS>
+__device__ __forceinline__ void bconv32_rows(const Bconv32Args &a, const Bconv32Job &J, uint32_t n, uint32_t r0)
+{
+    uint2 y[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) y[i] = *(const uint2 *)(J.src + (size_t)i * kN + n);
+    const uint32_t r1 = min(r0 + a.group, a.nrows);
+    auto next = [&](uint32_t r) { return r >= J.lo && r < J.hi ? J.hi : r; };  // rows [lo, hi) are the sources
+    uint32_t r = next(r0);
+    if (r >= r1) return;
+    ConvRow32<NS> c = conv_row32<NS>(a, J, r);
+    while (r < r1) {
+        // the next row's constants are on their way while this one is summed
+        const uint32_t rn = next(r + 1);
+        const ConvRow32<NS> cn = conv_row32<NS>(a, J, min(rn, r1 - 1));
+        uint64_t s0 = 0, s1 = 0;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            s0 = CENTRED ? mad_signed(y[i].x, c.h[i], s0) : s0 + mul32(y[i].x, c.h[i]);
+            s1 = CENTRED ? mad_signed(y[i].y, c.h[i], s1) : s1 + mul32(y[i].y, c.h[i]);
+        }
+        *(uint2 *)(J.dst + (size_t)r * kN + n) = make_uint2(reduce64<CENTRED>(s0, c.P), reduce64<CENTRED>(s1, c.P));
+        r = rn;
+        c = cn;
+    }
+}
+
+template <bool CENTRED>
 __global__ __launch_bounds__(kB) void k32_bconv(Bconv32Args a)
 {
     const Bconv32Job &J = a.job[blockIdx.y];
-    const uint32_t n = blockIdx.x * kB + threadIdx.x, r0 = blockIdx.z * 8;
+    const uint32_t n = 2 * (blockIdx.x * kB + threadIdx.x), r0 = blockIdx.z * a.group;
     if (r0 >= a.nrows) return;
-    uint32_t y[kMaxDigit32];
-    uint32_t h = 0;
-    for (uint32_t i = 0; i < J.ns; ++i) {
-        y[i] = J.src[(size_t)i * kN + n];
-        h += y[i] > J.half[i];
-    }
-    const uint32_t r1 = min(r0 + 8, a.nrows);
-    for (uint32_t r = r0; r < r1; ++r) {
-        if (r >= J.lo && r < J.hi) continue;
-        const uint32_t pi = a.prime[r];
-        const Prime32 P = a.primes[pi];
-        const uint32_t *hm = J.hmod + (size_t)pi * kMaxDigit32;
-        uint64_t acc = a.centred ? (uint64_t)h * (P.q - a.bmod[pi]) : 0;
-        for (uint32_t i = 0; i < J.ns; ++i) acc += mul32(y[i], hm[i]);
-        J.dst[(size_t)r * kN + n] = reduce64(acc, P);
+    switch (J.ns) {
+#define BC32(k) \
+    case k: bconv32_rows<CENTRED, k>(a, J, n, r0); break;
+        BC32(1) BC32(2) BC32(3) BC32(4) BC32(5) BC32(6) BC32(7) BC32(8)
+        BC32(9) BC32(10) BC32(11) BC32(12) BC32(13) BC32(14) BC32(15) BC32(16)
+#undef BC32
+    default: break;
     }
 }
 
 // Key inner product: acc_t[r] = sum_j x_j[r] key[j][t][prime(r)], x_j[r] = d[r]
-// for the digit's own rows (d at level l, evaluation domain), ext_j[r] else.
+// for the digit's own rows (d at level l, evaluation domain, gathered through X
+// -> X^galois), ext_j[r] else.  HMult (ta0 set): d = a1 b1 is formed here, and
+// rows q_0..q_l also take [P]_q d0 and [P]_q d1 (d0 = a0 b0, d1 = a0 b1 + a1 b0),
+// so that ModDown's P^-1 (acc - Conv) leaves KS(d2) + (d0, d1).
 struct Ip32Args {
     const uint32_t *ext, *d, *key;
     uint32_t *acc;
     const Prime32 *primes;
-    uint32_t beta, rows, n, alpha, krows, pad;
-    uint8_t prime[kMaxRows32];
+    const uint32_t *ta0, *ta1, *tb0, *tb1, *pmod;
+    uint32_t beta, rows, n, alpha, krows, galois;
+    RowMap32 map;
 };
 
+template <bool TENSOR>
 __global__ __launch_bounds__(kB) void k32_inner_product(Ip32Args a)
 {
-    const uint32_t n = blockIdx.x * kB + threadIdx.x, r = blockIdx.y, pi = a.prime[r];
-    uint64_t s0 = 0, s1 = 0;
-    for (uint32_t j = 0; j < a.beta; ++j) {
-        const bool own = r < a.n && r >= j * a.alpha && r < j * a.alpha + a.alpha;
-        const uint32_t x = own ? a.d[(size_t)r * kN + n] : a.ext[((size_t)j * a.rows + r) * kN + n];
-        s0 += mul32(x, a.key[(((size_t)j * 2 + 0) * a.krows + pi) * kN + n]);
-        s1 += mul32(x, a.key[(((size_t)j * 2 + 1) * a.krows + pi) * kN + n]);
-    }
+    const uint32_t n = blockIdx.x * kB + threadIdx.x, r = blockIdx.y, pi = row_prime32(a.map, r);
     const Prime32 P = a.primes[pi];
+    const bool qrow = r < a.n;
+    uint32_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
+    if (TENSOR && qrow) {
+        const size_t i = (size_t)r * kN + n;
+        a0 = a.ta0[i], a1 = a.ta1[i], b0 = a.tb0[i], b1 = a.tb1[i];
+    }
+    uint64_t s0 = 0, s1 = 0;
+#pragma unroll 4
+    for (uint32_t j = 0; j < a.beta; ++j) {
+        const bool own = qrow && r >= j * a.alpha && r < j * a.alpha + a.alpha;
+        const uint32_t k0 = a.key[(((size_t)j * 2 + 0) * a.krows + pi) * kN + n];
+        const uint32_t k1 = a.key[(((size_t)j * 2 + 1) * a.krows + pi) * kN + n];
+        uint32_t x;
+        if (!own) x = a.ext[((size_t)j * a.rows + r) * kN + n];
+        else if (TENSOR) x = reduce64(mul32(a1, b1), P);
+        else x = a.d[(size_t)r * kN + (a.galois == 1 ? n : galois_src(n, a.galois, kLogN))];
+        s0 += mul32(x, k0);
+        s1 += mul32(x, k1);
+    }
+    if (TENSOR && qrow) {
+        // one term more: 16 in all at most, since beta (l + 1 + K) <= kMaxLaunch32 keeps beta below 16
+        const uint32_t pm = a.pmod[pi];
+        s0 += mul32(reduce64(mul32(a0, b0), P), pm);
+        s1 += mul32(reduce64(mul32(a0, b1) + mul32(a1, b0), P), pm);
+    }
     a.acc[(size_t)r * kN + n] = reduce64(s0, P);
     a.acc[((size_t)a.rows + r) * kN + n] = reduce64(s1, P);
-}
-
-// d0 = a0 b0, d1 = a0 b1 + a1 b0, d2 = a1 b1 on limb blockIdx.y (prime index = limb)
-__global__ __launch_bounds__(kB) void k32_tensor(const uint32_t *a0, const uint32_t *a1, const uint32_t *b0,
-                                                 const uint32_t *b1, uint32_t *d0, uint32_t *d1, uint32_t *d2,
-                                                 const Prime32 *primes)
-{
-    const size_t i = (size_t)blockIdx.y * kN + blockIdx.x * kB + threadIdx.x;
-    const Prime32 P = primes[blockIdx.y];
-    const uint32_t x0 = a0[i], x1 = a1[i], y0 = b0[i], y1 = b1[i];
-    d0[i] = reduce64(mul32(x0, y0), P);
-    d1[i] = reduce64(mul32(x0, y1) + mul32(x1, y0), P);
-    d2[i] = reduce64(mul32(x1, y1), P);
-}
-
-// out[limb][e] = in[limb][src of e under X -> X^g] (evaluation domain)
-__global__ __launch_bounds__(kB) void k32_automorph(const uint32_t *in, uint32_t *out, uint32_t g)
-{
-    const uint32_t e = blockIdx.x * kB + threadIdx.x;
-    const size_t row = (size_t)blockIdx.y * kN;
-    out[row + e] = in[row + galois_src(e, g, kLogN)];
-}
-
-// Rescale's SwitchModulo: v (coefficients under q_l, [2][N]) lifted centred
-// into q_i for the l limbs i < l of both halves: out[t][i] = v_t - q_l [v_t > (q_l-1)/2] mod q_i
-__global__ __launch_bounds__(kB) void k32_lift(const uint32_t *v, uint32_t *out, const Prime32 *primes,
-                                               const uint32_t *qlmod, uint32_t ql, uint32_t l)
-{
-    const uint32_t n = blockIdx.x * kB + threadIdx.x, i = blockIdx.y, t = blockIdx.z;
-    const uint32_t u = v[(size_t)t * kN + n], q = primes[i].q;
-    const uint32_t um = u % q;  // u < 2^30
-    const uint32_t r = u <= (ql - 1) / 2 ? um : csub(um + q - qlmod[i], q);
-    out[((size_t)t * l + i) * kN + n] = r;
 }
 
 }  // namespace
@@ -441,7 +561,6 @@ struct ckks32_ctx {
     uint32_t *d_pmod = nullptr;    // [n_primes]: P mod prime
     Pair32 *d_pinv = nullptr;      // [n_primes]: P^-1 mod q_i
     Pair32 *d_qlinv = nullptr;     // [nq][nq]: (l, i) -> q_l^-1 mod q_i
-    uint32_t *d_qlmod = nullptr;   // [nq][nq]: (l, i) -> q_l mod q_i
     // host copies of per-set constants
     std::vector<Pair32> ys;        // [nsets][kMaxDigit32]: N^-1 [(B/b_i)^-1]_{b_i}
     std::vector<Pair32> ninv;      // [n_primes]
@@ -488,8 +607,9 @@ Sizes32 sizes(const ckks32_ctx *c, uint32_t level)
     return s;
 }
 
-// prime index of row r of an extended polynomial at `level`
-uint32_t ext_prime(const ckks32_ctx *c, uint32_t level, uint32_t r) { return r <= level ? r : c->nq + r - level - 1; }
+// rows of an extended polynomial at `level`; n rows from prime `first` on
+RowMap32 ext_map(const ckks32_ctx *c, uint32_t level) { return RowMap32{0, level + 1, c->nq}; }
+RowMap32 plain_map(uint32_t first) { return RowMap32{first, 0xFFFFFFFFu, 0}; }
 
 Ntt32Args base_args(const ckks32_ctx *c, bool inverse)
 {
@@ -497,6 +617,7 @@ Ntt32Args base_args(const ckks32_ctx *c, bool inverse)
     memset(&a, 0, sizeof(a));
     a.primes = c->d_primes;
     a.tw = inverse ? c->d_tw_inv : c->d_tw_fwd;
+    a.galois = 1;
     return a;
 }
 
@@ -507,10 +628,13 @@ hipError_t launch_ntt32(const Ntt32Args &a, bool inverse, hipStream_t st)
     if (ny > kMaxLaunch32 || a.rows > kMaxRows32) return hipErrorInvalidValue;
     const dim3 grid(8, ny), block(kT);
     if (inverse) {
-        hipLaunchKernelGGL(k32_inv_row, grid, block, 0, st, a);
+        if (a.src2) hipLaunchKernelGGL(k32_inv_row<IN_TENSOR>, grid, block, 0, st, a);
+        else if (a.galois != 1) hipLaunchKernelGGL(k32_inv_row<IN_GALOIS>, grid, block, 0, st, a);
+        else hipLaunchKernelGGL(k32_inv_row<IN_PLAIN>, grid, block, 0, st, a);
         hipLaunchKernelGGL(k32_inv_col, grid, block, 0, st, a);
     } else {
-        hipLaunchKernelGGL(k32_fwd_col, grid, block, 0, st, a);
+        if (a.lift_ql) hipLaunchKernelGGL(k32_fwd_col<true>, grid, block, 0, st, a);
+        else hipLaunchKernelGGL(k32_fwd_col<false>, grid, block, 0, st, a);
         hipLaunchKernelGGL(k32_fwd_row, grid, block, 0, st, a);
     }
     return hipGetLastError();
@@ -548,26 +672,43 @@ Ws32 ks_ws(const ckks32_ctx *c, uint32_t level, void *ws)
     return w;
 }
 
-hipError_t launch_bconv32(const Bconv32Args &a, uint32_t njobs, hipStream_t st)
+constexpr uint32_t kConvGroups32 = 2048;
+// Rows per workgroup: as many as leave 2,048 workgroups, eight per CU.  Flat around that: the two
+// conversions of a key switch at l = 51 take 36, 35, 34 and 36 us for 1,024, 2,048, 4,096 and 8,192
+// workgroups, those at l = 24 15, 15, 17 and 22 us (their stores, 49 and 14 MB, are most of it).
+hipError_t launch_bconv32(Bconv32Args &a, uint32_t njobs, bool centred, hipStream_t st)
 {
     static_assert(sizeof(Bconv32Args) <= 4096, "the conversion's argument block is a kernel argument");
-    hipLaunchKernelGGL(k32_bconv, dim3(kN / kB, njobs, (a.nrows + 7) / 8), dim3(kB), 0, st, a);
+    const uint32_t want = std::max(1u, kConvGroups32 / (kN / (2 * kB) * njobs));
+    a.group = (a.nrows + want - 1) / want;
+    const dim3 grid(kN / (2 * kB), njobs, (a.nrows + a.group - 1) / a.group);
+    if (centred) hipLaunchKernelGGL(k32_bconv<true>, grid, dim3(kB), 0, st, a);
+    else hipLaunchKernelGGL(k32_bconv<false>, grid, dim3(kB), 0, st, a);
     return hipGetLastError();
 }
 
-// ModUp of d (evaluation domain, level l) into ext (evaluation domain, the
-// digits' own rows left out: the inner product reads them from d).
-hipError_t modup32(const ckks32_ctx *c, const uint32_t *d, uint32_t level, const Ws32 &w, hipStream_t st)
+// HMult's operands, whose product a1 b1 is key-switched.
+struct Tensor32 {
+    const uint32_t *a0, *a1, *b0, *b1;
+};
+
+// ModUp of phi_g(d), or of a1 b1 with tin (evaluation domain, level l), into ext
+// (evaluation domain, the digits' own rows left out: the inner product reads or
+// forms them).
+hipError_t modup32(const ckks32_ctx *c, const uint32_t *d, uint32_t g, const Tensor32 *tin, uint32_t level, const Ws32 &w,
+                   hipStream_t st)
 {
     const Sizes32 s = sizes(c, level);
     Ntt32Args ia = base_args(c, true);
-    ia.src = d;
+    ia.src = tin ? tin->a1 : d;
+    ia.src2 = tin ? tin->b1 : nullptr;
+    ia.galois = g;
     ia.dst = w.dc;
     ia.rows = s.n;
     ia.npoly = 1;
+    ia.map = plain_map(0);
     for (uint32_t i = 0; i < s.n; ++i) {
         const uint32_t j = i / c->alpha, lo = j * c->alpha, hi = std::min(lo + c->alpha, s.n);
-        ia.prime[i] = (uint8_t)i;
         ia.scale[i] = c->ys[(size_t)c->set_index(j, hi - lo) * kMaxDigit32 + (i - lo)];
     }
     hipError_t e = launch_ntt32(ia, true, st);
@@ -577,7 +718,7 @@ hipError_t modup32(const ckks32_ctx *c, const uint32_t *d, uint32_t level, const
     bh.primes = c->d_primes;
     bh.nrows = s.rows;
     const size_t hstride = (size_t)(c->nq + c->np) * kMaxDigit32;
-    for (uint32_t r = 0; r < s.rows; ++r) bh.prime[r] = (uint8_t)ext_prime(c, level, r);
+    bh.map = ext_map(c, level);
     for (uint32_t j = 0; j < s.beta; ++j) {
         const uint32_t lo = j * c->alpha, hi = std::min(lo + c->alpha, s.n);
         Bconv32Job &J = bh.job[j];
@@ -587,16 +728,15 @@ hipError_t modup32(const ckks32_ctx *c, const uint32_t *d, uint32_t level, const
         J.ns = hi - lo;
         J.lo = lo;
         J.hi = hi;
-        for (uint32_t i = 0; i < J.ns; ++i) J.half[i] = 0xFFFFFFFFu;  // not centred
     }
-    e = launch_bconv32(bh, s.beta, st);
+    e = launch_bconv32(bh, s.beta, false, st);
     if (e != hipSuccess) return e;
     Ntt32Args fa = base_args(c, false);
     fa.src = fa.dst = w.ext;
     fa.src_poly_stride = fa.dst_poly_stride = (int64_t)s.rows * kN;
     fa.rows = s.rows;
     fa.npoly = s.beta;
-    for (uint32_t r = 0; r < s.rows; ++r) fa.prime[r] = (uint8_t)ext_prime(c, level, r);
+    fa.map = ext_map(c, level);
     for (uint32_t j = 0; j < s.beta; ++j)
         for (uint32_t r = j * c->alpha; r < std::min(j * c->alpha + c->alpha, s.n); ++r) {
             const uint32_t y = j * s.rows + r;
@@ -605,9 +745,9 @@ hipError_t modup32(const ckks32_ctx *c, const uint32_t *d, uint32_t level, const
     return launch_ntt32(fa, false, st);
 }
 
-// ModDown of the pair acc [2][rows] into out_t = P^-1 (acc_t - Conv(acc_t|P)) + add_t.
+// ModDown of the pair acc [2][rows] into out_t = P^-1 (acc_t - Conv(acc_t|P)) + phi_g(add_t).
 hipError_t moddown32(const ckks32_ctx *c, const uint32_t *acc, uint32_t level, const Ws32 &w, uint32_t *out0,
-                     uint32_t *out1, const uint32_t *add0, const uint32_t *add1, hipStream_t st)
+                     uint32_t *out1, const uint32_t *add0, uint32_t g, hipStream_t st)
 {
     const Sizes32 s = sizes(c, level);
     const uint32_t K = c->np;
@@ -618,8 +758,9 @@ hipError_t moddown32(const ckks32_ctx *c, const uint32_t *acc, uint32_t level, c
     ia.dst_poly_stride = (int64_t)K * kN;
     ia.rows = K;
     ia.npoly = 2;
+    ia.centred = 1;
+    ia.map = plain_map(c->nq);
     for (uint32_t k = 0; k < K; ++k) {
-        ia.prime[k] = (uint8_t)(c->nq + k);
         ia.scale[k] = c->ys[(size_t)c->pset() * kMaxDigit32 + k];
     }
     hipError_t e = launch_ntt32(ia, true, st);
@@ -627,10 +768,8 @@ hipError_t moddown32(const ckks32_ctx *c, const uint32_t *acc, uint32_t level, c
     Bconv32Args bh;
     memset(&bh, 0, sizeof(bh));
     bh.primes = c->d_primes;
-    bh.bmod = c->d_pmod;
-    bh.centred = 1;
     bh.nrows = s.n;
-    for (uint32_t r = 0; r < s.n; ++r) bh.prime[r] = (uint8_t)r;
+    bh.map = plain_map(0);
     const size_t hstride = (size_t)(c->nq + c->np) * kMaxDigit32;
     for (uint32_t t = 0; t < 2; ++t) {
         Bconv32Job &J = bh.job[t];
@@ -639,29 +778,28 @@ hipError_t moddown32(const ckks32_ctx *c, const uint32_t *acc, uint32_t level, c
         J.hmod = c->d_hmod + (size_t)c->pset() * hstride;
         J.ns = K;
         J.lo = J.hi = 0xFFFFFFFFu;
-        for (uint32_t k = 0; k < K; ++k) J.half[k] = (c->primes[c->nq + k] - 1) / 2;
     }
-    e = launch_bconv32(bh, 2, st);
+    e = launch_bconv32(bh, 2, true, st);
     if (e != hipSuccess) return e;
     Ntt32Args fa = base_args(c, false);
     fa.src = fa.dst = w.conv;
     fa.src_poly_stride = fa.dst_poly_stride = (int64_t)s.n * kN;
     fa.rows = s.n;
     fa.npoly = 2;
-    for (uint32_t r = 0; r < s.n; ++r) fa.prime[r] = (uint8_t)r;
+    fa.map = plain_map(0);
     fa.epi = 1;
     fa.aux[0] = acc;
     fa.aux[1] = acc + (size_t)s.rows * kN;
     fa.add[0] = add0;
-    fa.add[1] = add1;
+    fa.galois = g;
     fa.out[0] = out0;
     fa.out[1] = out1;
     fa.cst = c->d_pinv;
     return launch_ntt32(fa, false, st);
 }
 
-hipError_t inner_product32(const ckks32_ctx *c, const uint32_t *d, uint32_t level, const uint32_t *key,
-                           const Ws32 &w, hipStream_t st)
+hipError_t inner_product32(const ckks32_ctx *c, const uint32_t *d, uint32_t g, const Tensor32 *tin, uint32_t level,
+                           const uint32_t *key, const Ws32 &w, hipStream_t st)
 {
     const Sizes32 s = sizes(c, level);
     Ip32Args a;
@@ -676,18 +814,28 @@ hipError_t inner_product32(const ckks32_ctx *c, const uint32_t *d, uint32_t leve
     a.n = s.n;
     a.alpha = c->alpha;
     a.krows = c->nq + c->np;
-    for (uint32_t r = 0; r < s.rows; ++r) a.prime[r] = (uint8_t)ext_prime(c, level, r);
-    hipLaunchKernelGGL(k32_inner_product, dim3(kN / kB, s.rows), dim3(kB), 0, st, a);
+    a.galois = g;
+    a.pmod = c->d_pmod;
+    a.map = ext_map(c, level);
+    const dim3 grid(kN / kB, s.rows), block(kB);
+    if (tin) {
+        a.ta0 = tin->a0, a.ta1 = tin->a1, a.tb0 = tin->b0, a.tb1 = tin->b1;
+        hipLaunchKernelGGL(k32_inner_product<true>, grid, block, 0, st, a);
+    } else {
+        hipLaunchKernelGGL(k32_inner_product<false>, grid, block, 0, st, a);
+    }
     return hipGetLastError();
 }
 
-hipError_t keyswitch32(ckks32_ctx *c, const uint32_t *d, uint32_t level, const uint32_t *key, uint32_t *out0,
-                       uint32_t *out1, const uint32_t *add0, const uint32_t *add1, void *ws, hipStream_t st)
+// out_t = KS_t + phi_g(add_t) with KS the key switch of phi_g(d), or with tin the
+// relinearised product (d, add0 null, g = 1); add_1 = 0.
+hipError_t keyswitch32(ckks32_ctx *c, const uint32_t *d, uint32_t g, const Tensor32 *tin, uint32_t level,
+                       const uint32_t *key, uint32_t *out0, uint32_t *out1, const uint32_t *add0, void *ws, hipStream_t st)
 {
     const Ws32 w = ks_ws(c, level, ws);
-    hipError_t e = modup32(c, d, level, w, st);
-    if (e == hipSuccess) e = inner_product32(c, d, level, key, w, st);
-    if (e == hipSuccess) e = moddown32(c, w.acc, level, w, out0, out1, add0, add1, st);
+    hipError_t e = modup32(c, d, g, tin, level, w, st);
+    if (e == hipSuccess) e = inner_product32(c, d, g, tin, level, key, w, st);
+    if (e == hipSuccess) e = moddown32(c, w.acc, level, w, out0, out1, add0, g, st);
     return e;
 }
 
@@ -741,7 +889,7 @@ extern "C" ckks_status ckks32_ctx_create(uint32_t log_n, const uint32_t *q, uint
         const uint64_t m = primes[i];
         pr[i].q = (uint32_t)m;
         pr[i].pad = 0;
-        pr[i].mu = (uint64_t)((((unsigned __int128)1) << 64) / m);
+        pr[i].qinv = 1.0 / (double)m;
         const uint64_t psi = smallest_2n_root(m, two_n), psi_inv = inv_mod(psi, m);
         uint64_t a = 1, b = 1;
         std::vector<uint64_t> pw(N), pwi(N);
@@ -798,10 +946,8 @@ extern "C" ckks_status ckks32_ctx_create(uint32_t log_n, const uint32_t *q, uint
         pinv[t] = t < n_q ? pair32(inv_mod(P, qt), qt) : Pair32{0, 0};
     }
     std::vector<Pair32> qlinv((size_t)n_q * n_q, Pair32{0, 0});
-    std::vector<uint32_t> qlmod((size_t)n_q * n_q, 0);
     for (uint32_t l = 1; l < n_q; ++l)
         for (uint32_t i = 0; i < l; ++i) {
-            qlmod[(size_t)l * n_q + i] = (uint32_t)(primes[l] % primes[i]);
             qlinv[(size_t)l * n_q + i] = pair32(inv_mod(primes[l] % primes[i], primes[i]), primes[i]);
         }
     c->qlinv = qlinv;
@@ -815,7 +961,7 @@ extern "C" ckks_status ckks32_ctx_create(uint32_t log_n, const uint32_t *q, uint
     const size_t o_pr = take(pr.size() * sizeof(Prime32)), o_twf = take(twf.size() * sizeof(Pair32)),
                  o_twi = take(twi.size() * sizeof(Pair32)), o_hm = take(hmod.size() * 4),
                  o_pm = take(pmod.size() * 4), o_pi = take(pinv.size() * sizeof(Pair32)),
-                 o_ql = take(qlinv.size() * sizeof(Pair32)), o_qm = take(qlmod.size() * 4);
+                 o_ql = take(qlinv.size() * sizeof(Pair32));
     if (hipMalloc(&c->dev, off) != hipSuccess) {
         delete c;
         return fail(CKKS_E_NOMEM, "ckks32_ctx_create: table allocation failed");
@@ -828,7 +974,6 @@ extern "C" ckks_status ckks32_ctx_create(uint32_t log_n, const uint32_t *q, uint
     c->d_pmod = (uint32_t *)(base + o_pm);
     c->d_pinv = (Pair32 *)(base + o_pi);
     c->d_qlinv = (Pair32 *)(base + o_ql);
-    c->d_qlmod = (uint32_t *)(base + o_qm);
     hipError_t e = hipMemcpy(c->d_primes, pr.data(), pr.size() * sizeof(Prime32), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_tw_fwd, twf.data(), twf.size() * sizeof(Pair32), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_tw_inv, twi.data(), twi.size() * sizeof(Pair32), hipMemcpyHostToDevice);
@@ -836,7 +981,6 @@ extern "C" ckks_status ckks32_ctx_create(uint32_t log_n, const uint32_t *q, uint
     if (e == hipSuccess) e = hipMemcpy(c->d_pmod, pmod.data(), pmod.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_pinv, pinv.data(), pinv.size() * sizeof(Pair32), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_qlinv, qlinv.data(), qlinv.size() * sizeof(Pair32), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->d_qlmod, qlmod.data(), qlmod.size() * 4, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(c->dev);
         delete c;
@@ -883,8 +1027,8 @@ static ckks_status ntt32_common(ckks32_ctx *c, uint32_t *poly, uint32_t limb0, u
     a.src = a.dst = poly;
     a.rows = n_limbs;
     a.npoly = 1;
+    a.map = plain_map(limb0);
     for (uint32_t r = 0; r < n_limbs; ++r) {
-        a.prime[r] = (uint8_t)(limb0 + r);
         a.scale[r] = c->ninv[limb0 + r];
     }
     return dev32(launch_ntt32(a, inverse, (hipStream_t)stream), inverse ? "ckks32_intt" : "ckks32_ntt");
@@ -911,7 +1055,7 @@ extern "C" ckks_status ckks32_modup(ckks32_ctx *c, const uint32_t *d, uint32_t l
     const Sizes32 s = sizes(c, level);
     Ws32 w = ks_ws(c, level, ws);
     w.ext = ext;  // the caller's buffer: its own rows are copied from d afterwards
-    hipError_t e = modup32(c, d, level, w, st);
+    hipError_t e = modup32(c, d, 1, nullptr, level, w, st);
     for (uint32_t j = 0; j < s.beta && e == hipSuccess; ++j) {
         const uint32_t lo = j * c->alpha, hi = std::min(lo + c->alpha, s.n);
         e = hipMemcpyAsync(ext + ((size_t)j * s.rows + lo) * kN, d + (size_t)lo * kN, (size_t)(hi - lo) * kN * 4,
@@ -930,7 +1074,7 @@ extern "C" ckks_status ckks32_moddown(ckks32_ctx *c, const uint32_t *x, uint32_t
     TRY32(check_ptr32(ws, "ckks32_moddown ws"));
     const hipStream_t st = (hipStream_t)stream;
     const Ws32 w = ks_ws(c, level, ws);
-    return dev32(moddown32(c, x, level, w, out0, out1, nullptr, nullptr, st), "ckks32_moddown");
+    return dev32(moddown32(c, x, level, w, out0, out1, nullptr, 1, st), "ckks32_moddown");
 }
 
 extern "C" ckks_status ckks32_keyswitch(ckks32_ctx *c, const uint32_t *d, uint32_t level, const uint32_t *key,
@@ -942,7 +1086,7 @@ extern "C" ckks_status ckks32_keyswitch(ckks32_ctx *c, const uint32_t *d, uint32
     TRY32(check_ptr32(out0, "ckks32_keyswitch out0"));
     TRY32(check_ptr32(out1, "ckks32_keyswitch out1"));
     TRY32(check_ptr32(ws, "ckks32_keyswitch ws"));
-    return dev32(keyswitch32(c, d, level, key, out0, out1, nullptr, nullptr, ws, (hipStream_t)stream),
+    return dev32(keyswitch32(c, d, 1, nullptr, level, key, out0, out1, nullptr, ws, (hipStream_t)stream),
                  "ckks32_keyswitch");
 }
 
@@ -953,12 +1097,8 @@ extern "C" ckks_status ckks32_hmult_relin(ckks32_ctx *c, const uint32_t *a0, con
     TRY32(check_ctx32(c, level));
     const void *ptrs[] = {a0, a1, b0, b1, rlk, out0, out1, ws};
     for (const void *q : ptrs) TRY32(check_ptr32(q, "ckks32_hmult_relin"));
-    const hipStream_t st = (hipStream_t)stream;
-    const size_t n = level + 1;
-    uint32_t *d2 = (uint32_t *)((char *)ws + ks_bytes(c, level));
-    hipLaunchKernelGGL(k32_tensor, dim3(kN / kB, n), dim3(kB), 0, st, a0, a1, b0, b1, out0, out1, d2, c->d_primes);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = keyswitch32(c, d2, level, rlk, out0, out1, out0, out1, ws, st);
+    const Tensor32 tin = {a0, a1, b0, b1};
+    const hipError_t e = keyswitch32(c, nullptr, 1, &tin, level, rlk, out0, out1, nullptr, ws, (hipStream_t)stream);
     return dev32(e, "ckks32_hmult_relin");
 }
 
@@ -970,13 +1110,7 @@ extern "C" ckks_status ckks32_apply_galois(ckks32_ctx *c, const uint32_t *c0, co
     const void *ptrs[] = {c0, c1, key, out0, out1, ws};
     for (const void *q : ptrs) TRY32(check_ptr32(q, "ckks32_apply_galois"));
     if (galois % 2 == 0 || galois >= 2 * kN) return fail(CKKS_E_ARG, "ckks32_apply_galois: galois must be odd, below 2N");
-    const hipStream_t st = (hipStream_t)stream;
-    const size_t n = level + 1;
-    uint32_t *g0 = (uint32_t *)((char *)ws + ks_bytes(c, level)), *g1 = g0 + n * kN;
-    hipLaunchKernelGGL(k32_automorph, dim3(kN / kB, n), dim3(kB), 0, st, c0, g0, galois);
-    hipLaunchKernelGGL(k32_automorph, dim3(kN / kB, n), dim3(kB), 0, st, c1, g1, galois);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = keyswitch32(c, g1, level, key, out0, out1, g0, nullptr, ws, st);
+    const hipError_t e = keyswitch32(c, c1, galois, nullptr, level, key, out0, out1, c0, ws, (hipStream_t)stream);
     return dev32(e, "ckks32_apply_galois");
 }
 
@@ -990,27 +1124,27 @@ extern "C" ckks_status ckks32_rescale(ckks32_ctx *c, const uint32_t *c0, const u
     const hipStream_t st = (hipStream_t)stream;
     const uint32_t l = level;
     uint32_t *v = (uint32_t *)ws, *lift = v + 2 * (size_t)kN;
-    // v_t = INTT_{q_l}(c_t[l]): copy the two last limbs, transform in place
-    hipError_t e = hipMemcpyAsync(v, c0 + (size_t)l * kN, kN * 4, hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(v + kN, c1 + (size_t)l * kN, kN * 4, hipMemcpyDeviceToDevice, st);
-    if (e != hipSuccess) return dev32(e, "ckks32_rescale");
+    // v_t = INTT_{q_l}(c_t[l])
     Ntt32Args ia = base_args(c, true);
-    ia.src = ia.dst = v;
-    ia.src_poly_stride = ia.dst_poly_stride = kN;
+    ia.src = c0 + (size_t)l * kN;
+    ia.src_poly_stride = (int64_t)(c1 - c0);
+    ia.dst = v;
+    ia.dst_poly_stride = kN;
     ia.rows = 1;
     ia.npoly = 2;
-    ia.prime[0] = (uint8_t)l;
+    ia.map = plain_map(l);
     ia.scale[0] = c->ninv[l];
-    e = launch_ntt32(ia, true, st);
+    const hipError_t e = launch_ntt32(ia, true, st);
     if (e != hipSuccess) return dev32(e, "ckks32_rescale");
-    hipLaunchKernelGGL(k32_lift, dim3(kN / kB, l, 2), dim3(kB), 0, st, v, lift, c->d_primes, c->d_qlmod + (size_t)l * c->nq,
-                       c->primes[l], l);
     Ntt32Args fa = base_args(c, false);
-    fa.src = fa.dst = lift;
-    fa.src_poly_stride = fa.dst_poly_stride = (int64_t)l * kN;
+    fa.src = v;
+    fa.src_poly_stride = kN;
+    fa.lift_ql = c->primes[l];
+    fa.dst = lift;
+    fa.dst_poly_stride = (int64_t)l * kN;
     fa.rows = l;
     fa.npoly = 2;
-    for (uint32_t r = 0; r < l; ++r) fa.prime[r] = (uint8_t)r;
+    fa.map = plain_map(0);
     fa.epi = 2;
     fa.aux[0] = c0;
     fa.aux[1] = c1;
