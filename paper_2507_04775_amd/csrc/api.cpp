@@ -80,9 +80,18 @@ hipError_t modup(const ckks_ctx *c, const uint64_t *d, uint32_t g, uint32_t leve
         hipError_t e = launch_ntt_stage(first, ia, s.n, st);
         return e == hipSuccess ? modup_from_coeffs(c, d, g, level, w.dc, w.ext, false, st) : e;
     }
-    hipError_t e = launch_split12_inv_rows(first, ia, s.n, st);
-    if (e == hipSuccess)
-        e = launch_split12_cols(COLS_MODUP, args_cols(c, level, w.dc, 0, w.ext, (int64_t)s.rows * s.N), s.beta, st);
+    ColsArgs ca = args_cols(c, level, w.dc, 0, w.ext, (int64_t)s.rows * s.N);
+    hipError_t e = hipSuccess;
+    NttPro pro = PRO_MID;
+    if ((c->alpha < s.n ? c->alpha : s.n) <= split12_row_sources()) {
+        pro = tin ? PRO_TENSOR : g == 1 ? PRO_PLAIN : PRO_GALOIS;
+        ca.src = ia.src;
+        ca.src2 = ia.src2;
+        ca.galois = g;
+    } else {
+        e = launch_split12_inv_rows(first, ia, s.n, st);
+    }
+    if (e == hipSuccess) e = launch_split12_cols(COLS_MODUP, pro, ca, s.beta, st);
     if (e != hipSuccess || !finish) return e;
     NttArgs fa = args_modup_ntt(c, level, w.ext);
     fa.map.dense = 1;
@@ -113,7 +122,7 @@ hipError_t moddown(const ckks_ctx *c, const uint64_t *acc, int64_t acc_stride, u
     if (c->logn == 12) {
         if (!row_done) e = launch_split12_inv_rows(STAGE_INV_PLAIN, ia, npoly * c->np, st);
         if (e == hipSuccess)
-            e = launch_split12_cols(COLS_MODDOWN, args_cols(c, level, pc, ia.mid_stride, conv, fa.mid_stride), npoly, st);
+            e = launch_split12_cols(COLS_MODDOWN, PRO_MID, args_cols(c, level, pc, ia.mid_stride, conv, fa.mid_stride), npoly, st);
         return e == hipSuccess ? launch_split12_fwd_rows(EPI_MODDOWN, fa, npoly * s.n, st) : e;
     }
     e = launch_ntt_stage(STAGE_INV_PLAIN, ia, npoly * c->np, st, row_done ? 1 : 0);
@@ -482,20 +491,25 @@ extern "C" ckks_status ckks_rescale(ckks_ctx *ctx, const ckks_ct *in, ckks_ct *o
         if (overlap(ws, wb, I[x], ib) || overlap(ws, wb, O[x], ob))
             return fail(CKKS_E_ARG, "ckks_rescale: workspace overlaps a polynomial");
     uint64_t *v = (uint64_t *)ws, *mid = v + 2 * N;
-    NttArgs ia = base_args(ctx, true);
-    ia.src = in->c0 + (size_t)l * N;
-    ia.dst = v;
-    ia.map.rows = 1;
-    ia.map.prime0 = l;
-    ia.map.src_poly_stride = (int64_t)(in->c1 - in->c0);
-    ia.map.dst_poly_stride = (int64_t)N;
-    ia.mid = v;
-    ia.mid_stride = (int64_t)N;
-    const bool split = ctx->logn == 12;  // the transforms in their two passes, the lift in the column launch
-    hipError_t e = split ? launch_split12_inv_rows(STAGE_INV_PLAIN, ia, 2, S(stream))
-                         : launch_ntt_stage(STAGE_INV_PLAIN, ia, 2, S(stream));
-    if (e == hipSuccess && split)
-        e = launch_split12_cols(COLS_RESCALE, args_cols(ctx, l, v, (int64_t)N, mid, (int64_t)l * N), 2, S(stream));
+    const uint64_t *last = in->c0 + (size_t)l * N;
+    const int64_t half_stride = (int64_t)(in->c1 - in->c0);
+    const bool split = ctx->logn == 12;  // one launch up to the first forward pass
+    hipError_t e;
+    if (split) {
+        e = launch_split12_cols(COLS_RESCALE, PRO_PLAIN, args_cols(ctx, l, last, half_stride, mid, (int64_t)l * N), 2,
+                                S(stream));
+    } else {
+        NttArgs ia = base_args(ctx, true);
+        ia.src = last;
+        ia.dst = v;
+        ia.mid = v;
+        ia.mid_stride = (int64_t)N;
+        ia.map.rows = 1;
+        ia.map.prime0 = l;
+        ia.map.src_poly_stride = half_stride;
+        ia.map.dst_poly_stride = (int64_t)N;
+        e = launch_ntt_stage(STAGE_INV_PLAIN, ia, 2, S(stream));
+    }
     if (e == hipSuccess) {
         NttArgs a = base_args(ctx, false);
         a.src = v;

@@ -63,7 +63,8 @@ __device__ __forceinline__ uint32_t galois_src(uint32_t e, uint32_t g, uint32_t 
 }
 
 // Prologue of the first forward pass / epilogue of the last forward pass.
-enum NttPro { PRO_PLAIN = 0, PRO_RESCALE = 1, PRO_GALOIS = 2, PRO_BCONV = 3, PRO_TENSOR = 4 };
+enum NttPro { PRO_PLAIN = 0, PRO_RESCALE = 1, PRO_GALOIS = 2, PRO_BCONV = 3, PRO_TENSOR = 4,
+              PRO_MID = 5 };  // PRO_MID: no prologue, the other pass's output is in memory
 enum NttEpi { EPI_PLAIN = 0, EPI_MODDOWN = 1, EPI_RESCALE = 2 };
 
 struct NttArgs {
@@ -426,7 +427,8 @@ hipError_t launch_inner_product_rowpass(const IpArgs &ip, const NttArgs &ia, hip
 // polynomial t, source its row q_l, targets q_0..q_{l-1} (SwitchModulo in place of a conversion).
 enum ColsMode { COLS_MODUP = 0, COLS_MODDOWN = 1, COLS_RESCALE = 2 };
 struct ColsArgs {
-    const uint64_t *src;        // output of the first inverse pass; job j's rows at src + j src_stride
+    const uint64_t *src;        // evaluations, or (PRO_MID) the first inverse pass's output: job j's rows
+    const uint64_t *src2;       // at src + j src_stride; PRO_TENSOR: the other factor's, laid out alike
     uint64_t *dst;              // input of the last forward pass; job j's row r at dst + j dst_stride + r N
     int64_t src_stride, dst_stride;
     const Prime *primes;
@@ -436,10 +438,11 @@ struct ColsArgs {
     const double *ysd;
     const uint64_t *hmod;       // [nsets][n_primes][kConvRow]
     const uint64_t *rs_qlmod;   // COLS_RESCALE: q_l mod q_i
-    uint32_t level, nq, np, alpha, pset, pad;
+    uint32_t level, nq, np, alpha, pset, galois;
 };
 hipError_t launch_split12_inv_rows(NttStage st, const NttArgs &a, uint32_t nlimbs, hipStream_t stream);
-hipError_t launch_split12_cols(ColsMode mode, const ColsArgs &a, uint32_t njobs, hipStream_t stream);
+hipError_t launch_split12_cols(ColsMode mode, NttPro pro, const ColsArgs &a, uint32_t njobs, hipStream_t stream);
+uint32_t split12_row_sources();  // the most sources whose first inverse pass it runs itself
 hipError_t launch_split12_fwd_rows(NttEpi epi, const NttArgs &a, uint32_t nlimbs, hipStream_t stream);
 // The key inner product: rows q_0..q_l of both halves to ip.acc, the special rows through ModDown's
 // first inverse pass (ia: args_moddown_intt) to ia.mid.  ready: ip.ext holds finished transforms, else

@@ -138,6 +138,7 @@ ColsArgs args_cols(const ckks_ctx *c, uint32_t level, const uint64_t *src, int64
     a.np = c->np;
     a.alpha = c->alpha;
     a.pset = c->pset_index();
+    a.galois = 1;
     return a;
 }
 

@@ -1184,26 +1184,36 @@ __device__ __forceinline__ void inv64(const A &ar, typename A::V (&v)[8], uint64
     inv_rw<3>(v, wa, ar);
 }
 
-// Inverse rows: 8 rows of a limb (tile) from its evaluations to a.mid.
+// First inverse pass of 8 rows (tile) of a limb's evaluations src (gathered
+// through X -> X^g, or times src2: HMult's d2 = a1 b1), in layout A.
 template <int PRO, class A>
-__device__ __forceinline__ void inv_rows12(const NttArgs &a, const LimbPos &lp, const Prime &P, const A &ar, uint64_t *L,
-                                           uint32_t tile, uint32_t lane)
+__device__ __forceinline__ void inv_row_tile12(typename A::V (&v)[8], const A &ar, const Prime &P, const uint64_t *src,
+                                               const uint64_t *src2, uint32_t g, uint64_t *L, uint32_t tile,
+                                               uint32_t lane)
 {
-    const size_t row_off = (int64_t)lp.poly * a.map.src_poly_stride + (size_t)lp.row * 4096;
-    const uint64_t *src = a.src + row_off;
     const uint32_t row = lane >> 3, s = lane & 7, e0 = tile * kTile12 + 64 * row + 8 * s;
-    typename A::V v[8];
     uint64_t x[8], y[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = src[PRO == PRO_GALOIS ? galois_src(e0 + i, a.galois, 12) : e0 + i];
-    if (PRO == PRO_TENSOR) {  // HMult's d2 = a1 b1
+    for (int i = 0; i < 8; ++i) x[i] = src[PRO == PRO_GALOIS ? galois_src(e0 + i, g, 12) : e0 + i];
+    if (PRO == PRO_TENSOR) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) y[i] = a.src2[row_off + e0 + i];
+        for (int i = 0; i < 8; ++i) y[i] = src2[e0 + i];
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = PRO == PRO_TENSOR ? ar.product(x[i], y[i], P) : ar.from_u64(x[i]);
     ar.reduce_all(v);
     inv64(ar, v, L, s, 64 + 8 * tile + row, [&](uint32_t p) { return 64 * row + p; });
+}
+
+// Inverse rows: 8 rows of a limb from its evaluations to a.mid.
+template <int PRO, class A>
+__device__ __forceinline__ void inv_rows12(const NttArgs &a, const LimbPos &lp, const Prime &P, const A &ar, uint64_t *L,
+                                           uint32_t tile, uint32_t lane)
+{
+    const size_t row_off = (int64_t)lp.poly * a.map.src_poly_stride + (size_t)lp.row * 4096;
+    typename A::V v[8];
+    inv_row_tile12<PRO>(v, ar, P, a.src + row_off, PRO == PRO_TENSOR ? a.src2 + row_off : nullptr, a.galois, L, tile, lane);
+    const uint32_t row = lane >> 3, s = lane & 7;
     uint64_t *m = a.mid + (int64_t)lp.poly * a.mid_stride + (size_t)lp.row * 4096 + tile * kTile12;
 #pragma unroll
     for (int i = 0; i < 8; ++i) m[64 * row + s + 8 * i] = ar.to_bits(v[i]);
@@ -1267,18 +1277,36 @@ __global__ __launch_bounds__(64) void k12_fwd_rows(NttArgs a)
 }
 
 // Second inverse pass of a source row's 8 columns, scaled: canonical inputs of
-// the conversion (shifted for ModDown) to the tile y, element lane + 64 i.
-template <int MODE, class A>
+// the conversion (shifted for ModDown) to the tile y, element lane + 64 i.  The
+// first pass's output comes from m, or (ROWS) is in y already, element 8 row + col.
+template <int MODE, bool ROWS, class A>
 __device__ __forceinline__ void source_cols12(const A &ar, const uint64_t *m, uint64_t *y, uint32_t tile, uint32_t lane)
 {
     const uint32_t col = lane & 7, s = lane >> 3, c = 8 * tile + col;
     typename A::V v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(m[64 * (8 * s + i) + c]);
+    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(ROWS ? y[8 * (8 * s + i) + col] : m[64 * (8 * s + i) + c]);
+    if (ROWS) wave_sync();  // read before the exchange reuses the tile
     ar.reduce_all(v);
     inv64(ar, v, y, s, 1, [&](uint32_t p) { return 8 * p + col; });
     wave_sync();  // the exchange's reads are done: the tile takes the result
     inv_store(y, v, ar, MODE == COLS_MODDOWN ? 2 : 1, [&](int i) { return lane + 64 * i; });
+}
+
+// First inverse pass of a source row by one of the workgroup's waves (its row
+// tile `rows`), of which the column tile keeps 8 columns: col + 8 i, i = tile.
+template <int PRO, class A>
+__device__ __forceinline__ void source_rows12(const ColsArgs &a, const A &ar, const Prime &P, const uint64_t *src,
+                                              const uint64_t *src2, uint64_t *L, uint64_t *y, uint32_t tile,
+                                              uint32_t rows, uint32_t lane)
+{
+    typename A::V v[8];
+    inv_row_tile12<PRO>(v, ar, P, src, src2, a.galois, L, rows, lane);
+    typename A::V x = v[0];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) x = (uint32_t)i == tile ? v[i] : x;
+    y[8 * (8 * rows + (lane >> 3)) + (lane & 7)] = ar.to_bits(x);
+    wave_sync();  // the next source's exchange reuses L
 }
 
 // v[i] = Conv(y)[lane + 64 i] from the source tiles in LDS.
@@ -1335,12 +1363,16 @@ __device__ __forceinline__ void target_cols12(const A &ar, const Prime &P, const
 // A workgroup of 8 waves: a job's sources for one tile (each wave a row, two
 // when there are more than eight), then one target row per wave.  A job with
 // more than eight targets takes several workgroups, which all form the sources:
-// that costs no time, since they do it side by side.
+// that costs no time, since they do it side by side.  With PRO the sources are
+// evaluations and the workgroup runs their first inverse pass as well, a row tile
+// per wave: no launch for it, but ns passes one after another in each of the
+// workgroups, so only for few sources.
 constexpr uint32_t kColsWaves = 8;
 
-template <int MODE>
+template <int MODE, int PRO>
 __global__ __launch_bounds__(64 * kColsWaves) void k12_cols(ColsArgs a)
 {
+    constexpr bool kRows = PRO != PRO_MID;
     extern __shared__ uint64_t lds12[];  // ns source tiles, then a tile per wave
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const uint32_t tile = blockIdx.x, job = blockIdx.y, n = a.level + 1;
@@ -1356,7 +1388,21 @@ __global__ __launch_bounds__(64 * kColsWaves) void k12_cols(ColsArgs a)
         prime0 = a.nq;
         ntgt = n;
     }
-    const uint64_t *src = a.src + (MODE == COLS_MODUP ? (int64_t)lo * 4096 : (int64_t)job * a.src_stride);
+    const int64_t src_off = MODE == COLS_MODUP ? (int64_t)lo * 4096 : (int64_t)job * a.src_stride;
+    const uint64_t *src = a.src + src_off;
+    if (kRows) {
+        uint64_t *L = lds12 + (ns + w) * kTile12;
+        for (uint32_t k = 0; k < ns; ++k) {
+            const uint32_t pi = prime0 + k;
+            const Prime P = a.primes[pi];
+            const uint64_t *x = src + (size_t)k * 4096, *x2 = PRO == PRO_TENSOR ? a.src2 + src_off + (size_t)k * 4096 : nullptr;
+            if (P.q < kFpMaxPrime)
+                source_rows12<PRO>(a, fp_arith(a.twdi, P, pi, 4096), P, x, x2, L, lds12 + k * kTile12, tile, w, lane);
+            else
+                source_rows12<PRO>(a, int_arith(a.twi, P, pi, 4096), P, x, x2, L, lds12 + k * kTile12, tile, w, lane);
+        }
+        __syncthreads();
+    }
     for (uint32_t k = w; k < ns; k += kColsWaves) {
         const uint32_t pi = prime0 + k;
         const Prime P = a.primes[pi];
@@ -1364,7 +1410,7 @@ __global__ __launch_bounds__(64 * kColsWaves) void k12_cols(ColsArgs a)
         if (P.q < kFpMaxPrime) {
             FpArith ar = fp_arith(a.twdi, P, pi, 4096);
             if (MODE != COLS_RESCALE) ar.fc = a.ysd[set * kMaxDigitPrimes + k];
-            source_cols12<MODE>(ar, src + (size_t)k * 4096, y, tile, lane);
+            source_cols12<MODE, kRows>(ar, src + (size_t)k * 4096, y, tile, lane);
         } else {
             IntArith ar = int_arith(a.twi, P, pi, 4096);
             if (MODE != COLS_RESCALE) {
@@ -1372,7 +1418,7 @@ __global__ __launch_bounds__(64 * kColsWaves) void k12_cols(ColsArgs a)
                 ar.fc = f.x;
                 ar.fc_s = f.y;
             }
-            source_cols12<MODE>(ar, src + (size_t)k * 4096, y, tile, lane);
+            source_cols12<MODE, kRows>(ar, src + (size_t)k * 4096, y, tile, lane);
         }
     }
     __syncthreads();
@@ -2007,7 +2053,13 @@ hipError_t launch_split12_inv_rows(NttStage st, const NttArgs &a, uint32_t nlimb
     return hipGetLastError();
 }
 
-hipError_t launch_split12_cols(ColsMode mode, const ColsArgs &a, uint32_t njobs, hipStream_t stream)
+// Sources whose first inverse pass the column launch runs itself.  A launch costs about 4 us of GPU
+// time and 2 of the host's.  One source (Rescale, digits of one prime): Rescale at l = 17 takes 12.4 us
+// so, 15 with a launch for it, a key switch at level 0 27.6 us against 28.4.  Two sources run their
+// passes one after the other in every workgroup: HMult of the small set 33.6 us against 31.8.
+uint32_t split12_row_sources() { return 1; }
+
+hipError_t launch_split12_cols(ColsMode mode, NttPro pro, const ColsArgs &a, uint32_t njobs, hipStream_t stream)
 {
     const uint32_t n = a.level + 1;
     // the most sources and targets of a job; LDS holds a tile per source and per wave (96 KB at most)
@@ -2017,12 +2069,19 @@ hipError_t launch_split12_cols(ColsMode mode, const ColsArgs &a, uint32_t njobs,
     if (targets == 0 || njobs == 0) return hipSuccess;
     const dim3 grid(8, njobs, (targets + kColsWaves - 1) / kColsWaves), block(64 * kColsWaves);
     const size_t lds = (size_t)(ns + kColsWaves) * kTile12 * 8;
-    switch (mode) {
-    case COLS_MODUP: hipLaunchKernelGGL(k12_cols<COLS_MODUP>, grid, block, lds, stream, a); break;
-    case COLS_MODDOWN: hipLaunchKernelGGL(k12_cols<COLS_MODDOWN>, grid, block, lds, stream, a); break;
-    case COLS_RESCALE: hipLaunchKernelGGL(k12_cols<COLS_RESCALE>, grid, block, lds, stream, a); break;
+#define COLS12(M, PRO) \
+    if (mode == M && pro == PRO) { \
+        hipLaunchKernelGGL((k12_cols<M, PRO>), grid, block, lds, stream, a); \
+        return hipGetLastError(); \
     }
-    return hipGetLastError();
+    COLS12(COLS_MODUP, PRO_MID)
+    COLS12(COLS_MODUP, PRO_PLAIN)
+    COLS12(COLS_MODUP, PRO_GALOIS)
+    COLS12(COLS_MODUP, PRO_TENSOR)
+    COLS12(COLS_MODDOWN, PRO_MID)
+    COLS12(COLS_RESCALE, PRO_PLAIN)
+#undef COLS12
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_split12_fwd_rows(NttEpi epi, const NttArgs &a, uint32_t nlimbs, hipStream_t stream)
