@@ -76,14 +76,27 @@ hipError_t modup(const ckks_ctx *c, const uint64_t *d, uint32_t g, uint32_t leve
     NttArgs ia = args_modup_intt(c, tin ? tin->a1 : d, g, level, w.dc);
     if (tin) ia.src2 = tin->b1;
     const NttStage first = tin ? STAGE_INV_TENSOR : g == 1 ? STAGE_INV_PLAIN : STAGE_INV_GALOIS;
-    if (c->logn != 12) {
-        hipError_t e = launch_ntt_stage(first, ia, s.n, st);
-        return e == hipSuccess ? modup_from_coeffs(c, d, g, level, w.dc, w.ext, false, st) : e;
-    }
+    const uint32_t ns = c->alpha < s.n ? c->alpha : s.n;
     ColsArgs ca = args_cols(c, level, w.dc, 0, w.ext, (int64_t)s.rows * s.N);
+    NttArgs fa = args_modup_ntt(c, level, w.ext);
+    fa.map.dense = 1;
+    const uint32_t converted = s.beta * s.rows - s.n;
     hipError_t e = hipSuccess;
+    if (c->logn == 16) {
+        // the row pass can't work in place on tiles: the column launch writes to the workspace behind
+        // ext (acc, pc and conv, not in use yet), which holds 4 (l + 1 + K) rows
+        if (!cols16_fits(ns) || s.beta > 4) {
+            e = launch_ntt_stage(first, ia, s.n, st);
+            return e == hipSuccess ? modup_from_coeffs(c, d, g, level, w.dc, w.ext, false, st) : e;
+        }
+        ia.tiled = fa.tiled = 1;
+        ca.dst = fa.mid = w.acc;
+        e = launch_ntt_stage(first, ia, s.n, st, 0, 0);
+        if (e == hipSuccess) e = launch_cols16(COLS_MODUP, ca, s.beta, st);
+        return e == hipSuccess ? launch_ntt_stage(STAGE_FWD_PLAIN, fa, converted, st, 1, 1) : e;
+    }
     NttPro pro = PRO_MID;
-    if ((c->alpha < s.n ? c->alpha : s.n) <= split12_row_sources()) {
+    if (ns <= split12_row_sources()) {
         pro = tin ? PRO_TENSOR : g == 1 ? PRO_PLAIN : PRO_GALOIS;
         ca.src = ia.src;
         ca.src2 = ia.src2;
@@ -92,10 +105,7 @@ hipError_t modup(const ckks_ctx *c, const uint64_t *d, uint32_t g, uint32_t leve
         e = launch_split12_inv_rows(first, ia, s.n, st);
     }
     if (e == hipSuccess) e = launch_split12_cols(COLS_MODUP, pro, ca, s.beta, st);
-    if (e != hipSuccess || !finish) return e;
-    NttArgs fa = args_modup_ntt(c, level, w.ext);
-    fa.map.dense = 1;
-    return launch_split12_fwd_rows(EPI_PLAIN, fa, s.beta * s.rows - s.n, st);
+    return e == hipSuccess && finish ? launch_split12_fwd_rows(EPI_PLAIN, fa, converted, st) : e;
 }
 
 hipError_t inner_product(const ckks_ctx *c, const uint64_t *ext, uint32_t level, const uint64_t *key, uint32_t g,
@@ -116,14 +126,20 @@ hipError_t moddown(const ckks_ctx *c, const uint64_t *acc, int64_t acc_stride, u
                    hipStream_t st, bool row_done = false)
 {
     KsSizes s = ks_sizes(c, level);
-    const NttArgs ia = args_moddown_intt(c, acc, acc_stride, level, pc);
-    const NttArgs fa = args_moddown_ntt(c, acc, acc_stride, npoly, level, out, add, g, pc, conv);
+    NttArgs ia = args_moddown_intt(c, acc, acc_stride, level, pc);
+    NttArgs fa = args_moddown_ntt(c, acc, acc_stride, npoly, level, out, add, g, pc, conv);
+    const ColsArgs ca = args_cols(c, level, pc, ia.mid_stride, conv, fa.mid_stride);
     hipError_t e = hipSuccess;
     if (c->logn == 12) {
         if (!row_done) e = launch_split12_inv_rows(STAGE_INV_PLAIN, ia, npoly * c->np, st);
-        if (e == hipSuccess)
-            e = launch_split12_cols(COLS_MODDOWN, PRO_MID, args_cols(c, level, pc, ia.mid_stride, conv, fa.mid_stride), npoly, st);
+        if (e == hipSuccess) e = launch_split12_cols(COLS_MODDOWN, PRO_MID, ca, npoly, st);
         return e == hipSuccess ? launch_split12_fwd_rows(EPI_MODDOWN, fa, npoly * s.n, st) : e;
+    }
+    if (cols16_fits(c->np)) {
+        ia.tiled = fa.tiled = 1;
+        if (!row_done) e = launch_ntt_stage(STAGE_INV_PLAIN, ia, npoly * c->np, st, 0, 0);
+        if (e == hipSuccess) e = launch_cols16(COLS_MODDOWN, ca, npoly, st);
+        return e == hipSuccess ? launch_ntt_stage(STAGE_FWD_BCONV_MODDOWN, fa, npoly * s.n, st, 1, 1) : e;
     }
     e = launch_ntt_stage(STAGE_INV_PLAIN, ia, npoly * c->np, st, row_done ? 1 : 0);
     return e == hipSuccess ? launch_ntt_stage(STAGE_FWD_BCONV_MODDOWN, fa, npoly * s.n, st) : e;
@@ -137,7 +153,8 @@ hipError_t ip_moddown(const ckks_ctx *c, const IpArgs &ip, bool ready, uint32_t 
 {
     const KsSizes s = ks_sizes(c, level);
     const int64_t acc_stride = (int64_t)s.rows * s.N;
-    const NttArgs ia = args_moddown_intt(c, w.acc, acc_stride, level, w.pc);
+    NttArgs ia = args_moddown_intt(c, w.acc, acc_stride, level, w.pc);
+    ia.tiled = c->logn == 16 && cols16_fits(c->np);
     hipError_t e = c->logn == 12 ? launch_split12_ip(ip, ia, base_args(c, false), ready, st)
                                  : launch_inner_product_rowpass(ip, ia, st);
     return e == hipSuccess ? moddown(c, w.acc, acc_stride, 2, level, out, add, g, w.pc, w.conv, st, true) : e;
@@ -493,35 +510,28 @@ extern "C" ckks_status ckks_rescale(ckks_ctx *ctx, const ckks_ct *in, ckks_ct *o
     uint64_t *v = (uint64_t *)ws, *mid = v + 2 * N;
     const uint64_t *last = in->c0 + (size_t)l * N;
     const int64_t half_stride = (int64_t)(in->c1 - in->c0);
-    const bool split = ctx->logn == 12;  // one launch up to the first forward pass
+    // N = 2^12: one launch up to the first forward pass; N = 2^16: the inverse row pass, then the columns
+    const bool split = ctx->logn == 12;
+    const ColsArgs ca = args_cols(ctx, l, split ? last : v, split ? half_stride : (int64_t)N, mid, (int64_t)l * N);
     hipError_t e;
     if (split) {
-        e = launch_split12_cols(COLS_RESCALE, PRO_PLAIN, args_cols(ctx, l, last, half_stride, mid, (int64_t)l * N), 2,
-                                S(stream));
+        e = launch_split12_cols(COLS_RESCALE, PRO_PLAIN, ca, 2, S(stream));
     } else {
         NttArgs ia = base_args(ctx, true);
         ia.src = last;
-        ia.dst = v;
         ia.mid = v;
         ia.mid_stride = (int64_t)N;
         ia.map.rows = 1;
         ia.map.prime0 = l;
         ia.map.src_poly_stride = half_stride;
-        ia.map.dst_poly_stride = (int64_t)N;
-        e = launch_ntt_stage(STAGE_INV_PLAIN, ia, 2, S(stream));
+        ia.tiled = 1;
+        e = launch_ntt_stage(STAGE_INV_PLAIN, ia, 2, S(stream), 0, 0);
+        if (e == hipSuccess) e = launch_cols16(COLS_RESCALE, ca, 2, S(stream));
     }
     if (e == hipSuccess) {
         NttArgs a = base_args(ctx, false);
-        a.src = v;
-        a.dst = mid;
         a.map.rows = l;
         a.map.prime0 = 0;
-        a.map.src_poly_stride = 0;
-        a.map.dst_poly_stride = (int64_t)l * N;
-        a.rs_src[0] = v;
-        a.rs_src[1] = v + N;
-        a.rs_qlmod = ctx->d_rs_mod + (size_t)l * ctx->nq;
-        a.rs_ql = ctx->primes[l];
         a.cst = ctx->d_rs_inv + (size_t)l * ctx->nq;
         a.aux[0] = in->c0;
         a.aux[1] = in->c1;
@@ -529,8 +539,9 @@ extern "C" ckks_status ckks_rescale(ckks_ctx *ctx, const ckks_ct *in, ckks_ct *o
         a.out[1] = o.c1;
         a.mid = mid;
         a.mid_stride = (int64_t)l * N;
+        a.tiled = split ? 0 : 1;
         e = split ? launch_split12_fwd_rows(EPI_RESCALE, a, 2 * l, S(stream))
-                  : launch_ntt_stage(STAGE_FWD_RESCALE, a, 2 * l, S(stream));
+                  : launch_ntt_stage(STAGE_FWD_RESCALE, a, 2 * l, S(stream), 1, 1);
     }
     TRY(dev(e, "ckks_rescale"));
     out->level = l - 1;

@@ -106,6 +106,7 @@ struct NttArgs {
     uint64_t int_primes;        // bit i: prime i is on the integer path
     uint32_t n_heavy, by_tile;  // by_tile: workgroups in plain (tile, limb) order
     uint8_t heavy[kMaxHeavy];   // launch limbs on the integer path, ascending (n_heavy of them)
+    uint32_t tiled, tiled_pad;  // N = 2^16: mid is laid out for the column launch (row passes)
     // PRO_TENSOR (first inverse pass): the input row is [src * src2]_q, HMult's d2 = a1 b1
     const uint64_t *src2;
 };
@@ -402,9 +403,9 @@ uint32_t ntt_tiles(uint32_t logn);  // tiles per limb of the persistent passes
 constexpr uint32_t kMaxTileLimbs = 128;
 bool ntt_tile_set(uint32_t inverse, uint32_t nlimbs, uint32_t tile);
 uint32_t ntt_tile_get(uint32_t inverse, uint32_t nlimbs);
-// first_pass 1 (N = 2^16): the second pass only, the first pass's output already in a.mid
+// N = 2^16: passes first_pass to last_pass; the first pass's output is in a.mid
 hipError_t launch_ntt_stage(NttStage st, const NttArgs &a, uint32_t nlimbs, hipStream_t stream,
-                            uint32_t first_pass = 0);
+                            uint32_t first_pass = 0, uint32_t last_pass = 1);
 hipError_t launch_ntt_stage_queue(NttStage st, uint32_t logn, uint32_t pass, const NttArgs *insts,
                                   const WorkQueue &q, uint32_t grid, hipStream_t stream);
 hipError_t launch_bconv(const BconvArgs &a, uint32_t njobs, hipStream_t stream);
@@ -419,8 +420,7 @@ hipError_t launch_inner_product(const IpArgs &a, hipStream_t stream);  // ta0 se
 // same accumulators), with that INTT's first pass on the special rows run by the same launch; the
 // INTT then runs with first_pass 1.  The special rows of ip.acc are not written.
 hipError_t launch_inner_product_rowpass(const IpArgs &ip, const NttArgs &ia, hipStream_t stream);
-// ---- N = 2^12 in split transforms (64 x 64, a wave per 8 columns or rows of a limb)
-// The column launch of a conversion: job j takes its ns source rows through the second inverse pass
+// ---- The column launch of a conversion (N = 2^12, in split transforms of 64 x 64; N = 2^16, tiled): job j takes its ns source rows through the second inverse pass
 // (times the conversion scale), converts them to its target rows and runs those through the first
 // forward pass.  COLS_MODUP: job j is digit j, targets every extended row but its own.  COLS_MODDOWN:
 // job t is polynomial t, sources the K special rows, targets q_0..q_l.  COLS_RESCALE: job t is
@@ -439,9 +439,13 @@ struct ColsArgs {
     const uint64_t *hmod;       // [nsets][n_primes][kConvRow]
     const uint64_t *rs_qlmod;   // COLS_RESCALE: q_l mod q_i
     uint32_t level, nq, np, alpha, pset, galois;
+    uint64_t int_primes;        // bit i: prime i is on the integer path
 };
 hipError_t launch_split12_inv_rows(NttStage st, const NttArgs &a, uint32_t nlimbs, hipStream_t stream);
 hipError_t launch_split12_cols(ColsMode mode, NttPro pro, const ColsArgs &a, uint32_t njobs, hipStream_t stream);
+// N = 2^16, PRO_MID only, for at most cols16_fits sources; its row passes run with NttArgs::tiled.
+hipError_t launch_cols16(ColsMode mode, const ColsArgs &a, uint32_t njobs, hipStream_t stream);
+bool cols16_fits(uint32_t ns);
 uint32_t split12_row_sources();  // the most sources whose first inverse pass it runs itself
 hipError_t launch_split12_fwd_rows(NttEpi epi, const NttArgs &a, uint32_t nlimbs, hipStream_t stream);
 // The key inner product: rows q_0..q_l of both halves to ip.acc, the special rows through ModDown's

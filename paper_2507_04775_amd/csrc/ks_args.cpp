@@ -139,6 +139,7 @@ ColsArgs args_cols(const ckks_ctx *c, uint32_t level, const uint64_t *src, int64
     a.alpha = c->alpha;
     a.pset = c->pset_index();
     a.galois = 1;
+    a.int_primes = base_args(c, false).int_primes;
     return a;
 }
 

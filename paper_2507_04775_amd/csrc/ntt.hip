@@ -582,6 +582,32 @@ constexpr int kLds16 = kColLds > 16 * 256 ? kColLds : 16 * 256;
 template <int TW>
 constexpr int lds_words() { return TW * (255 + 31 + 1); }
 
+// Where the row passes keep the values between a transform's two passes.
+// Natural: row b of 256 words, as the column passes read it.  Tiled (a.tiled):
+// tiles of 4 columns x 256 rows in 8 KB each, for the column launch (k16_cols),
+// whose wave takes one tile; in a tile the rows come as 16 (b mod 16) + b / 16,
+// so that its round on rows 16 s + i reads and writes 512 consecutive bytes.
+// A row pass's workgroup then takes rows with the same b mod 16: its accesses
+// run over 32 TW bytes of every tile.  Such a pass does not work in place.
+struct MidRow {
+    uint64_t *p;      // the thread's first value, column s
+    uint32_t step;    // to column s + step columns
+};
+template <int STEP>
+__device__ __forceinline__ MidRow mid_row(const NttArgs &a, uint64_t *limb, uint32_t b, uint32_t s)
+{
+    MidRow m;
+    m.p = limb + (a.tiled ? (s >> 2) * 1024 + (b & 15) * 64 + (b >> 4) * 4 + (s & 3) : b * 256 + s);
+    m.step = a.tiled ? STEP * 256 : STEP;
+    return m;
+}
+template <int TW>
+__device__ __forceinline__ uint32_t pass_row(const NttArgs &a, uint32_t tile, uint32_t blk)
+{
+    constexpr uint32_t G = 16 / TW;
+    return a.tiled ? 16 * ((tile % G) * TW + blk) + tile / G : tile * TW + blk;
+}
+
 template <int PRO, int TW, class A>
 __device__ __forceinline__ void fwd_col_body(const NttArgs &a, const LimbPos &lp, const Prime &P, const A &ar,
                                              uint64_t *lds, uint32_t tile, uint32_t tx)
@@ -640,14 +666,14 @@ template <int EPI, int TW, class A>
 __device__ __forceinline__ void fwd_row_body(const NttArgs &a, const LimbPos &lp, const Prime &P, const A &ar,
                                              uint64_t *lds, uint32_t tile, uint32_t tx)
 {
-    const uint32_t blk = tx >> 5, s = tx & 31, b = tile * TW + blk;
-    const uint64_t *m = a.mid + (int64_t)lp.poly * a.mid_stride + (size_t)lp.row * 65536 + b * 256;
+    const uint32_t blk = tx >> 5, s = tx & 31, b = pass_row<TW>(a, tile, blk);
+    const MidRow m = mid_row<32>(a, a.mid + (int64_t)lp.poly * a.mid_stride + (size_t)lp.row * 65536, b, s);
     uint64_t *L = lds + blk * 256;
     typename A::W wa[7], wb[7], wc[6];
     tw_fwd<3, 256, 32, A, true>(wa, s, ar, 256 + b);
     typename A::V v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(m[pos_wide(s, i)]);
+    for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(m.p[i * m.step]);
     ar.reduce_all(v);
     fwd_rw<3>(v, wa, ar);
     tw_fwd<3, 256, 4, A, true>(wb, pos_mid(s, 0), ar, 256 + b);  // in flight across the exchange
@@ -724,7 +750,7 @@ template <int PRO, int TW, class A>
 __device__ __forceinline__ void inv_row_body(const NttArgs &a, const LimbPos &lp, const Prime &P, const A &ar,
                                              uint64_t *lds, uint32_t tile, uint32_t tx)
 {
-    const uint32_t blk = tx >> 5, s = tx & 31, b = tile * TW + blk;
+    const uint32_t blk = tx >> 5, s = tx & 31, b = pass_row<TW>(a, tile, blk);
     const size_t row_off = (int64_t)lp.poly * a.map.src_poly_stride + (size_t)lp.row * 65536;
     const uint64_t *src = a.src + row_off;
     uint64_t *L = lds + blk * 256;
@@ -763,9 +789,9 @@ __device__ __forceinline__ void inv_row_body(const NttArgs &a, const LimbPos &lp
     for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(L[row_slot(pos_wide(s, i))]);
     ar.reduce_all(v);
     inv_rw<3>(v, wc, ar);
-    uint64_t *m = a.mid + (int64_t)lp.poly * a.mid_stride + (size_t)lp.row * 65536 + b * 256;
+    const MidRow m = mid_row<32>(a, a.mid + (int64_t)lp.poly * a.mid_stride + (size_t)lp.row * 65536, b, s);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) m[pos_wide(s, i)] = ar.to_bits(v[i]);
+    for (int i = 0; i < 8; ++i) m.p[i * m.step] = ar.to_bits(v[i]);
 }
 
 template <int PRO, int TW = 16>
@@ -853,10 +879,9 @@ __device__ __forceinline__ uint32_t col4_slot(uint32_t e, uint32_t col) { return
 constexpr int kLds4 = 8 * (255 + 63 + 1);
 
 // The rounds of one row: thread s < 64 of the row's wave, element loads
-// load(i) at position p4a(s, i), scratch L (256 words), output row m.
+// load(i) at position p4a(s, i), scratch L (256 words), output m (mid_row<64>).
 template <class A, class Load>
-__device__ __forceinline__ void inv_row4_rounds(const A &ar, uint64_t *L, uint32_t s, uint32_t b, Load load,
-                                                uint64_t *m)
+__device__ __forceinline__ void inv_row4_rounds(const A &ar, uint64_t *L, uint32_t s, uint32_t b, Load load, MidRow m)
 {
     typename A::W wa[3], wb[3];
     typename A::V v[4];
@@ -890,16 +915,16 @@ __device__ __forceinline__ void inv_row4_rounds(const A &ar, uint64_t *L, uint32
     ar.reduce_all(v);
     inv_rw<2>(v, wb, ar);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) m[p4d(s, i)] = ar.to_bits(v[i]);
+    for (int i = 0; i < 4; ++i) m.p[i * m.step] = ar.to_bits(v[i]);
 }
 
 template <class A>
 __device__ __forceinline__ void inv_row4_body(const NttArgs &a, const LimbPos &lp, const A &ar, uint64_t *lds,
                                               uint32_t tile, uint32_t tx)
 {
-    const uint32_t blk = tx >> 6, s = tx & 63, b = tile * 8 + blk;
+    const uint32_t blk = tx >> 6, s = tx & 63, b = pass_row<8>(a, tile, blk);
     const uint64_t *src = a.src + (int64_t)lp.poly * a.map.src_poly_stride + (size_t)lp.row * 65536 + b * 256;
-    uint64_t *m = a.mid + (int64_t)lp.poly * a.mid_stride + (size_t)lp.row * 65536 + b * 256;
+    const MidRow m = mid_row<64>(a, a.mid + (int64_t)lp.poly * a.mid_stride + (size_t)lp.row * 65536, b, s);
     inv_row4_rounds(ar, lds + blk * 256, s, b, [&](int i) { return src[p4a(s, i)]; }, m);
 }
 
@@ -1530,6 +1555,195 @@ __global__ __launch_bounds__(64) void k12_ip_rows(IpArgs ip, NttArgs ia, const u
                          threadIdx.x);
 }
 
+// ----------------------------- N = 2^16, the columns of a conversion in one launch
+// Between the row passes of a key switch everything is local to a column: the
+// second inverse pass of the source rows, the base conversion, the first
+// forward pass of the target rows.  A workgroup takes a tile of 4 columns of one
+// job (a digit, a polynomial): its waves bring the sources' tiles to scaled
+// coefficients in LDS, then each takes target rows, converts and transforms
+// them.  A wave works a tile of a row alone, 16 elements per lane in two rounds
+// of four stages with one exchange inside the wave.  No scaled coefficient or
+// converted row goes through memory, three launches are one, and a wave has
+// nothing to wait for but its LDS: the separate passes wrote and read every row
+// once more (they run at the memory's rate, not the VALU's) and spent half
+// their time between loads and stores.
+// Lane layouts (col = lane % 4, s = lane / 4, element e = 4 row + col): A rows
+// s + 16 i, e = lane + 64 i; B rows 16 s + i, stored at 64 i + lane (mid_row).
+constexpr uint32_t kTile16 = 1024;
+constexpr uint32_t kCols16Waves = 8;
+
+// LDS slot of element e: bits 2 to 4 XOR-ed with bits 6 to 8, so that a half-wave
+// hits 32 distinct 8-byte banks in both layouts.
+__device__ __forceinline__ uint32_t slot16(uint32_t e) { return e ^ (((e >> 6) & 7) << 2); }
+
+template <class A>
+__device__ __forceinline__ void fwd256(const A &ar, typename A::V (&v)[16], uint64_t *L, uint32_t lane)
+{
+    const uint32_t col = lane & 3, s = lane >> 2;
+    typename A::W wa[15], wb[15];
+    tw_fwd<4, 256, 16>(wa, 0, ar, 1);  // s < 16: one group per twiddle, the same for all lanes
+    fwd_rw<4>(v, wa, ar);
+    tw_fwd<4, 256, 1>(wb, 16 * s, ar, 1);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) L[slot16(lane + 64 * i)] = ar.to_bits(v[i]);
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = ar.from_bits(L[slot16(64 * s + 4 * i + col)]);
+    wave_sync();
+    ar.reduce_all(v);
+    fwd_rw<4>(v, wb, ar);
+}
+
+template <class A>
+__device__ __forceinline__ void inv256(const A &ar, typename A::V (&v)[16], uint64_t *L, uint32_t lane)
+{
+    const uint32_t col = lane & 3, s = lane >> 2;
+    typename A::W wa[15], wb[15];
+    tw_inv<4, 256, 1>(wb, 16 * s, ar, 1);
+    tw_inv<4, 256, 16>(wa, 0, ar, 1);
+    inv_rw<4>(v, wb, ar);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) L[slot16(64 * s + 4 * i + col)] = ar.to_bits(v[i]);
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = ar.from_bits(L[slot16(lane + 64 * i)]);
+    wave_sync();
+    ar.reduce_all(v);
+    inv_rw<4>(v, wa, ar);
+}
+
+// Second inverse pass of a source tile m, scaled, to y (element lane + 64 i).
+template <int MODE, class A>
+__device__ __forceinline__ void source_cols16(const A &ar, const uint64_t *m, uint64_t *y, uint32_t lane)
+{
+    typename A::V v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = ar.from_bits(m[lane + 64 * i]);
+    ar.reduce_all(v);
+    inv256(ar, v, y, lane);
+    inv_store(y, v, ar, MODE == COLS_MODDOWN ? 2 : 1, [&](int i) { return lane + 64 * i; });
+}
+
+// v[i] = Conv(y)[lane + 64 i], G elements at a time (the sums of 8 FP64 targets
+// or 4 integer ones stay in registers).
+template <class Acc, int G, class A>
+__device__ __forceinline__ void conv16_acc(typename A::V (&v)[16], const A &ar, const uint64_t *y, uint32_t ns,
+                                           ConvWord *h, const Prime &P, uint32_t lane)
+{
+#pragma unroll
+    for (int g = 0; g < 16; g += G) {
+        Acc acc[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) acc[i].start(h);
+        for (uint32_t k = 0; k < ns; ++k) {
+            uint64_t x[G];
+#pragma unroll
+            for (int i = 0; i < G; ++i) x[i] = y[k * kTile16 + lane + 64 * (g + i)];
+#pragma unroll
+            for (int i = 0; i < G; ++i) acc[i].add(x[i], h, k);
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i) v[g + i] = acc[i].value(ar, h, P);
+    }
+}
+__device__ __forceinline__ void conv16(double (&v)[16], const FpArith &ar, const uint64_t *y, uint32_t ns, ConvWord *h,
+                                       const Prime &P, uint32_t lane)
+{
+    conv16_acc<FoldAcc, 8>(v, ar, y, ns, h, P, lane);
+}
+__device__ __forceinline__ void conv16(uint64_t (&v)[16], const IntArith &ar, const uint64_t *y, uint32_t ns, ConvWord *h,
+                                       const Prime &P, uint32_t lane)
+{
+    conv16_acc<WideAcc<MacColsAcc>, 4>(v, ar, y, ns, h, P, lane);
+}
+
+// First forward pass of a target tile to m, converted from the sources (lifted
+// from the one source by Rescale).
+template <int MODE, class A>
+__device__ __forceinline__ void target_cols16(const A &ar, const Prime &P, const uint64_t *y, uint32_t ns, ConvWord *h,
+                                              uint64_t qlmod, uint64_t ql, uint64_t *L, uint64_t *m, uint32_t lane)
+{
+    typename A::V v[16];
+    if (MODE == COLS_RESCALE) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = ar.lift(y[lane + 64 * i], ql, qlmod, P);
+    } else {
+        conv16(v, ar, y, ns, h, P, lane);
+    }
+    fwd256(ar, v, L, lane);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) m[lane + 64 * i] = ar.to_bits(v[i]);
+}
+
+// The k-th set bit of m (k below its population).
+__device__ __forceinline__ uint32_t nth_bit(uint64_t m, uint32_t k)
+{
+    for (; k; --k) m &= m - 1;
+    return (uint32_t)__builtin_ctzll(m);
+}
+
+// blockIdx: (tile, job, part); the parts of a job share its targets and each
+// form the sources.  Targets on the integer path, about twice the work of the
+// others, come first in the order in which the waves take them.
+template <int MODE>
+__global__ __launch_bounds__(64 * kCols16Waves) void k16_cols(ColsArgs a)
+{
+    extern __shared__ uint64_t lds16[];  // ns source tiles, then a tile per wave
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const uint32_t tile = blockIdx.x, job = blockIdx.y, n = a.level + 1;
+    uint32_t lo = 0, ns = 1, set = a.pset, prime0 = a.level;
+    uint64_t targets = (1ull << a.level) - 1;  // by prime; Rescale: q_0..q_{l-1}
+    if (MODE == COLS_MODUP) {
+        lo = job * a.alpha;
+        ns = min(a.alpha, n - lo);
+        set = job * a.alpha + ns - 1;
+        prime0 = lo;
+        const uint64_t own = ((1ull << ns) - 1) << lo, special = ((1ull << a.np) - 1) << a.nq;
+        targets = (((2ull << a.level) - 1) & ~own) | special;
+    } else if (MODE == COLS_MODDOWN) {
+        ns = a.np;
+        prime0 = a.nq;
+        targets = (2ull << a.level) - 1;
+    }
+    const uint64_t *src = a.src + (MODE == COLS_MODUP ? (int64_t)lo * 65536 : (int64_t)job * a.src_stride) + tile * kTile16;
+    for (uint32_t k = w; k < ns; k += kCols16Waves) {
+        const uint32_t pi = prime0 + k;
+        const Prime P = a.primes[pi];
+        uint64_t *y = lds16 + k * kTile16;
+        const uint64_t *m = src + (size_t)k * 65536;
+        if (P.q < kFpMaxPrime) {
+            FpArith ar = fp_arith(a.twdi, P, pi, 65536);
+            if (MODE != COLS_RESCALE) ar.fc = a.ysd[set * kMaxDigitPrimes + k];
+            source_cols16<MODE>(ar, m, y, lane);
+        } else {
+            IntArith ar = int_arith(a.twi, P, pi, 65536);
+            if (MODE != COLS_RESCALE) {
+                const ulonglong2 f = a.ys[set * kMaxDigitPrimes + k];
+                ar.fc = f.x;
+                ar.fc_s = f.y;
+            }
+            source_cols16<MODE>(ar, m, y, lane);
+        }
+    }
+    __syncthreads();
+    const uint64_t heavy = targets & a.int_primes, light = targets & ~a.int_primes;
+    const uint32_t nh = (uint32_t)__builtin_popcountll(heavy), nt = (uint32_t)__builtin_popcountll(targets);
+    uint64_t *L = lds16 + (ns + w) * kTile16, *dst = a.dst + (int64_t)job * a.dst_stride + tile * kTile16;
+    for (uint32_t t = blockIdx.z + gridDim.z * w; t < nt; t += gridDim.z * kCols16Waves) {
+        const uint32_t pi = t < nh ? nth_bit(heavy, t) : nth_bit(light, t - nh);
+        const uint32_t r = pi <= a.level ? pi : pi - a.nq + n;
+        const Prime P = a.primes[pi];
+        ConvWord *h = (ConvWord *)(a.hmod + ((size_t)set * (a.nq + a.np) + pi) * kConvRow);
+        const uint64_t qlmod = MODE == COLS_RESCALE ? a.rs_qlmod[pi] : 0;
+        const uint64_t ql = MODE == COLS_RESCALE ? a.primes[a.level].q : 0;
+        uint64_t *m = dst + (size_t)r * 65536;
+        if (P.q < kFpMaxPrime)
+            target_cols16<MODE>(fp_arith(a.twdf, P, pi, 65536), P, lds16, ns, h, qlmod, ql, L, m, lane);
+        else
+            target_cols16<MODE>(int_arith(a.twf, P, pi, 65536), P, lds16, ns, h, qlmod, ql, L, m, lane);
+    }
+}
+
 // ---------------------------------------------------- kernels: grid and queue
 // Every NTT stage exists as a grid kernel (one launch = one NttArgs, unit =
 // (blockIdx.x, blockIdx.y)) and as a persistent kernel that claims units
@@ -1574,12 +1788,13 @@ __device__ __forceinline__ UnitId grid_unit(const NttArgs &a)
 // over 35 limbs (not over 74, and the tensor prologue's pass loses, so it
 // keeps two workgroups per CU).
 #define OCC6 __attribute__((amdgpu_waves_per_eu(6)))
+#define OCC4 __attribute__((amdgpu_waves_per_eu(4)))  // two: 128 VGPRs
 
 NTT_KERNELS(fwd_col_plain, kLds16, kThreads16, OCC6, fwd_col_unit<PRO_PLAIN>)
 NTT_GRID(fwd_col_rescale, kLds16, kThreads16, , fwd_col_unit<PRO_RESCALE>)
 NTT_KERNELS(fwd_col_bconv, kLds16, kThreads16, , fwd_col_unit<PRO_BCONV>)
 NTT_KERNELS(fwd_row_plain, kLds16, kThreads16, OCC6, fwd_row_unit<EPI_PLAIN>)
-NTT_KERNELS(fwd_row_moddown, kLds16, kThreads16, , fwd_row_unit<EPI_MODDOWN>)
+NTT_KERNELS(fwd_row_moddown, kLds16, kThreads16, OCC4, fwd_row_unit<EPI_MODDOWN>)
 NTT_GRID(fwd_row_rescale, kLds16, kThreads16, , fwd_row_unit<EPI_RESCALE>)
 NTT_KERNELS(inv_row_plain, kLds16, kThreads16, OCC6, inv_row_unit<PRO_PLAIN>)
 NTT_KERNELS(inv_row_galois, kLds16, kThreads16, , inv_row_unit<PRO_GALOIS>)
@@ -1588,12 +1803,12 @@ NTT_KERNELS(inv_col, kLds16, kThreads16, OCC6, inv_col_unit)
 // Grid kernels with narrower tiles (TW = 8, 4 columns or rows per workgroup of
 // 32 TW threads), for launches over few limbs; unit = (blockIdx.x, blockIdx.y).
 #define NTT_NARROW(NAME, UNIT_T)                                                                    \
-    __global__ __launch_bounds__(256) void k_##NAME##_w8(NttArgs a)                                \
+    __global__ __launch_bounds__(256) OCC4 void k_##NAME##_w8(NttArgs a)                                \
     {                                                                                               \
         __shared__ uint64_t lds[lds_words<8>()];                                                    \
         UNIT_T(8)(a, blockIdx.y, blockIdx.x, lds, threadIdx.x);                                     \
     }                                                                                               \
-    __global__ __launch_bounds__(128) void k_##NAME##_w4(NttArgs a)                                \
+    __global__ __launch_bounds__(128) OCC4 void k_##NAME##_w4(NttArgs a)                                \
     {                                                                                               \
         __shared__ uint64_t lds[lds_words<4>()];                                                    \
         UNIT_T(4)(a, blockIdx.y, blockIdx.x, lds, threadIdx.x);                                     \
@@ -1656,6 +1871,7 @@ NTT_QUEUE(inv12_galois, kLds12, kThreads12, inv12_unit<PRO_GALOIS>)
 #undef NTT_GRID
 #undef NTT_QUEUE
 #undef OCC6
+#undef OCC4
 
 // ------------------------------------------- one launch for a whole batch
 // The persistent kernel of a batch of key switches in one launch (N = 2^16):
@@ -1880,7 +2096,7 @@ __device__ __forceinline__ void ip_rowpass_unit(const IpArgs &ip, const NttArgs 
     const Prime P = ia.primes[prime];
     const uint64_t *x = in + ((w >> 1) * 2 + poly) * coef::kCoefThreads;
     uint64_t *L = lds + w * 256;
-    uint64_t *m = ia.mid + (int64_t)poly * ia.mid_stride + (size_t)k * 65536 + b * 256;
+    const MidRow m = mid_row<64>(ia, ia.mid + (int64_t)poly * ia.mid_stride + (size_t)k * 65536, b, s);
     auto load = [&](int i) { return x[p4a(s, i)]; };
     if (P.q < kFpMaxPrime)
         inv_row4_rounds(fp_arith(ia, P, prime, 65536), L, s, b, load, m);
@@ -2015,7 +2231,8 @@ static uint32_t tile_width(NttStage st, uint32_t logn, uint32_t nlimbs)
     return inv && nlimbs <= 8 ? 2 : default_tile(nlimbs);
 }
 
-hipError_t launch_ntt_stage(NttStage st, const NttArgs &a0, uint32_t nlimbs, hipStream_t stream, uint32_t first_pass)
+hipError_t launch_ntt_stage(NttStage st, const NttArgs &a0, uint32_t nlimbs, hipStream_t stream, uint32_t first_pass,
+                            uint32_t last_pass)
 {
     if (nlimbs == 0) return hipSuccess;
     if (first_pass >= ntt_passes(a0.logn)) return hipErrorInvalidValue;
@@ -2023,7 +2240,7 @@ hipError_t launch_ntt_stage(NttStage st, const NttArgs &a0, uint32_t nlimbs, hip
     const uint32_t tw = effective_tile(st, tile_width(st, a.logn, nlimbs));
     if (tw == 16) set_heavy(a, nlimbs);
     else a.n_heavy = 0;
-    for (uint32_t pass = first_pass; pass < ntt_passes(a.logn); ++pass) {
+    for (uint32_t pass = first_pass; pass < ntt_passes(a.logn) && pass <= last_pass; ++pass) {
         StageKernels k;
         if (!stage_kernels(st, a.logn, pass, k, tw) || !k.grid) return hipErrorInvalidValue;
         const bool four = a.logn == 16 && four_element_pass(st, pass, tw);
@@ -2082,6 +2299,27 @@ hipError_t launch_split12_cols(ColsMode mode, NttPro pro, const ColsArgs &a, uin
     COLS12(COLS_RESCALE, PRO_PLAIN)
 #undef COLS12
     return hipErrorInvalidValue;
+}
+
+// Parts of a job: workgroups fill LDS, one to a CU, so as many parts as the CUs take at once.
+constexpr uint32_t kCols16Parts = 256;
+
+bool cols16_fits(uint32_t ns) { return ns <= kFoldMaxTerms; }
+
+hipError_t launch_cols16(ColsMode mode, const ColsArgs &a, uint32_t njobs, hipStream_t stream)
+{
+    const uint32_t n = a.level + 1, ns = mode == COLS_MODUP ? (a.alpha < n ? a.alpha : n) : mode == COLS_MODDOWN ? a.np : 1;
+    if (!cols16_fits(ns) || a.nq + a.np > 64) return hipErrorInvalidValue;
+    if (njobs == 0 || (mode == COLS_RESCALE && a.level == 0)) return hipSuccess;
+    const uint32_t parts = njobs < kCols16Parts / 64 ? kCols16Parts / 64 / njobs : 1;
+    const dim3 grid(64, njobs, parts), block(64 * kCols16Waves);
+    const size_t lds = (size_t)(ns + kCols16Waves) * kTile16 * 8;
+    switch (mode) {
+    case COLS_MODUP: hipLaunchKernelGGL(k16_cols<COLS_MODUP>, grid, block, lds, stream, a); break;
+    case COLS_MODDOWN: hipLaunchKernelGGL(k16_cols<COLS_MODDOWN>, grid, block, lds, stream, a); break;
+    case COLS_RESCALE: hipLaunchKernelGGL(k16_cols<COLS_RESCALE>, grid, block, lds, stream, a); break;
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_split12_fwd_rows(NttEpi epi, const NttArgs &a, uint32_t nlimbs, hipStream_t stream)
