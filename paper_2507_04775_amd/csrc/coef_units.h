@@ -23,31 +23,34 @@ __device__ __forceinline__ uint32_t row_prime(uint32_t r, uint32_t level, uint32
 // Read-only tables read through the scalar cache when the address is uniform.
 typedef const __attribute__((address_space(4))) uint64_t ConstU64;
 
-// Conv_{B->C}: y_i = [x_i (B/b_i)^-1]_{b_i} (Shoup; skipped when the inverse
-// NTT already produced y_i), then every output row c gets
-// [sum_i y_i [B/b_i]_c]_c, reduced once (as the paper does): by FoldSum when
-// the row's prime is below 2^50 and the sources are at most kFoldMaxTerms,
-// else exactly in 128 bits (MacSplit's columns below 2^50, mac_cols above).
-// `J` is the digit (or polynomial), `bz` a group of kBconvRowGroup output
-// rows.  The source count NS is a template parameter (no predicated
-// iterations), and the constant rows and the prime's constants, uniform over
-// the workgroup, come through the scalar cache.
+// Conv_{B->C} of the scaled inputs y_i = [x_i (B/b_i)^-1]_{b_i}, which the inverse
+// NTT left cut (cut_word): every output row c gets [sum_i y_i [B/b_i]_c]_c,
+// reduced once (as the paper does): by FoldSum or FoldSumWide where they hold the
+// sum (see conv_row; the latter's value is below 1.52 c, which the forward
+// transform takes), else exactly in 128 bits (MacSplit's columns below 2^50,
+// mac_cols above).  `J` is the digit (or polynomial), `bz` a group of
+// kBconvRowGroup output rows.  The source count NS is a template parameter (no
+// predicated iterations), and the constant rows and the prime's constants, uniform
+// over the workgroup, come through the scalar cache.
 template <class Acc, int NS>
 __device__ __forceinline__ uint64_t conv_sum(const uint64_t (&y)[NS], ConstU64 *h, const Prime &P)
 {
     Acc acc;
 #pragma unroll
-    for (int i = 0; i < NS; ++i) acc.add(y[i], h[i]);
+    for (int i = 0; i < NS; ++i) acc.add(join_word(y[i]), h[i]);
     return reduce128(acc.total(), P);
 }
 
 template <int NS>
-__device__ __forceinline__ uint64_t conv_fold(const uint64_t (&y)[NS], ConstU64 *h, FpMod m)
+__device__ __forceinline__ uint64_t conv_fold(const uint64_t (&y)[NS], ConstU64 *h, const Prime &P)
 {
-    FoldSum acc = {h[kConvStart], h[kConvStart + 1]};
+    const bool fp = P.q < kFpMaxPrime;
+    FoldColumns acc = {fp ? h[kConvStart] : 0, h[kConvStart + 1]};
 #pragma unroll
     for (int i = 0; i < NS; ++i) acc.add(y[i], h[2 * i], h[2 * i + 1]);
-    return fp_canonical(acc.residue(m), m);
+    if (!fp) return FoldSumWide{acc}.residue(P.q, P.qinv);
+    const FpMod m = {(double)P.q, P.qinv};
+    return fp_canonical(FoldSum{acc}.residue(m), m);
 }
 
 // Constants of prime pi through the scalar cache (the rows' stores keep the
@@ -72,15 +75,7 @@ __device__ __forceinline__ void bconv_rows(const BconvCommon &a, const BconvJob 
     const uint32_t N = a.N;
     uint64_t y[NS];
 #pragma unroll
-    for (int i = 0; i < NS; ++i) {
-        const uint64_t x = J.src[(size_t)i * N + n];
-        if (a.prescaled) {
-            y[i] = x;
-        } else {
-            const ulonglong2 h = J.hinv[i];
-            y[i] = shoup(x, h.x, h.y, a.primes[J.src_prime0 + i].q);
-        }
-    }
+    for (int i = 0; i < NS; ++i) y[i] = J.src[(size_t)i * N + n];
     for (uint32_t r = r0; r < r1; ++r) {
         if (r >= J.lo && r < J.hi) {
             if (J.copy_src)
@@ -91,9 +86,10 @@ __device__ __forceinline__ void bconv_rows(const BconvCommon &a, const BconvJob 
         const uint32_t pi = row_prime(r, a.level, a.nq);
         ConstU64 *h = (ConstU64 *)(J.hmod + (size_t)pi * kConvRow);
         const Prime P = uniform_prime(a.primes, pi);
+        const bool fold = NS <= (int)kFoldMaxTerms && (P.q < kFpMaxPrime || h[kConvStart]);
         uint64_t v;
-        if (P.q >= kFpMaxPrime) v = conv_sum<MacColsAcc, NS>(y, h, P);
-        else if constexpr (NS <= (int)kFoldMaxTerms) v = conv_fold<NS>(y, h, FpMod{(double)P.q, P.qinv});
+        if (fold) v = conv_fold<NS>(y, h, P);
+        else if (P.q >= kFpMaxPrime) v = conv_sum<MacColsAcc, NS>(y, h, P);
         else v = conv_sum<MacSplit, NS>(y, h, P);
         J.dst[(size_t)r * N + n] = v;
     }

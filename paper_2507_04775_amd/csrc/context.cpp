@@ -180,7 +180,6 @@ extern "C" ckks_status ckks_ctx_create(uint32_t log_n, const uint64_t *q, uint32
     // base-conversion sets: every digit j of every possible size, then P
     ctx->nsets = dnum * alpha + 1;
     const size_t hm_stride = (size_t)np_all * kConvRow;
-    std::vector<ulonglong2> bc_hinv((size_t)ctx->nsets * kMaxDigitPrimes);
     std::vector<uint64_t> bc_hmod((size_t)ctx->nsets * hm_stride, 0);
     std::vector<ulonglong2> bc_ys((size_t)ctx->nsets * kMaxDigitPrimes);
     std::vector<double> bc_ysd((size_t)ctx->nsets * kMaxDigitPrimes, 0.0);
@@ -191,7 +190,6 @@ extern "C" ckks_status ckks_ctx_create(uint32_t log_n, const uint64_t *q, uint32
             for (uint32_t k = 0; k < ns; ++k)
                 if (k != i) prod = mul_mod(prod, src[k] % src[i], src[i]);
             uint64_t hinv = inv_mod(prod, src[i]);
-            bc_hinv[(size_t)set * kMaxDigitPrimes + i] = pair(hinv, src[i]);
             uint64_t ys = mul_mod(hinv, inv_mod(N % src[i], src[i]), src[i]);
             bc_ys[(size_t)set * kMaxDigitPrimes + i] = pair(ys, src[i]);
             bc_ysd[(size_t)set * kMaxDigitPrimes + i] = (double)ys;
@@ -228,8 +226,7 @@ extern "C" ckks_status ckks_ctx_create(uint32_t log_n, const uint64_t *q, uint32
     size_t off_twi = align_up(off_twf + tw_f.size() * sizeof(ulonglong2));
     size_t off_twdf = align_up(off_twi + tw_i.size() * sizeof(ulonglong2));
     size_t off_twdi = align_up(off_twdf + twd_f.size() * sizeof(double));
-    size_t off_hinv = align_up(off_twdi + twd_i.size() * sizeof(double));
-    size_t off_hmod = align_up(off_hinv + bc_hinv.size() * sizeof(ulonglong2));
+    size_t off_hmod = align_up(off_twdi + twd_i.size() * sizeof(double));
     size_t off_ys = align_up(off_hmod + bc_hmod.size() * sizeof(uint64_t));
     size_t off_ysd = align_up(off_ys + bc_ys.size() * sizeof(ulonglong2));
     size_t off_pinv = align_up(off_ysd + bc_ysd.size() * sizeof(double));
@@ -248,7 +245,6 @@ extern "C" ckks_status ckks_ctx_create(uint32_t log_n, const uint64_t *q, uint32
     ctx->d_tw_inv = (ulonglong2 *)(blk + off_twi);
     ctx->d_twd_fwd = (double *)(blk + off_twdf);
     ctx->d_twd_inv = (double *)(blk + off_twdi);
-    ctx->d_bc_hinv = (ulonglong2 *)(blk + off_hinv);
     ctx->d_bc_hmod = (uint64_t *)(blk + off_hmod);
     ctx->d_bc_ys = (ulonglong2 *)(blk + off_ys);
     ctx->d_bc_ysd = (double *)(blk + off_ysd);
@@ -265,8 +261,6 @@ extern "C" ckks_status ckks_ctx_create(uint32_t log_n, const uint64_t *q, uint32
                   hipSuccess &&
               hipMemcpy(ctx->d_twd_inv, twd_i.data(), twd_i.size() * sizeof(double), hipMemcpyHostToDevice) ==
                   hipSuccess &&
-              hipMemcpy(ctx->d_bc_hinv, bc_hinv.data(), bc_hinv.size() * sizeof(ulonglong2),
-                        hipMemcpyHostToDevice) == hipSuccess &&
               hipMemcpy(ctx->d_bc_hmod, bc_hmod.data(), bc_hmod.size() * sizeof(uint64_t), hipMemcpyHostToDevice) ==
                   hipSuccess &&
               hipMemcpy(ctx->d_bc_ys, bc_ys.data(), bc_ys.size() * sizeof(ulonglong2), hipMemcpyHostToDevice) ==

@@ -189,14 +189,13 @@ enum NttStage {
 };
 
 struct BconvJob {
-    const uint64_t *src;        // ns coefficient-domain limbs, stride N
+    const uint64_t *src;        // ns limbs of scaled, cut coefficients, stride N
     uint64_t *dst;              // output rows at dst + r N
     const uint64_t *copy_src;   // rows [lo, hi) copied from here to dst (may be null)
-    const ulonglong2 *hinv;     // ns pairs {[(B/b_i)^-1]_{b_i}, shoup}
     const uint64_t *hmod;       // [n_primes][kConvRow]
     uint32_t ns;
-    uint32_t src_prime0;
     uint32_t lo, hi;            // output rows not converted
+    uint32_t pad;
 };
 
 // What the jobs of one conversion share.
@@ -206,8 +205,6 @@ struct BconvCommon {
     uint32_t level, nq;         // row -> prime map as in LimbMap
     uint32_t N, logn;
     uint32_t copy_galois;       // copied rows are gathered through X -> X^g (1 = plain copy)
-    uint32_t prescaled;         // sources already hold y_i (the iNTT folded the scaling in)
-    uint32_t pad;
 };
 
 struct BconvArgs {
@@ -300,7 +297,7 @@ __device__ __forceinline__ void global_ptrs(TensorArgs &a)
 }
 __device__ __forceinline__ void global_ptrs(BconvJob &j)
 {
-    global_ptr(j.src), global_ptr(j.dst), global_ptr(j.copy_src), global_ptr(j.hinv), global_ptr(j.hmod);
+    global_ptr(j.src), global_ptr(j.dst), global_ptr(j.copy_src), global_ptr(j.hmod);
 }
 __device__ __forceinline__ void global_ptrs(BconvCommon &c) { global_ptr(c.primes); }
 
@@ -484,7 +481,6 @@ struct ckks_ctx {
     double *d_twd_fwd = nullptr;        // [n][N] same twiddles as doubles (primes below 2^50)
     double *d_twd_inv = nullptr;
     // base-conversion sets: digit sets indexed (j * alpha + size - 1), then the P set
-    ulonglong2 *d_bc_hinv = nullptr;    // [nsets][kMaxDigitPrimes]
     uint64_t *d_bc_hmod = nullptr;      // [nsets][n_primes][kConvRow]
     ulonglong2 *d_bc_ys = nullptr;      // [nsets][kMaxDigitPrimes]: N^-1 [(B/b_i)^-1]_{b_i}
     double *d_bc_ysd = nullptr;         // the same as doubles (primes below 2^50)

@@ -82,10 +82,8 @@ BconvArgs args_modup_bconv(const ckks_ctx *c, const uint64_t *d, uint32_t g, uin
         J.src = dc + (size_t)lo * s.N;
         J.dst = ext + (size_t)j * s.rows * s.N;
         J.copy_src = copy_own ? d : nullptr;
-        J.hinv = c->d_bc_hinv + (size_t)set * kMaxDigitPrimes;
         J.hmod = c->d_bc_hmod + (size_t)set * hm_stride;
         J.ns = hi - lo;
-        J.src_prime0 = lo;
         J.lo = lo;
         J.hi = hi;
     }
@@ -96,7 +94,6 @@ BconvArgs args_modup_bconv(const ckks_ctx *c, const uint64_t *d, uint32_t g, uin
     b.c.N = c->N;
     b.c.logn = c->logn;
     b.c.copy_galois = g;
-    b.c.prescaled = 1;
     return b;
 }
 

@@ -283,37 +283,42 @@ __host__ __device__ __forceinline__ uint64_t fp_canonical(double x, FpMod m)
     return fp_to_word(r);
 }
 
-// ------------------------------------ base conversion into primes below 2^50
-// Sum of y_i h_i modulo q < 2^50 for at most kFoldMaxTerms inputs y_i < 2^62
-// and constants h_i < q, as a centred-ish FP64 representative.  An input is cut
-// at bit 32, and the weight of its upper word goes into a second constant:
-//   y h == y0 h + y1 [2^32 h]_q (mod q),  y0 < 2^32, y1 < 2^30.
-// The sum S of these products is then below 2^86 instead of 2^116, and with
-// both constants split at bit 25 it needs two 64-bit columns (S = 2^25 a + b),
-// each below 2^61 over 12 terms: four multiply-adds a term, no carries.  The
-// column a starts at -floor(Smax / 2^26), Smax the largest possible sum (the
-// host computes it from the constants), and b at the residue that makes up for
-// it, so that |S| < 2^85 and S / 2^32 is an exact double.  One quotient
-// estimate then leaves S mod q: k = rint(S / q) < 2^37 is within 1/2 + 2^-14 of
-// S / q, and S - k q is exact (every partial result is an integer below 2^53):
-// fourteen instructions, where forming 128 bits, folding them with two 64-bit
-// Shoup products and converting to double takes about seventy.
+// --------------------------------------------- base conversion, two columns
+// Sum of y_i h_i modulo q for at most kFoldMaxTerms inputs y_i < 2^62 and
+// constants h_i < q.  An input is cut at bit 30, and the weight of its upper part
+// goes into a second constant:
+//   y h == y0 h + y1 [2^30 h]_q (mod q),  y0 < 2^30, y1 < 2^32.
+// The sum S of these products is far shorter than the sum of the y h (2^86 in
+// place of 2^116 for q < 2^50), so that a quotient estimate in FP64 reduces it in
+// one step, and two 64-bit columns hold it with the constants split in two:
+// four multiply-adds a term, no carries.  The inverse transforms store the
+// inputs cut (cut_word), so their halves are ready in two registers.
 constexpr uint32_t kFoldMaxTerms = 12;
-constexpr int kFoldShift = 25;
+constexpr int kFoldCut = 30;
 
-// h < 2^50 split at bit 25: the upper half in the upper word
-__host__ __device__ __forceinline__ uint64_t fold_const(uint64_t h)
+__host__ __device__ __forceinline__ uint64_t cut_word(uint64_t y)
 {
-    return ((h >> kFoldShift) << 32) | (h & ((1ull << kFoldShift) - 1));
+    return ((y >> kFoldCut) << 32) | (y & ((1u << kFoldCut) - 1));
+}
+__host__ __device__ __forceinline__ uint64_t join_word(uint64_t w)
+{
+    return mad32((uint32_t)(w >> 32), 1u << kFoldCut, (uint32_t)w);
 }
 
-struct FoldSum {
-    uint64_t a, b;  // a is signed
+// a constant split at bit SH: the upper part in the upper word
+template <int SH>
+__host__ __device__ __forceinline__ uint64_t fold_const(uint64_t h)
+{
+    return ((h >> SH) << 32) | (h & ((1ull << SH) - 1));
+}
 
-    // y < 2^62; c0 = fold_const(h), c1 = fold_const([2^32 h]_q)
-    __host__ __device__ __forceinline__ void add(uint64_t y, uint64_t c0, uint64_t c1)
+struct FoldColumns {
+    uint64_t a, b;  // sum = 2^SH a + b
+
+    // w = cut_word(y), c0 = fold_const(h), c1 = fold_const([2^30 h]_q)
+    __host__ __device__ __forceinline__ void add(uint64_t w, uint64_t c0, uint64_t c1)
     {
-        const uint32_t y0 = (uint32_t)y, y1 = (uint32_t)(y >> 32);
+        const uint32_t y0 = (uint32_t)w, y1 = (uint32_t)(w >> 32);
         const uint32_t b0 = (uint32_t)c0, a0 = (uint32_t)(c0 >> 32);
         const uint32_t b1 = (uint32_t)c1, a1 = (uint32_t)(c1 >> 32);
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -329,6 +334,19 @@ struct FoldSum {
         b = mad32(y1, b1, mad32(y0, b0, b));
 #endif
     }
+};
+
+// Primes below 2^50, constants split at bit 25 (columns below 2^62 over 12
+// terms): the residue as a centred-ish FP64 representative.  The column a is
+// signed and starts at -floor(Smax / 2^26), Smax the largest possible sum (the
+// host computes it from the constants), and b at the residue that makes up for
+// it, so that |S| < 2^85 and S / 2^32 is an exact double.  k = rint(S / q) < 2^37
+// is within 1/2 + 2^-14 of S / q, and S - k q is exact (every partial result is
+// an integer below 2^53): fourteen instructions, where forming 128 bits, folding
+// them with two 64-bit Shoup products and converting takes about seventy.
+constexpr int kFoldShift = 25;
+
+struct FoldSum : FoldColumns {
     // |result| <= (1/2 + 2^-14) q + 2^32
     __host__ __device__ __forceinline__ double residue(FpMod m) const
     {
@@ -337,6 +355,27 @@ struct FoldSum {
         const double s = fma((double)hi, 0x1p64, (double)(uint32_t)(lo >> 32) * 0x1p32);
         const double k = rint(s * m.qinv);
         return fma(-k, m.q, s) + (double)(uint32_t)lo;
+    }
+};
+
+// Primes of 2^50 to 2^61, constants split at bit 30, where the host finds both
+// columns below 2^64 (ModUp from primes below 2^50: their y1 is short).  S < 2^94,
+// k < 2^45 from S's upper words is within 1/2 + 2^-6 of S / q, and S - k q + q is
+// formed modulo 2^64: twenty instructions for about eighty.
+constexpr int kFoldShiftWide = 30;
+
+struct FoldSumWide : FoldColumns {
+    // in (0.48 q, 1.52 q)
+    __host__ __device__ __forceinline__ uint64_t residue(uint64_t q, double qinv) const
+    {
+        const uint64_t lo = b + (a << kFoldShiftWide);
+        const uint32_t hi = (uint32_t)(a >> (64 - kFoldShiftWide)) + (lo < b ? 1 : 0);
+        const double s = fma((double)hi, 0x1p64, (double)(uint32_t)(lo >> 32) * 0x1p32);
+        const uint64_t k = __builtin_bit_cast(uint64_t, fma(s, qinv, 0x1p52));  // 2^52 + k: the mantissa is k
+        const uint64_t nq = 0 - q;
+        const uint32_t k0 = (uint32_t)k, k1 = (uint32_t)(k >> 32) & 0xFFFFF;
+        const uint64_t r = mad32(k0, (uint32_t)nq, lo + q);
+        return r + ((uint64_t)(k0 * (uint32_t)(nq >> 32) + k1 * (uint32_t)nq) << 32);
     }
 };
 __host__ __device__ __forceinline__ uint64_t submod(uint64_t a, uint64_t b, uint64_t q) { return a >= b ? a - b : a + q - b; }

@@ -179,11 +179,12 @@ struct FpArith {
     }
 };
 
-// Stores the last inverse pass's outputs.  For ModDown's centred conversion
-// (ys_mode 2) each canonical y of the special limb p is stored as y + p when
-// y <= (p - 1)/2, else as y: the centred representative plus p, in
-// [(p + 1)/2, 3 (p - 1)/2], below 2^62, so the conversion's sums take no
-// per-term comparison (their constant rows remove the shift).
+// Stores the last inverse pass's outputs: coefficients (ys_mode 0), or a base
+// conversion's inputs, cut for its sums (cut_word).  For ModDown's centred
+// conversion (ys_mode 2) each canonical y of the special limb p goes in as y + p
+// when y <= (p - 1)/2, else as y: the centred representative plus p, in
+// [(p + 1)/2, 3 (p - 1)/2], below 2^62, so the sums take no per-term comparison
+// (their constant rows remove the shift).
 template <int NV, class A, class Idx>
 __device__ __forceinline__ void inv_store(uint64_t *dst, const typename A::V (&v)[NV], const A &ar, uint32_t ys_mode,
                                           Idx idx)
@@ -193,8 +194,11 @@ __device__ __forceinline__ void inv_store(uint64_t *dst, const typename A::V (&v
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const uint64_t y = ar.inv_final(v[i]);
-            dst[idx(i)] = y <= half ? y + q : y;
+            dst[idx(i)] = cut_word(y <= half ? y + q : y);
         }
+    } else if (ys_mode == 1) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) dst[idx(i)] = cut_word(ar.inv_final(v[i]));
     } else {
 #pragma unroll
         for (int i = 0; i < NV; ++i) dst[idx(i)] = ar.inv_final(v[i]);
@@ -444,22 +448,30 @@ __device__ __forceinline__ BcSrc bc_source(const NttArgs &a, uint32_t poly, uint
 typedef const __attribute__((address_space(4))) uint64_t ConvWord;  // constants through the scalar cache
 
 // Accumulator of one converted element: the sum of its terms, then its value
-// in the limb's arithmetic.  FoldAcc: targets below 2^50 with at most
-// kFoldMaxTerms source rows (four multiply-adds a term, fourteen instructions
-// for the residue, which is the FP64 element itself).  WideAcc: exact 128-bit
-// sums reduced once, by MacSplit's carry-free columns below 2^50 (more source
-// rows than FoldSum's columns hold) and by MacCols (carries counted) above.
+// in the limb's arithmetic.  FoldAcc, FoldWideAcc: two columns and an FP64
+// quotient (four multiply-adds a term, 14 and 20 instructions for the residue).
+// WideAcc, where those do not hold the sum: exact 128-bit sums reduced once, by
+// MacSplit's carry-free columns below 2^50 and by MacCols (carries counted) above.
 struct FoldAcc {
     FoldSum s;
     __device__ __forceinline__ void start(ConvWord *h) { s.a = h[kConvStart], s.b = h[kConvStart + 1]; }
     __device__ __forceinline__ void add(uint64_t y, ConvWord *h, uint32_t k) { s.add(y, h[2 * k], h[2 * k + 1]); }
     __device__ __forceinline__ double value(const FpArith &ar, ConvWord *, const Prime &) const { return s.residue(ar.m); }
 };
+struct FoldWideAcc {
+    FoldSumWide s;
+    __device__ __forceinline__ void start(ConvWord *h) { s.a = 0, s.b = h[kConvStart + 1]; }
+    __device__ __forceinline__ void add(uint64_t y, ConvWord *h, uint32_t k) { s.add(y, h[2 * k], h[2 * k + 1]); }
+    __device__ __forceinline__ uint64_t value(const IntArith &, ConvWord *, const Prime &P) const
+    {
+        return s.residue(P.q, P.qinv);
+    }
+};
 template <class Acc>
 struct WideAcc {
     Acc s;
     __device__ __forceinline__ void start(ConvWord *) {}
-    __device__ __forceinline__ void add(uint64_t y, ConvWord *h, uint32_t k) { s.add(y, h[k]); }
+    __device__ __forceinline__ void add(uint64_t y, ConvWord *h, uint32_t k) { s.add(join_word(y), h[k]); }
     template <class A>
     __device__ __forceinline__ typename A::V value(const A &ar, ConvWord *h, const Prime &P) const
     {
@@ -520,7 +532,10 @@ template <int NV, class Pos>
 __device__ __forceinline__ void bconv_load(uint64_t (&v)[NV], const IntArith &ar, const BcSrc &b, const Prime &P,
                                            size_t N, Pos pos)
 {
-    bconv_acc<WideAcc<MacColsAcc>>(v, ar, b, P, N, pos);
+    if (((ConvWord *)b.hm)[kConvStart])
+        bconv_acc<FoldWideAcc>(v, ar, b, P, N, pos);
+    else
+        bconv_acc<WideAcc<MacColsAcc>>(v, ar, b, P, N, pos);
 }
 
 // ------------------------------------------------------------------ N = 2^16
@@ -1301,6 +1316,10 @@ __global__ __launch_bounds__(64) void k12_fwd_rows(NttArgs a)
         fwd_rows12<EPI>(a, lp, int_arith(a, P, lp.prime, 4096), L, blockIdx.x, threadIdx.x);
 }
 
+// inv_store's mode for a conversion's sources (Rescale lifts plain coefficients)
+template <int MODE>
+constexpr uint32_t kSourceMode = MODE == COLS_MODDOWN ? 2 : MODE == COLS_MODUP ? 1 : 0;
+
 // Second inverse pass of a source row's 8 columns, scaled: canonical inputs of
 // the conversion (shifted for ModDown) to the tile y, element lane + 64 i.  The
 // first pass's output comes from m, or (ROWS) is in y already, element 8 row + col.
@@ -1315,7 +1334,7 @@ __device__ __forceinline__ void source_cols12(const A &ar, const uint64_t *m, ui
     ar.reduce_all(v);
     inv64(ar, v, y, s, 1, [&](uint32_t p) { return 8 * p + col; });
     wave_sync();  // the exchange's reads are done: the tile takes the result
-    inv_store(y, v, ar, MODE == COLS_MODDOWN ? 2 : 1, [&](int i) { return lane + 64 * i; });
+    inv_store(y, v, ar, kSourceMode<MODE>, [&](int i) { return lane + 64 * i; });
 }
 
 // First inverse pass of a source row by one of the workgroup's waves (its row
@@ -1363,7 +1382,10 @@ __device__ __forceinline__ void conv12(double (&v)[8], const FpArith &ar, const 
 __device__ __forceinline__ void conv12(uint64_t (&v)[8], const IntArith &ar, const uint64_t *y, uint32_t ns, ConvWord *h,
                                        const Prime &P, uint32_t lane)
 {
-    conv12_acc<WideAcc<MacColsAcc>>(v, ar, y, ns, h, P, lane);
+    if (h[kConvStart])
+        conv12_acc<FoldWideAcc>(v, ar, y, ns, h, P, lane);
+    else
+        conv12_acc<WideAcc<MacColsAcc>>(v, ar, y, ns, h, P, lane);
 }
 
 // First forward pass of a target row's 8 columns, converted from the sources.
@@ -1576,14 +1598,15 @@ constexpr uint32_t kCols16Waves = 8;
 // hits 32 distinct 8-byte banks in both layouts.
 __device__ __forceinline__ uint32_t slot16(uint32_t e) { return e ^ (((e >> 6) & 7) << 2); }
 
+// wb: tw_fwd<4, 256, 1> of the lane, loaded by the caller ahead of the input.
 template <class A>
-__device__ __forceinline__ void fwd256(const A &ar, typename A::V (&v)[16], uint64_t *L, uint32_t lane)
+__device__ __forceinline__ void fwd256(const A &ar, typename A::V (&v)[16], const typename A::W (&wb)[15], uint64_t *L,
+                                       uint32_t lane)
 {
     const uint32_t col = lane & 3, s = lane >> 2;
-    typename A::W wa[15], wb[15];
+    typename A::W wa[15];
     tw_fwd<4, 256, 16>(wa, 0, ar, 1);  // s < 16: one group per twiddle, the same for all lanes
     fwd_rw<4>(v, wa, ar);
-    tw_fwd<4, 256, 1>(wb, 16 * s, ar, 1);
 #pragma unroll
     for (int i = 0; i < 16; ++i) L[slot16(lane + 64 * i)] = ar.to_bits(v[i]);
     wave_sync();
@@ -1621,7 +1644,7 @@ __device__ __forceinline__ void source_cols16(const A &ar, const uint64_t *m, ui
     for (int i = 0; i < 16; ++i) v[i] = ar.from_bits(m[lane + 64 * i]);
     ar.reduce_all(v);
     inv256(ar, v, y, lane);
-    inv_store(y, v, ar, MODE == COLS_MODDOWN ? 2 : 1, [&](int i) { return lane + 64 * i; });
+    inv_store(y, v, ar, kSourceMode<MODE>, [&](int i) { return lane + 64 * i; });
 }
 
 // v[i] = Conv(y)[lane + 64 i], G elements at a time (the sums of 8 FP64 targets
@@ -1654,7 +1677,10 @@ __device__ __forceinline__ void conv16(double (&v)[16], const FpArith &ar, const
 __device__ __forceinline__ void conv16(uint64_t (&v)[16], const IntArith &ar, const uint64_t *y, uint32_t ns, ConvWord *h,
                                        const Prime &P, uint32_t lane)
 {
-    conv16_acc<WideAcc<MacColsAcc>, 4>(v, ar, y, ns, h, P, lane);
+    if (h[kConvStart])
+        conv16_acc<FoldWideAcc, 8>(v, ar, y, ns, h, P, lane);
+    else
+        conv16_acc<WideAcc<MacColsAcc>, 4>(v, ar, y, ns, h, P, lane);
 }
 
 // First forward pass of a target tile to m, converted from the sources (lifted
@@ -1664,13 +1690,15 @@ __device__ __forceinline__ void target_cols16(const A &ar, const Prime &P, const
                                               uint64_t qlmod, uint64_t ql, uint64_t *L, uint64_t *m, uint32_t lane)
 {
     typename A::V v[16];
+    typename A::W wb[15];
+    tw_fwd<4, 256, 1>(wb, 16 * (lane >> 2), ar, 1);
     if (MODE == COLS_RESCALE) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) v[i] = ar.lift(y[lane + 64 * i], ql, qlmod, P);
     } else {
         conv16(v, ar, y, ns, h, P, lane);
     }
-    fwd256(ar, v, L, lane);
+    fwd256(ar, v, wb, L, lane);
 #pragma unroll
     for (int i = 0; i < 16; ++i) m[lane + 64 * i] = ar.to_bits(v[i]);
 }

@@ -1,7 +1,8 @@
 // CPU check of the base conversions' constant rows (conv_row.h) with the
 // kernels' own sums (modarith.h): FoldSum for targets below 2^50 and at most
-// kFoldMaxTerms source rows, MacSplit's exact columns for more, against the
-// exact sum of y_i [B/b_i]_c reduced by 128-bit arithmetic.
+// kFoldMaxTerms source rows, FoldSumWide above 2^50 where the row says so,
+// MacSplit's exact columns for more source rows, against the exact sum of y_i
+// [B/b_i]_c reduced by 128-bit arithmetic.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -56,7 +57,7 @@ int main()
     int fails = 0;
     for (int sbits : {30, 50, 60, 61}) {
         const std::vector<uint64_t> all = primes_of(sbits, 16);
-        for (int tbits : {20, 30, 40, 50}) {
+        for (int tbits : {20, 30, 40, 50, 51, 60, 61}) {
             // a target outside the source basis
             const uint64_t c = primes_of(tbits, tbits == sbits ? 17 : 1).back();
             const FpMod m = {(double)c, 1.0 / (double)c};
@@ -87,9 +88,25 @@ int main()
                         }
                         want %= c;
                         uint64_t got;
-                        if (ns <= kFoldMaxTerms) {
-                            FoldSum s = {row[kConvStart], row[kConvStart + 1]};
-                            for (uint32_t i = 0; i < ns; ++i) s.add(y[i], row[2 * i], row[2 * i + 1]);
+                        if (c >= kFpMaxPrime) {
+                            if (!row[kConvStart]) {  // mac_cols: inline assembly, checked on the GPU
+                                if (rep == 0 && ns <= kFoldMaxTerms && sbits <= 50 && !shifted) {
+                                    std::printf("ns %u of %d bits into %d bits is not folded\n", ns, sbits, tbits);
+                                    ++fails;
+                                }
+                                continue;
+                            }
+                            FoldSumWide s = {{0, row[kConvStart + 1]}};
+                            for (uint32_t i = 0; i < ns; ++i) s.add(cut_word(y[i]), row[2 * i], row[2 * i + 1]);
+                            got = s.residue(c, m.qinv);
+                            if (!((double)got > 0.48 * (double)c && (double)got < 1.52 * (double)c)) {
+                                std::printf("ns %u c %llu: residue out of range\n", ns, (unsigned long long)c);
+                                ++fails;
+                            }
+                            got %= c;
+                        } else if (ns <= kFoldMaxTerms) {
+                            FoldSum s = {{row[kConvStart], row[kConvStart + 1]}};
+                            for (uint32_t i = 0; i < ns; ++i) s.add(cut_word(y[i]), row[2 * i], row[2 * i + 1]);
                             const double r = s.residue(m), bound = (0.5 + 0x1p-14) * (double)c + 0x1p32;
                             if (!(r <= bound && r >= -bound)) {
                                 std::printf("ns %u c %llu: |residue| %g above %g\n", ns, (unsigned long long)c, r, bound);
@@ -98,7 +115,7 @@ int main()
                             got = fp_canonical(r, m);
                         } else {
                             MacSplit s;
-                            for (uint32_t i = 0; i < ns; ++i) s.add(y[i], row[i]);
+                            for (uint32_t i = 0; i < ns; ++i) s.add(join_word(cut_word(y[i])), row[i]);
                             got = addmod(reduce128(s.total(), P), row[kConvStart + 1], c);
                         }
                         if (got != (uint64_t)want) {
