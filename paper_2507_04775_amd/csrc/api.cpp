@@ -66,9 +66,14 @@ hipError_t modup_from_coeffs(const ckks_ctx *c, const uint64_t *d, uint32_t g, u
     return launch_ntt_stage(STAGE_FWD_PLAIN, a, s.beta * s.rows - s.n, st);
 }
 
+// Whether ModUp can leave its last forward pass to the inner product: where its column launch runs.
+bool modup_in_tiles(const ckks_ctx *c, uint32_t level)
+{
+    return c->logn == 12 || cols16_fits(std::min(c->alpha, level + 1));
+}
+
 // ModUp of phi_g(d) (of a1 b1 with tin) into ext, the digits' own rows left out.  finish: false leaves
-// the last forward pass to the inner product (N = 2^12, where the transforms run in their two passes
-// and the conversion inside the column launch).
+// the last forward pass to the inner product, where modup_in_tiles.
 hipError_t modup(const ckks_ctx *c, const uint64_t *d, uint32_t g, uint32_t level, const KsWs &w, const TensorIn *tin,
                  bool finish, hipStream_t st)
 {
@@ -83,17 +88,17 @@ hipError_t modup(const ckks_ctx *c, const uint64_t *d, uint32_t g, uint32_t leve
     const uint32_t converted = s.beta * s.rows - s.n;
     hipError_t e = hipSuccess;
     if (c->logn == 16) {
-        // the row pass can't work in place on tiles: the column launch writes to the workspace behind
-        // ext (acc, pc and conv, not in use yet), which holds 4 (l + 1 + K) rows
-        if (!cols16_fits(ns) || s.beta > 4) {
+        // the row pass can't work in place on tiles: the column launch before it writes to the workspace
+        // behind ext (acc, pc and conv, not in use yet), which holds 4 (l + 1 + K) rows
+        if (!cols16_fits(ns) || (finish && s.beta > 4)) {
             e = launch_ntt_stage(first, ia, s.n, st);
             return e == hipSuccess ? modup_from_coeffs(c, d, g, level, w.dc, w.ext, false, st) : e;
         }
         ia.tiled = fa.tiled = 1;
-        ca.dst = fa.mid = w.acc;
+        if (finish) ca.dst = fa.mid = w.acc;
         e = launch_ntt_stage(first, ia, s.n, st, 0, 0);
         if (e == hipSuccess) e = launch_cols16(COLS_MODUP, ca, s.beta, st);
-        return e == hipSuccess ? launch_ntt_stage(STAGE_FWD_PLAIN, fa, converted, st, 1, 1) : e;
+        return e == hipSuccess && finish ? launch_ntt_stage(STAGE_FWD_PLAIN, fa, converted, st, 1, 1) : e;
     }
     NttPro pro = PRO_MID;
     if (ns <= split12_row_sources()) {
@@ -147,7 +152,7 @@ hipError_t moddown(const ckks_ctx *c, const uint64_t *acc, int64_t acc_stride, u
 
 // The inner product ip, with the first pass of ModDown's INTT on the special rows in its launch, and
 // the ModDown of its two accumulators (in w) into out.  ready: ip.ext holds finished transforms (see
-// modup; always so at N = 2^16).
+// modup).
 hipError_t ip_moddown(const ckks_ctx *c, const IpArgs &ip, bool ready, uint32_t level, uint64_t *const *out,
                       const uint64_t *const *add, uint32_t g, const KsWs &w, hipStream_t st)
 {
@@ -156,7 +161,8 @@ hipError_t ip_moddown(const ckks_ctx *c, const IpArgs &ip, bool ready, uint32_t 
     NttArgs ia = args_moddown_intt(c, w.acc, acc_stride, level, w.pc);
     ia.tiled = c->logn == 16 && cols16_fits(c->np);
     hipError_t e = c->logn == 12 ? launch_split12_ip(ip, ia, base_args(c, false), ready, st)
-                                 : launch_inner_product_rowpass(ip, ia, st);
+                   : ready       ? launch_inner_product_rowpass(ip, ia, st)
+                                 : launch_ip_rows16(ip, ia, base_args(c, false), st);
     return e == hipSuccess ? moddown(c, w.acc, acc_stride, 2, level, out, add, g, w.pc, w.conv, st, true) : e;
 }
 
@@ -191,7 +197,7 @@ hipError_t keyswitch_core(const ckks_ctx *c, const uint64_t *d, uint32_t g_in, u
     }
     uint64_t *outs[2] = {out0, out1};
     const uint64_t *adds[2] = {add0, add1};
-    return ip_moddown(c, ip, c->logn != 12, level, outs, adds, g_add, w, st);
+    return ip_moddown(c, ip, !modup_in_tiles(c, level), level, outs, adds, g_add, w, st);
 }
 
 }  // namespace ckks
@@ -255,6 +261,20 @@ uint32_t galois_of_rotation(const ckks_ctx *c, int32_t k)
 
 }  // namespace
 
+namespace {
+
+// The key switch ip of phi_g(d) up to its extended accumulators (ip.acc, or ip.fold_tot)
+hipError_t extended(const ckks_ctx *c, const uint64_t *d, uint32_t g, uint32_t level, const KsWs &w, const IpArgs &ip,
+                    hipStream_t st)
+{
+    const bool tiles = c->logn == 16 && modup_in_tiles(c, level);
+    hipError_t e = modup(c, d, g, level, w, nullptr, !tiles, st);
+    if (e != hipSuccess) return e;
+    return tiles ? launch_ip_rows16(ip, NttArgs(), base_args(c, false), st) : launch_inner_product(ip, st);
+}
+
+}  // namespace
+
 namespace ckks {
 
 hipError_t keyswitch_extended(ckks_ctx *c, const uint64_t *d, uint32_t g, uint32_t level, const uint64_t *key,
@@ -262,22 +282,18 @@ hipError_t keyswitch_extended(ckks_ctx *c, const uint64_t *d, uint32_t g, uint32
 {
     KsWs w = ks_ws(c, level, ws);
     *acc = w.acc;
-    hipError_t e = modup(c, d, g, level, w, nullptr, true, st);
-    if (e == hipSuccess) e = inner_product(c, w.ext, level, key, 1, w.acc, st, d, g);
-    return e;
+    return extended(c, d, g, level, w, args_ip(c, w.ext, level, key, 1, w.acc, d, g), st);
 }
 
 hipError_t keyswitch_extended_fold(ckks_ctx *c, const uint64_t *d, uint32_t g, uint32_t level, const uint64_t *key,
                                    void *ws, hipStream_t st, const uint64_t *c0, uint64_t *tot, bool first)
 {
     KsWs w = ks_ws(c, level, ws);
-    hipError_t e = modup(c, d, g, level, w, nullptr, true, st);
-    if (e != hipSuccess) return e;
     IpArgs ip = args_ip(c, w.ext, level, key, 1, w.acc, d, g);
     ip.fold_c0 = c0;
     ip.fold_tot = tot;
     ip.fold_first = first ? 1 : 0;
-    return launch_inner_product(ip, st);
+    return extended(c, d, g, level, w, ip, st);
 }
 
 hipError_t moddown_pair(ckks_ctx *c, const uint64_t *x, uint32_t level, uint64_t *out0, uint64_t *out1, void *ws,

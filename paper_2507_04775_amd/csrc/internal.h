@@ -417,6 +417,9 @@ hipError_t launch_inner_product(const IpArgs &a, hipStream_t stream);  // ta0 se
 // same accumulators), with that INTT's first pass on the special rows run by the same launch; the
 // INTT then runs with first_pass 1.  The special rows of ip.acc are not written.
 hipError_t launch_inner_product_rowpass(const IpArgs &ip, const NttArgs &ia, hipStream_t stream);
+// The same on launch_cols16's output in ip.ext, whose last forward pass runs here too (fa: any forward
+// arguments, for the tables).  ia.mid null: all rows' sums to ip.acc, or into ip.fold_tot.
+hipError_t launch_ip_rows16(const IpArgs &ip, const NttArgs &ia, const NttArgs &fa, hipStream_t stream);
 // ---- The column launch of a conversion (N = 2^12, in split transforms of 64 x 64; N = 2^16, tiled): job j takes its ns source rows through the second inverse pass
 // (times the conversion scale), converts them to its target rows and runs those through the first
 // forward pass.  COLS_MODUP: job j is digit j, targets every extended row but its own.  COLS_MODDOWN:

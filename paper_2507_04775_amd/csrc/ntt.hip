@@ -94,6 +94,7 @@ struct IntArith {
     typedef u128 Sum;
     __device__ __forceinline__ void sum_start(Sum &s) const { s = {0, 0}; }
     __device__ __forceinline__ void sum_add(Sum &s, V x, uint64_t k) const { s = add128(s, mul_wide(x, k)); }
+    __device__ __forceinline__ void sum_centre(Sum &) const {}
     __device__ __forceinline__ V sum_value(const Sum &s, const Prime &P) const { return reduce128(s, P); }
     __device__ __forceinline__ V sum_input(V x) const { return fwd_final(x); }  // of a forward output
     // c (aux - x) + add for a forward output x and canonical aux, add: P^-1 (acc - Conv) + add of
@@ -155,14 +156,12 @@ struct FpArith {
     __device__ __forceinline__ uint64_t fwd_final(V x) const { return fp_canonical(x, m); }
     __device__ __forceinline__ uint64_t inv_final(V x) const { return fp_canonical(fp_mulmod(x, fc, m), m); }
     __device__ __forceinline__ uint64_t modulus() const { return (uint64_t)m.q; }
-    // sums of products re-centred term by term
+    // sums of products, each below 2.9 q: sum_centre after every second term at the latest
     typedef double Sum;
     __device__ __forceinline__ void sum_start(Sum &s) const { s = 0.0; }
-    __device__ __forceinline__ void sum_add(Sum &s, V x, uint64_t k) const
-    {
-        s = fp_reduce(s + fp_mulmod(x, fp_from_word(k), m), m);
-    }
-    __device__ __forceinline__ V sum_value(const Sum &s, const Prime &) const { return s; }
+    __device__ __forceinline__ void sum_add(Sum &s, V x, uint64_t k) const { s += fp_mulmod(x, fp_from_word(k), m); }
+    __device__ __forceinline__ void sum_centre(Sum &s) const { s = fp_reduce(s, m); }
+    __device__ __forceinline__ V sum_value(const Sum &s, const Prime &) const { return fp_reduce(s, m); }
     __device__ __forceinline__ V sum_input(V x) const { return x; }
     // as IntArith's; |x| < 5.3 q, |aux| <= q leave the difference below 2^53 and the product below 2.9 q
     __device__ __forceinline__ uint64_t scaled_difference(V x, V aux, uint64_t add, ulonglong2 c) const
@@ -761,30 +760,13 @@ __device__ __forceinline__ void fwd_row_unit(const NttArgs &a, uint32_t limb, ui
         fwd_row_body<EPI, TW>(a, lp, P, int_arith(a, P, lp.prime, 65536), lds, tile, tx);
 }
 
-template <int PRO, int TW, class A>
-__device__ __forceinline__ void inv_row_body(const NttArgs &a, const LimbPos &lp, const Prime &P, const A &ar,
-                                             uint64_t *lds, uint32_t tile, uint32_t tx)
+// The rounds of row b from the narrow layout on, output m (mid_row<32>); wa: the first round's
+// twiddles, L the row's scratch.
+template <class A>
+__device__ __forceinline__ void inv_row_rounds(const A &ar, typename A::V (&v)[8], const typename A::W (&wa)[6],
+                                               uint64_t *L, uint32_t s, uint32_t b, MidRow m)
 {
-    const uint32_t blk = tx >> 5, s = tx & 31, b = pass_row<TW>(a, tile, blk);
-    const size_t row_off = (int64_t)lp.poly * a.map.src_poly_stride + (size_t)lp.row * 65536;
-    const uint64_t *src = a.src + row_off;
-    uint64_t *L = lds + blk * 256;
-    typename A::W wa[6], wb[7], wc[7];
-    tw_inv<2, 256, 1, A, true>(wa, 8 * s, ar, 256 + b);
-    tw_inv<2, 256, 1, A, true>(wa + 3, 8 * s + 4, ar, 256 + b);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const uint32_t e = b * 256 + pos_wide(s, i);
-        if (PRO == PRO_TENSOR)  // HMult's d2 = a1 b1, formed on the fly in the limb's arithmetic
-            L[row_slot(pos_wide(s, i))] = ar.to_bits(ar.product(src[e], a.src2[row_off + e], P));
-        else
-            L[row_slot(pos_wide(s, i))] = src[PRO == PRO_GALOIS ? galois_src(e, a.galois, 16) : e];
-    }
-    wave_sync();
-    typename A::V v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        v[i] = PRO == PRO_TENSOR ? ar.from_bits(L[row_slot(pos_narrow(s, i))]) : ar.from_u64(L[row_slot(pos_narrow(s, i))]);
+    typename A::W wb[7], wc[7];
     ar.reduce_all(v);
     inv_rw<2>(v, wa, ar);
     inv_rw<2>(v + 4, wa + 3, ar);
@@ -804,9 +786,36 @@ __device__ __forceinline__ void inv_row_body(const NttArgs &a, const LimbPos &lp
     for (int i = 0; i < 8; ++i) v[i] = ar.from_bits(L[row_slot(pos_wide(s, i))]);
     ar.reduce_all(v);
     inv_rw<3>(v, wc, ar);
-    const MidRow m = mid_row<32>(a, a.mid + (int64_t)lp.poly * a.mid_stride + (size_t)lp.row * 65536, b, s);
 #pragma unroll
     for (int i = 0; i < 8; ++i) m.p[i * m.step] = ar.to_bits(v[i]);
+}
+
+template <int PRO, int TW, class A>
+__device__ __forceinline__ void inv_row_body(const NttArgs &a, const LimbPos &lp, const Prime &P, const A &ar,
+                                             uint64_t *lds, uint32_t tile, uint32_t tx)
+{
+    const uint32_t blk = tx >> 5, s = tx & 31, b = pass_row<TW>(a, tile, blk);
+    const size_t row_off = (int64_t)lp.poly * a.map.src_poly_stride + (size_t)lp.row * 65536;
+    const uint64_t *src = a.src + row_off;
+    uint64_t *L = lds + blk * 256;
+    typename A::W wa[6];
+    tw_inv<2, 256, 1, A, true>(wa, 8 * s, ar, 256 + b);
+    tw_inv<2, 256, 1, A, true>(wa + 3, 8 * s + 4, ar, 256 + b);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const uint32_t e = b * 256 + pos_wide(s, i);
+        if (PRO == PRO_TENSOR)  // HMult's d2 = a1 b1, formed on the fly in the limb's arithmetic
+            L[row_slot(pos_wide(s, i))] = ar.to_bits(ar.product(src[e], a.src2[row_off + e], P));
+        else
+            L[row_slot(pos_wide(s, i))] = src[PRO == PRO_GALOIS ? galois_src(e, a.galois, 16) : e];
+    }
+    wave_sync();
+    typename A::V v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        v[i] = PRO == PRO_TENSOR ? ar.from_bits(L[row_slot(pos_narrow(s, i))]) : ar.from_u64(L[row_slot(pos_narrow(s, i))]);
+    inv_row_rounds(ar, v, wa, L, s, b,
+                   mid_row<32>(a, a.mid + (int64_t)lp.poly * a.mid_stride + (size_t)lp.row * 65536, b, s));
 }
 
 template <int PRO, int TW = 16>
@@ -893,16 +902,16 @@ __device__ __forceinline__ uint32_t row4_slot(uint32_t e)
 __device__ __forceinline__ uint32_t col4_slot(uint32_t e, uint32_t col) { return 8 * (e + (e >> 2)) + col; }
 constexpr int kLds4 = 8 * (255 + 63 + 1);
 
-// The rounds of one row: thread s < 64 of the row's wave, element loads
-// load(i) at position p4a(s, i), scratch L (256 words), output m (mid_row<64>).
-template <class A, class Load>
-__device__ __forceinline__ void inv_row4_rounds(const A &ar, uint64_t *L, uint32_t s, uint32_t b, Load load, MidRow m)
+// The rounds of one row: thread s < 64 of the row's wave, values
+// value(i) at position p4a(s, i), scratch L (256 words), output m (mid_row<64>).
+template <class A, class Value>
+__device__ __forceinline__ void inv_row4_values(const A &ar, uint64_t *L, uint32_t s, uint32_t b, Value value, MidRow m)
 {
     typename A::W wa[3], wb[3];
     typename A::V v[4];
     tw_inv<2, 256, 1, A, true>(wa, p4a(s, 0), ar, 256 + b);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = ar.from_u64(load(i));
+    for (int i = 0; i < 4; ++i) v[i] = value(i);
     ar.reduce_all(v);
     inv_rw<2>(v, wa, ar);
     tw_inv<2, 256, 4, A, true>(wb, p4b(s, 0), ar, 256 + b);
@@ -931,6 +940,12 @@ __device__ __forceinline__ void inv_row4_rounds(const A &ar, uint64_t *L, uint32
     inv_rw<2>(v, wb, ar);
 #pragma unroll
     for (int i = 0; i < 4; ++i) m.p[i * m.step] = ar.to_bits(v[i]);
+}
+
+template <class A, class Load>
+__device__ __forceinline__ void inv_row4_rounds(const A &ar, uint64_t *L, uint32_t s, uint32_t b, Load load, MidRow m)
+{
+    inv_row4_values(ar, L, s, b, [&](int i) { return ar.from_u64(load(i)); }, m);
 }
 
 template <class A>
@@ -1532,10 +1547,16 @@ __device__ __forceinline__ void ip_rows12(const IpArgs &ip, const NttArgs &ia, c
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) fwd.sum_add(sum[i], v[i], k[i]);
+        if (j & 1) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) fwd.sum_centre(sum[i]);
+        }
     }
     if (qrow && ip.ta0) {
         const uint64_t pm = ip.pmod[pi];
         uint64_t x[8], y[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) fwd.sum_centre(sum[i]);
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = ip.ta0[off + e0 + i], y[i] = (half ? ip.tb1 : ip.tb0)[off + e0 + i];
 #pragma unroll
@@ -1770,6 +1791,188 @@ __global__ __launch_bounds__(64 * kCols16Waves) void k16_cols(ColsArgs a)
         else
             target_cols16<MODE>(int_arith(a.twf, P, pi, 65536), P, lds16, ns, h, qlmod, ql, L, m, lane);
     }
+}
+
+// The key inner product at N = 2^16 on ModUp's tiles: the last forward pass of
+// every digit's row runs here, so the finished transforms never go through
+// memory.  A wave takes one row of the 256 x 256 view of extended row r, 4
+// elements per lane in the layouts of the 4-element inverse passes (D, C, B, A);
+// it ends in A, four consecutive positions, in which the keys are read and the
+// sums stored, and from which ModDown's first inverse pass starts.  (With 8
+// elements per lane the sums of both halves, 64 registers on the integer path,
+// leave one wave per SIMD.)  A digit's own row comes from ip.own (gathered
+// through ip.own_galois) or, with a tensor, is the product a1 b1.
+// IP_MODDOWN, IP_TENSOR: the special rows, whose workgroups come first, go on to
+// ModDown's first inverse pass.  IP_EXTENDED: all rows' sums are stored, or
+// accumulated (see IpArgs).
+enum IpMode { IP_MODDOWN, IP_TENSOR, IP_EXTENDED };
+// Four rows a workgroup read 128-byte runs of the tiles: 56 us at l = 30 with a
+// tensor (digits of 12, 35 rows; 250 MB, 50 us at the rate of a copy) where eight
+// rows take 58, two 60, sixteen 65, and the row pass and the inner product apart
+// 25 + 47.  A rotation's at l = 17 takes 24 us for 12 + 20.
+constexpr uint32_t kIpRows = 4;
+
+// The rounds of a forward row pass from layout D to layout A.
+template <class A>
+__device__ __forceinline__ void fwd_row4_rounds(const A &ar, typename A::V (&v)[4], uint64_t *L, uint32_t s, uint32_t b)
+{
+    typename A::W w[3], w2[3];
+    tw_fwd<2, 256, 64, A, true>(w, p4d(s, 0), ar, 256 + b);
+    tw_fwd<2, 256, 16, A, true>(w2, p4c(s, 0), ar, 256 + b);
+    ar.reduce_all(v);
+    fwd_rw<2>(v, w, ar);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) L[row4_slot(p4d(s, i))] = ar.to_bits(v[i]);
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = ar.from_bits(L[row4_slot(p4c(s, i))]);
+    tw_fwd<2, 256, 4, A, true>(w, p4b(s, 0), ar, 256 + b);
+    fwd_rw<2>(v, w2, ar);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) L[row4_slot(p4c(s, i))] = ar.to_bits(v[i]);
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = ar.from_bits(L[row4_slot(p4b(s, i))]);
+    tw_fwd<2, 256, 1, A, true>(w2, p4a(s, 0), ar, 256 + b);
+    ar.reduce_all(v);
+    fwd_rw<2>(v, w, ar);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) L[row4_slot(p4b(s, i))] = ar.to_bits(v[i]);
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = ar.from_bits(L[row4_slot(p4a(s, i))]);
+    wave_sync();
+    fwd_rw<2>(v, w2, ar);
+}
+
+template <IpMode MODE, class A>
+__device__ __forceinline__ void ip_rows16(const IpArgs &ip, const NttArgs &ia, const A &fwd, const A &inv, const Prime &P,
+                                          uint32_t r, uint32_t pi, uint64_t *L, uint32_t b, uint32_t s)
+{
+    const bool qrow = r <= ip.level;
+    const uint32_t own = qrow ? r / ip.alpha : ~0u, e0 = b * 256 + 4 * s;
+    const size_t off = (size_t)r * 65536, kstep = (size_t)(ip.nq + ip.np) * 65536;
+    const uint32_t g = ip.own_galois, sb = MODE == IP_TENSOR || g == 1 ? b * 256 : galois_src(b * 256, g, 16) & ~255u;
+    const uint64_t *mid = ip.ext + off + (s >> 2) * 1024 + (b & 15) * 64 + (b >> 4) * 4 + (s & 3);
+    auto read = [&](uint64_t (&x)[4], const uint64_t *p) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = p[i];
+    };
+    auto gather = [&](uint64_t (&x)[4], const uint64_t *row) {  // x = phi_g(row) at e0
+        read(x, row + sb + 4 * s);
+        if (g == 1) return;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) L[row4_slot(p4a(s, i))] = x[i];
+        wave_sync();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = L[row4_slot(galois_src(e0 + i, g, 16) - sb)];
+        wave_sync();
+    };
+    typename A::Sum s0[4], s1[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fwd.sum_start(s0[i]), fwd.sum_start(s1[i]);
+    for (uint32_t j = 0; j < ip.beta; ++j) {
+        const uint64_t *key = ip.key + (size_t)j * 2 * kstep + (size_t)pi * 65536 + e0;
+        uint64_t k0[4], k1[4], x[4];
+        typename A::V v[4];
+        if (j != own) {
+            const uint64_t *m = mid + (size_t)j * ip.rows * 65536;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = m[i * 16384];
+            read(k0, key);
+            read(k1, key + kstep);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = fwd.from_bits(x[i]);
+            fwd_row4_rounds(fwd, v, L, s, b);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = fwd.sum_input(v[i]);
+        } else {
+            read(k0, key);
+            read(k1, key + kstep);
+            if (MODE == IP_TENSOR) {
+                uint64_t y[4];
+                read(x, ip.ta1 + off + e0);
+                read(y, ip.tb1 + off + e0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = fwd.product(x[i], y[i], P);
+            } else {
+                gather(x, ip.own + off);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = fwd.from_u64(x[i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) fwd.sum_add(s0[i], v[i], k0[i]), fwd.sum_add(s1[i], v[i], k1[i]);
+        if (j & 1) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) fwd.sum_centre(s0[i]), fwd.sum_centre(s1[i]);
+        }
+    }
+    if (MODE == IP_TENSOR && qrow) {
+        const uint64_t pm = ip.pmod[pi];
+        uint64_t a0[4], a1[4], b0[4], b1[4];
+        read(a0, ip.ta0 + off + e0);
+        read(b0, ip.tb0 + off + e0);
+        read(a1, ip.ta1 + off + e0);
+        read(b1, ip.tb1 + off + e0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            fwd.sum_centre(s0[i]), fwd.sum_centre(s1[i]);
+            fwd.sum_add(s0[i], fwd.product(a0[i], b0[i], P), pm);
+            fwd.sum_add(s1[i], fwd.product(a0[i], b1[i], P), pm);
+            fwd.sum_add(s1[i], fwd.product(a1[i], b0[i], P), pm);
+        }
+    }
+    if (MODE == IP_EXTENDED && ip.fold_tot && ip.fold_c0 && qrow) {
+        const uint64_t pm = ip.pmod[pi];
+        uint64_t x[4];
+        gather(x, ip.fold_c0 + off);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) fwd.sum_centre(s0[i]), fwd.sum_add(s0[i], fwd.from_u64(x[i]), pm);
+    }
+    if (MODE == IP_EXTENDED || qrow) {
+        const bool fold = MODE == IP_EXTENDED && ip.fold_tot, more = fold && !ip.fold_first;
+        uint64_t *out = (fold ? ip.fold_tot : ip.acc) + off + e0;
+        const size_t half = (size_t)ip.rows * 65536;
+        uint64_t t0[4] = {}, t1[4] = {};
+        if (more) {
+            read(t0, out);
+            read(t1, out + half);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint64_t y0 = fwd.fwd_final(fwd.sum_value(s0[i], P)), y1 = fwd.fwd_final(fwd.sum_value(s1[i], P));
+            t0[i] = more ? addmod(t0[i], y0, P.q) : y0;
+            t1[i] = more ? addmod(t1[i], y1, P.q) : y1;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = t0[i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[half + i] = t1[i];
+        return;
+    }
+#pragma unroll
+    for (uint32_t t = 0; t < 2; ++t) {
+        uint64_t *limb = ia.mid + (int64_t)t * ia.mid_stride + (size_t)(r - ip.level - 1) * 65536;
+        wave_sync();
+        inv_row4_values(inv, L, s, b, [&](int i) { return fwd.sum_value(t ? s1[i] : s0[i], P); }, mid_row<64>(ia, limb, b, s));
+    }
+}
+
+template <IpMode MODE>
+__global__ __launch_bounds__(64 * kIpRows) void k16_ip_rows(IpArgs ip, NttArgs ia, const ulonglong2 *twf, const double *twdf)
+{
+    __shared__ uint64_t lds[kIpRows * 256];
+    const uint32_t y = blockIdx.y, nqr = ip.level + 1, nsp = ip.rows - nqr, r = y < nsp ? nqr + y : y - nsp;
+    const uint32_t pi = coef::row_prime(r, ip.level, ip.nq), s = threadIdx.x & 63;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), groups = 16 / kIpRows;
+    const uint32_t b = 16 * (blockIdx.x % groups * kIpRows + w) + blockIdx.x / groups;
+    uint64_t *L = lds + w * 256;
+    const Prime P = ip.primes[pi];
+    if (P.q < kFpMaxPrime)
+        ip_rows16<MODE>(ip, ia, fp_arith(twdf, P, pi, 65536), fp_arith(ia.twd, P, pi, 65536), P, r, pi, L, b, s);
+    else
+        ip_rows16<MODE>(ip, ia, int_arith(twf, P, pi, 65536), int_arith(ia.tw, P, pi, 65536), P, r, pi, L, b, s);
 }
 
 // ---------------------------------------------------- kernels: grid and queue
@@ -2402,6 +2605,23 @@ hipError_t launch_inner_product_rowpass(const IpArgs &ip, const NttArgs &ia, hip
     } else {
         hipLaunchKernelGGL(k_inner_product_rowpass, grid, dim3(coef::kCoefThreads), 0, stream, ip, ia);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_ip_rows16(const IpArgs &ip, const NttArgs &ia, const NttArgs &fa, hipStream_t stream)
+{
+    const bool extended = !ia.mid;
+    if (ip.logn != 16 || ip.galois != 1 || ip.rows != ip.level + 1 + ip.np || (!ip.own && !ip.ta0) ||
+        (extended ? ip.ta0 != nullptr : ip.fold_tot || ia.logn != 16 || ia.map.rows != ip.np || ia.ys_mode != 2) ||
+        (ip.ta0 && (!ip.ta1 || !ip.tb0 || !ip.tb1 || !ip.pmod)))
+        return hipErrorInvalidValue;
+    const dim3 grid(256 / kIpRows, ip.rows), block(64 * kIpRows);
+    if (extended)
+        hipLaunchKernelGGL(k16_ip_rows<IP_EXTENDED>, grid, block, 0, stream, ip, ia, fa.tw, fa.twd);
+    else if (ip.ta0)
+        hipLaunchKernelGGL(k16_ip_rows<IP_TENSOR>, grid, block, 0, stream, ip, ia, fa.tw, fa.twd);
+    else
+        hipLaunchKernelGGL(k16_ip_rows<IP_MODDOWN>, grid, block, 0, stream, ip, ia, fa.tw, fa.twd);
     return hipGetLastError();
 }
 
