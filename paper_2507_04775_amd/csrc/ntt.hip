@@ -59,6 +59,12 @@ struct IntArith {
     __device__ __forceinline__ W tw(uint32_t i) const { return T[i]; }
     // the twiddle at hi + k (k below the lowest set bit of hi): read from the table
     __device__ __forceinline__ W tw_split(uint32_t hi, uint32_t k) const { return T[hi + k]; }
+    // the same twiddle for all lanes, through the scalar cache
+    __device__ __forceinline__ W tw_uniform(uint32_t i) const
+    {
+        const auto *t = (const __attribute__((address_space(4))) uint64_t *)T;
+        return make_ulonglong2(t[2 * i], t[2 * i + 1]);
+    }
     // [x y]_q of two canonical residues (HMult's d2 = a1 b1 as it is loaded)
     __device__ __forceinline__ V product(uint64_t x, uint64_t y, const Prime &P) const
     {
@@ -128,6 +134,10 @@ struct FpArith {
     // inverse), and br(hi + k) = br(hi) + br(k) for such k, so it is T[hi] T[k], formed here (a
     // centred representative) from the row's one entry and the first entries shared by every row
     __device__ __forceinline__ W tw_split(uint32_t hi, uint32_t k) const { return fp_mulmod(T[hi], T[k], m); }
+    __device__ __forceinline__ W tw_uniform(uint32_t i) const
+    {
+        return ((const __attribute__((address_space(4))) double *)T)[i];
+    }
     // [x y]_q of two canonical residues below 2^50, a centred representative
     __device__ __forceinline__ V product(uint64_t x, uint64_t y, const Prime &) const
     {
@@ -1626,7 +1636,8 @@ __device__ __forceinline__ void fwd256(const A &ar, typename A::V (&v)[16], cons
 {
     const uint32_t col = lane & 3, s = lane >> 2;
     typename A::W wa[15];
-    tw_fwd<4, 256, 16>(wa, 0, ar, 1);  // s < 16: one group per twiddle, the same for all lanes
+#pragma unroll
+    for (int i = 0; i < 15; ++i) wa[i] = ar.tw_uniform(1 + i);  // tw_fwd<4, 256, 16>: the same for all lanes
     fwd_rw<4>(v, wa, ar);
 #pragma unroll
     for (int i = 0; i < 16; ++i) L[slot16(lane + 64 * i)] = ar.to_bits(v[i]);
@@ -1644,7 +1655,8 @@ __device__ __forceinline__ void inv256(const A &ar, typename A::V (&v)[16], uint
     const uint32_t col = lane & 3, s = lane >> 2;
     typename A::W wa[15], wb[15];
     tw_inv<4, 256, 1>(wb, 16 * s, ar, 1);
-    tw_inv<4, 256, 16>(wa, 0, ar, 1);
+#pragma unroll
+    for (int i = 0; i < 15; ++i) wa[i] = ar.tw_uniform(i < 8 ? 8 + i : i < 12 ? i - 4 : i < 14 ? i - 10 : 1);
     inv_rw<4>(v, wb, ar);
 #pragma unroll
     for (int i = 0; i < 16; ++i) L[slot16(64 * s + 4 * i + col)] = ar.to_bits(v[i]);
@@ -1668,8 +1680,9 @@ __device__ __forceinline__ void source_cols16(const A &ar, const uint64_t *m, ui
     inv_store(y, v, ar, kSourceMode<MODE>, [&](int i) { return lane + 64 * i; });
 }
 
-// v[i] = Conv(y)[lane + 64 i], G elements at a time (the sums of 8 FP64 targets
-// or 4 integer ones stay in registers).
+// v[i] = Conv(y)[lane + 64 i], G elements at a time: all 16 where two columns hold
+// a sum, so that a source's constants are fetched once (with 8, ModUp's launch of
+// HMult at l = 30 takes 46.3 us in place of 44.4), 4 with 128-bit sums.
 template <class Acc, int G, class A>
 __device__ __forceinline__ void conv16_acc(typename A::V (&v)[16], const A &ar, const uint64_t *y, uint32_t ns,
                                            ConvWord *h, const Prime &P, uint32_t lane)
@@ -1693,13 +1706,13 @@ __device__ __forceinline__ void conv16_acc(typename A::V (&v)[16], const A &ar, 
 __device__ __forceinline__ void conv16(double (&v)[16], const FpArith &ar, const uint64_t *y, uint32_t ns, ConvWord *h,
                                        const Prime &P, uint32_t lane)
 {
-    conv16_acc<FoldAcc, 8>(v, ar, y, ns, h, P, lane);
+    conv16_acc<FoldAcc, 16>(v, ar, y, ns, h, P, lane);
 }
 __device__ __forceinline__ void conv16(uint64_t (&v)[16], const IntArith &ar, const uint64_t *y, uint32_t ns, ConvWord *h,
                                        const Prime &P, uint32_t lane)
 {
     if (h[kConvStart])
-        conv16_acc<FoldWideAcc, 8>(v, ar, y, ns, h, P, lane);
+        conv16_acc<FoldWideAcc, 16>(v, ar, y, ns, h, P, lane);
     else
         conv16_acc<WideAcc<MacColsAcc>, 4>(v, ar, y, ns, h, P, lane);
 }
