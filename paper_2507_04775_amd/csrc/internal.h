@@ -412,7 +412,7 @@ hipError_t launch_tensor_queue(const TensorArgs *insts, const WorkQueue &q, uint
 hipError_t launch_zero_u32(uint32_t *p, uint32_t n, hipStream_t stream);
 // The one-launch batch kernel (N = 2^16 only): `grid` workgroups of 512 threads.
 hipError_t launch_fused_batch(const FusedArgs &f, uint32_t grid, hipStream_t stream);
-hipError_t launch_inner_product(const IpArgs &a, hipStream_t stream);  // ta0 set: the tensor form
+hipError_t launch_inner_product(const IpArgs &a, hipStream_t stream);  // without the tensor
 // N = 2^16: the inner product of a key switch whose ModDown INTT is `ia` (args_moddown_intt over the
 // same accumulators), with that INTT's first pass on the special rows run by the same launch; the
 // INTT then runs with first_pass 1.  The special rows of ip.acc are not written.
