@@ -124,10 +124,11 @@ ckks_status ckks_intt(ckks_ctx *ctx, uint64_t *poly, uint32_t limb0, uint32_t n_
  * pass has this form, and the plain inverse row pass (the ModDown and Rescale
  * INTTs, ckks_intt); the gathered and tensor row passes then use tiles of 8.  The choice holds per direction (inverse 0 / 1) and per number of
  * limbs in the launch (1..128), for every NTT launch of every operation in the
- * process; tile 0 restores the default (16 from 24 limbs up, 8 from 6, else 4;
- * inverse launches of at most 8 limbs 2).  Results do not depend on it.  An
- * autotuner sets it from measurements.  ckks_ntt_tile_get returns the code in
- * effect (0 for bad arguments).  Persistent batch kernels always use 16.
+ * process; tile 0 restores the default (16 from 8 limbs up, else 8; row passes
+ * next to a column launch 8 from 8 limbs up, else 4; inverse launches of at most
+ * 8 limbs 2).  Results do not depend on it.  An autotuner sets it from
+ * measurements.  ckks_ntt_tile_get returns the code in effect for a whole
+ * transform (0 for bad arguments).  Persistent batch kernels always use 16.
  */
 ckks_status ckks_ntt_tile_set(uint32_t inverse, uint32_t n_limbs, uint32_t tile);
 uint32_t ckks_ntt_tile_get(uint32_t inverse, uint32_t n_limbs);

@@ -2448,10 +2448,18 @@ static void set_heavy(NttArgs &a, uint32_t nlimbs)
 // by every grid launch.
 static std::atomic<uint8_t> g_tile[2][kMaxTileLimbs + 1];
 
-static uint32_t default_tile(uint32_t nlimbs)
+// The default.  Whole transforms: a column pass reads runs of 8 TW bytes, so 16
+// columns (whole lines) from 8 limbs on (12 limbs 12.4 us, 16.9 with 8, 18.8 with
+// 4), with rows alike, so that unit_of places a limb's passes on one XCD (24
+// limbs inverse 17.8 us, 21 with rows of 8); 8 below, for twice the workgroups (4
+// limbs 10.2 us, 11.7 with 16, 11.2 with 4).  A row pass alone (next to a column
+// launch) reads whole rows at any width: 8 rows, which spread more evenly than 16
+// (ModDown's over 36 limbs 18.2 us, 19.8 with 16, 18.1 to 23.4 with 4; Rescale's
+// over 24 limbs 11.9, 12.8, 12.7), 4 below 8 limbs (4 limbs 5.1 us, 5.8 with 8).
+static uint32_t default_tile(bool row_alone, uint32_t nlimbs)
 {
-    if (nlimbs >= 24) return 16;
-    return nlimbs >= 6 ? 8 : 4;
+    if (row_alone) return nlimbs >= 8 ? 8 : 4;
+    return nlimbs >= 8 ? 16 : 8;
 }
 
 // tile code 2 (the 4-element inverse passes) applies to inverse stages only; a pass without a
@@ -2466,13 +2474,13 @@ static bool four_element_pass(NttStage st, uint32_t pass, uint32_t tw)
     return tw == 2 && (pass == 1 || st == STAGE_INV_PLAIN);
 }
 
-static uint32_t tile_width(NttStage st, uint32_t logn, uint32_t nlimbs)
+static uint32_t tile_width(NttStage st, uint32_t logn, uint32_t nlimbs, bool row_alone)
 {
     if (logn != 16) return 16;
     const int inv = st == STAGE_INV_PLAIN || st == STAGE_INV_GALOIS || st == STAGE_INV_TENSOR;
     const uint32_t t = nlimbs <= kMaxTileLimbs ? g_tile[inv][nlimbs].load(std::memory_order_relaxed) : 0;
     if (t) return t;
-    return inv && nlimbs <= 8 ? 2 : default_tile(nlimbs);
+    return inv && nlimbs <= 8 ? 2 : default_tile(row_alone, nlimbs);
 }
 
 hipError_t launch_ntt_stage(NttStage st, const NttArgs &a0, uint32_t nlimbs, hipStream_t stream, uint32_t first_pass,
@@ -2481,7 +2489,8 @@ hipError_t launch_ntt_stage(NttStage st, const NttArgs &a0, uint32_t nlimbs, hip
     if (nlimbs == 0) return hipSuccess;
     if (first_pass >= ntt_passes(a0.logn)) return hipErrorInvalidValue;
     NttArgs a = a0;
-    const uint32_t tw = effective_tile(st, tile_width(st, a.logn, nlimbs));
+    const bool inverse = st == STAGE_INV_PLAIN || st == STAGE_INV_GALOIS || st == STAGE_INV_TENSOR;
+    const uint32_t tw = effective_tile(st, tile_width(st, a.logn, nlimbs, inverse ? last_pass == 0 : first_pass == 1));
     if (tw == 16) set_heavy(a, nlimbs);
     else a.n_heavy = 0;
     for (uint32_t pass = first_pass; pass < ntt_passes(a.logn) && pass <= last_pass; ++pass) {
@@ -2603,7 +2612,7 @@ bool ntt_tile_set(uint32_t inverse, uint32_t nlimbs, uint32_t tile)
 
 uint32_t ntt_tile_get(uint32_t inverse, uint32_t nlimbs)
 {
-    return tile_width(inverse ? STAGE_INV_PLAIN : STAGE_FWD_PLAIN, 16, nlimbs);
+    return tile_width(inverse ? STAGE_INV_PLAIN : STAGE_FWD_PLAIN, 16, nlimbs, false);
 }
 
 hipError_t launch_inner_product_rowpass(const IpArgs &ip, const NttArgs &ia, hipStream_t stream)
