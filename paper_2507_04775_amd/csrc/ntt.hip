@@ -8,8 +8,8 @@
 //
 // Layout of the work: threads own a few elements each and run several radix-2
 // stages on them in registers ("rounds"); rounds exchange data through LDS.
-// N = 2^12 fits one workgroup of 256 threads with 16 elements each (three
-// rounds of four stages).  N = 2^16 is the paper's 2-D / hierarchical scheme:
+// N = 2^12 fits one workgroup of 512 threads with 8 elements each (four rounds
+// of three stages); inside key switches it runs as 64 x 64 in two passes.  N = 2^16 is the paper's 2-D / hierarchical scheme:
 // viewed as a 256 x 256 matrix, a column pass runs the first eight stages
 // (each column is an independent 256-point problem) and a row pass runs the
 // last eight (each row of 256 contiguous elements is independent, with its own
@@ -1618,8 +1618,15 @@ __global__ __launch_bounds__(64) void k12_ip_rows(IpArgs ip, NttArgs ia, const u
 // of four stages with one exchange inside the wave.  No scaled coefficient or
 // converted row goes through memory, three launches are one, and a wave has
 // nothing to wait for but its LDS: the separate passes wrote and read every row
-// once more (they run at the memory's rate, not the VALU's) and spent half
-// their time between loads and stores.
+// once more and spent half their time between loads and stores.  ModUp's three
+// passes of HMult at l = 30 (digits of 12, K = 4) took 67 us, this launch 44;
+// ModDown's two 38, this 27; Rescale's two at l = 12 17, this 12.  What bounds it
+// is the VALU: ModUp's issues 10.4 M wave instructions, 23 us at the card's rate
+// for 64-bit multiply-adds, over 192 workgroups of a digit's tile each (a CU
+// takes one: LDS), 66 % of the issue slots of the CUs that have one; the rest is
+// the wait for the sources and the first loads.  Not kept: two targets per wave
+// over each source read from LDS (46 us; LDS does not bound it) and Rescale with
+// two workgroups per CU (128 registers spill: 20 us).
 // Lane layouts (col = lane % 4, s = lane / 4, element e = 4 row + col): A rows
 // s + 16 i, e = lane + 64 i; B rows 16 s + i, stored at 64 i + lane (mid_row).
 constexpr uint32_t kTile16 = 1024;
@@ -2394,8 +2401,9 @@ bool stage_kernels(NttStage st, uint32_t logn, int pass, StageKernels &k, uint32
     switch (st) {
     case STAGE_FWD_PLAIN:
         if (pass == 0) { SK16(fwd_col_plain) } else { SK16(fwd_row_plain) }
-    case STAGE_FWD_RESCALE:
-        if (pass == 0) { SK16_GRID(fwd_col_rescale) } else { SK16_GRID(fwd_row_rescale) }
+    case STAGE_FWD_RESCALE:  // the first pass: launch_cols16
+        if (pass == 0) return false;
+        SK16_GRID(fwd_row_rescale)
     case STAGE_FWD_LIFT:
         if (pass == 0) { SK16_GRID(fwd_col_rescale) } else { SK16(fwd_row_plain) }
     case STAGE_FWD_BCONV_MODDOWN:
@@ -2557,6 +2565,8 @@ hipError_t launch_split12_cols(ColsMode mode, NttPro pro, const ColsArgs &a, uin
 // Parts of a job: workgroups fill LDS, one to a CU, so as many parts as the CUs take at once.
 constexpr uint32_t kCols16Parts = 256;
 
+// LDS holds a tile per source and one per wave, 160 KB at 12 sources; more (whose sums
+// the two columns do not hold either) go through the separate passes.
 bool cols16_fits(uint32_t ns) { return ns <= kFoldMaxTerms; }
 
 hipError_t launch_cols16(ColsMode mode, const ColsArgs &a, uint32_t njobs, hipStream_t stream)
