@@ -290,7 +290,7 @@ def valu_fractions(probe):
     rows = {}
     for line in text.splitlines():
         cells = [c.strip() for c in line.strip().strip("|").split("|")]
-        if len(cells) >= 7 and cells[0].startswith("k_") and cells[2].isdigit():
+        if len(cells) >= 7 and cells[0].startswith(("k_", "k16_")) and cells[2].isdigit():
             name = "%s %s" % (cells[0], cells[1])
             if name in rows:
                 continue
@@ -298,9 +298,8 @@ def valu_fractions(probe):
             rate = waves * per / (us / 1e6)
             rows[name] = {"wave_instr_per_launch": waves * per, "avg_us": us,
                           "frac_of_issue_peak": round(rate / VALU_ISSUE_PEAK, 3)}
-    keep = ["k_fwd_col_bconv 8192x62x1", "k_inner_product 65536x35x1", "k_inner_product_tensor_rowpass 65536x35x1",
-            "k_inner_product_rowpass 65536x35x1", "k_bconv 65536x3x5", "k_fwd_row_moddown 8192x62x1",
-            "k_fwd_col_plain 8192x74x1", "k_fwd_row_plain 8192x74x1"]
+    keep = ["k16_cols<0> 32768x3x1", "k16_ip_rows 16384x35x1", "k16_cols<1> 32768x2x2", "k_inv_row_tensor 8192x31x1",
+            "k_fwd_row_moddown 8192x62x1", "k_inner_product 65536x35x1"]
     # the NTT passes appear under the tile width the autotuner chose (suffix _w8 or _w4 for 8 or 4)
     kernels = {}
     for k in keep:
