@@ -67,6 +67,8 @@ hipError_t modup_from_coeffs(const ckks_ctx *c, const uint64_t *d, uint32_t g, u
 }
 
 // Whether ModUp can leave its last forward pass to the inner product: where its column launch runs.
+// At N = 2^16 and l = 30 the pass and the inner product apart take 25 + 47 us, together 56; a rotation's
+// at l = 17 12 + 20 and 24.  Larger digits (13 to 16 primes) have no column launch.
 bool modup_in_tiles(const ckks_ctx *c, uint32_t level)
 {
     return c->logn == 12 || cols16_fits(std::min(c->alpha, level + 1));
