@@ -514,7 +514,7 @@ void ckks_boot_destroy(ckks_boot *boot);
  *                   centred conversion of ckks_moddown.
  *   ckks32_keyswitch: (out0, out1) = ModDown(InnerProduct(ModUp(d), key)).
  *   ckks32_hmult_relin: (a0 b0, a0 b1 + a1 b0) + KeySwitch(a1 b1, rlk); out may not alias inputs.
- *   ckks32_apply_galois: (phi_g(c0), 0) + KeySwitch(phi_g(c1), key of g).
+ *   ckks32_apply_galois: (phi_g(c0), 0) + KeySwitch(phi_g(c1), key of g); out may alias c (in place).
  *   ckks32_rescale: out_t = q_l^-1 (c_t - NTT(SwitchModulo(INTT_{q_l}(c_t[l])))) at level l-1;
  *                   out may equal c (in place).
  */

@@ -546,6 +546,15 @@ __global__ __launch_bounds__(kB) void k32_inner_product(Ip32Args a)
     a.acc[((size_t)a.rows + r) * kN + n] = reduce64(s1, P);
 }
 
+// out[limb][e] = in[limb][src of e under X -> X^g] (evaluation domain), for a
+// rotation whose outputs overlap c0
+__global__ __launch_bounds__(kB) void k32_automorph(const uint32_t *in, uint32_t *out, uint32_t g)
+{
+    const uint32_t e = blockIdx.x * kB + threadIdx.x;
+    const size_t row = (size_t)blockIdx.y * kN;
+    out[row + e] = in[row + galois_src(e, g, kLogN)];
+}
+
 }  // namespace
 
 // --------------------------------------------------------------- host side
@@ -644,6 +653,13 @@ ckks_status check_ptr32(const void *p, const char *what)
 {
     if (!p || ((uintptr_t)p & 15)) return fail(CKKS_E_ARG, std::string(what) + ": null or not 16-byte aligned");
     return CKKS_OK;
+}
+
+// whether [a, a + bytes) and [b, b + bytes) overlap
+bool overlap32(const void *a, const void *b, size_t bytes)
+{
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return x < y + bytes && y < x + bytes;
 }
 
 // Workspace layout of a key switch at `level` (words): dc [n], ext [beta][rows],
@@ -827,15 +843,17 @@ hipError_t inner_product32(const ckks32_ctx *c, const uint32_t *d, uint32_t g, c
     return hipGetLastError();
 }
 
-// out_t = KS_t + phi_g(add_t) with KS the key switch of phi_g(d), or with tin the
-// relinearised product (d, add0 null, g = 1); add_1 = 0.
+// out_t = KS_t + phi_g_add(add_t) with KS the key switch of phi_g(d), or with tin
+// the relinearised product (d, add0 null, g = 1); add_1 = 0.  With g_add other than
+// 1 the outputs may not overlap add0: its blocks are gathered as they are written.
 hipError_t keyswitch32(ckks32_ctx *c, const uint32_t *d, uint32_t g, const Tensor32 *tin, uint32_t level,
-                       const uint32_t *key, uint32_t *out0, uint32_t *out1, const uint32_t *add0, void *ws, hipStream_t st)
+                       const uint32_t *key, uint32_t *out0, uint32_t *out1, const uint32_t *add0, uint32_t g_add, void *ws,
+                       hipStream_t st)
 {
     const Ws32 w = ks_ws(c, level, ws);
     hipError_t e = modup32(c, d, g, tin, level, w, st);
     if (e == hipSuccess) e = inner_product32(c, d, g, tin, level, key, w, st);
-    if (e == hipSuccess) e = moddown32(c, w.acc, level, w, out0, out1, add0, g, st);
+    if (e == hipSuccess) e = moddown32(c, w.acc, level, w, out0, out1, add0, g_add, st);
     return e;
 }
 
@@ -1086,7 +1104,7 @@ extern "C" ckks_status ckks32_keyswitch(ckks32_ctx *c, const uint32_t *d, uint32
     TRY32(check_ptr32(out0, "ckks32_keyswitch out0"));
     TRY32(check_ptr32(out1, "ckks32_keyswitch out1"));
     TRY32(check_ptr32(ws, "ckks32_keyswitch ws"));
-    return dev32(keyswitch32(c, d, 1, nullptr, level, key, out0, out1, nullptr, ws, (hipStream_t)stream),
+    return dev32(keyswitch32(c, d, 1, nullptr, level, key, out0, out1, nullptr, 1, ws, (hipStream_t)stream),
                  "ckks32_keyswitch");
 }
 
@@ -1098,7 +1116,7 @@ extern "C" ckks_status ckks32_hmult_relin(ckks32_ctx *c, const uint32_t *a0, con
     const void *ptrs[] = {a0, a1, b0, b1, rlk, out0, out1, ws};
     for (const void *q : ptrs) TRY32(check_ptr32(q, "ckks32_hmult_relin"));
     const Tensor32 tin = {a0, a1, b0, b1};
-    const hipError_t e = keyswitch32(c, nullptr, 1, &tin, level, rlk, out0, out1, nullptr, ws, (hipStream_t)stream);
+    const hipError_t e = keyswitch32(c, nullptr, 1, &tin, level, rlk, out0, out1, nullptr, 1, ws, (hipStream_t)stream);
     return dev32(e, "ckks32_hmult_relin");
 }
 
@@ -1110,7 +1128,21 @@ extern "C" ckks_status ckks32_apply_galois(ckks32_ctx *c, const uint32_t *c0, co
     const void *ptrs[] = {c0, c1, key, out0, out1, ws};
     for (const void *q : ptrs) TRY32(check_ptr32(q, "ckks32_apply_galois"));
     if (galois % 2 == 0 || galois >= 2 * kN) return fail(CKKS_E_ARG, "ckks32_apply_galois: galois must be odd, below 2N");
-    const hipError_t e = keyswitch32(c, c1, galois, nullptr, level, key, out0, out1, c0, ws, (hipStream_t)stream);
+    const hipStream_t st = (hipStream_t)stream;
+    const size_t bytes = (size_t)(level + 1) * kN * 4;
+    const uint32_t *add = c0;
+    uint32_t g_add = galois;
+    hipError_t e = hipSuccess;
+    // c1 is read out before the last launch, which writes the outputs, but c0 is gathered by it: where an
+    // output overlaps c0, phi_g(c0) goes to the workspace behind the key switch's first
+    if (overlap32(c0, out0, bytes) || overlap32(c0, out1, bytes)) {
+        uint32_t *g0 = (uint32_t *)((char *)ws + ks_bytes(c, level));
+        hipLaunchKernelGGL(k32_automorph, dim3(kN / kB, level + 1), dim3(kB), 0, st, c0, g0, galois);
+        e = hipGetLastError();
+        add = g0;
+        g_add = 1;
+    }
+    if (e == hipSuccess) e = keyswitch32(c, c1, galois, nullptr, level, key, out0, out1, add, g_add, ws, st);
     return dev32(e, "ckks32_apply_galois");
 }
 
