@@ -13,10 +13,11 @@ Three choices are measured on the GPU and kept:
 
 Each candidate is timed as the median of several bursts of launches on
 rotating buffers larger than the last-level cache.  Results are kept in a JSON
-cache keyed by (logN, limbs, K, op, arch): op is "ntt_fwd" / "ntt_inv" or a
-batch signature; limbs is the launch's number of limbs.  A later process with
-the same parameter set and GPU architecture loads the cache instead of
-measuring again.  The tuner only chooses among launch shapes that give the
+cache keyed by (logN, limbs, K, op, arch, launches): op is "ntt_fwd" / "ntt_inv"
+or a batch signature; limbs is the launch's number of limbs; launches is
+LAUNCHES, so that what was measured on other kernels is measured again.  A later
+process with the same parameter set and GPU architecture loads the cache instead
+of measuring again.  The tuner only chooses among launch shapes that give the
 same result bit for bit.
 """
 from __future__ import annotations
@@ -34,6 +35,11 @@ CACHE_ENV = "CKKS_TUNE_CACHE"
 TILES = (16, 8, 4)
 # inverse launches also have tile code 2: 8 rows (columns) per workgroup with 4 elements per thread
 INV_TILES = TILES + (2,)
+# Version of the launches the measurements are of: counted up when an operation's launches change.
+LAUNCHES = 2
+# Most source primes a conversion's column launch takes (kFoldMaxTerms of modarith.h).  With digits of
+# at most as many, HMult, rotation and key switch finish ModUp's rows inside the inner product.
+COLUMN_SOURCES = 12
 
 
 def cache_path() -> str:
@@ -49,7 +55,7 @@ def arch() -> str:
 
 
 def _key(logn: int, limbs: int, K: int, op: str, arch_name: str) -> str:
-    return "logN=%d|limbs=%d|K=%d|op=%s|arch=%s" % (logn, limbs, K, op, arch_name)
+    return "logN=%d|limbs=%d|K=%d|op=%s|arch=%s|launches=%d" % (logn, limbs, K, op, arch_name, LAUNCHES)
 
 
 def load_cache(path: Optional[str] = None) -> dict:
@@ -129,21 +135,27 @@ def tune_ntt_tiles(ctx: ckks.Context, limb_counts=None, samples: int = 5, burst:
     return out
 
 
-def op_launch_sizes(ctx: ckks.Context, level: int) -> dict:
-    """Limb counts of the NTT launches inside HMult+relin and Rescale at
-    `level` that exceed the context's primes (and so cannot be timed through
-    ckks_ntt alone): ModUp's forward NTT (beta (l+1+K) - (l+1) rows), ModDown's
-    (2 (l+1)) and Rescale's (2 l)."""
+def op_launches(ctx: ckks.Context, level: int) -> dict:
+    """Limb counts of the forward NTT launches inside the operations at `level`,
+    which ckks_ntt alone does not launch, and the operation each is timed
+    through: ModDown's 2 (l+1) through HMult+relin, Rescale's 2 l through
+    Rescale, ModUp's beta (l+1+K) - (l+1) through HMult+relin where it launches
+    them, else through a hoisted rotation, whose ModUp always does."""
     n, K = level + 1, ctx.np
-    beta = ctx.beta(level)
-    return {"ntt_fwd": sorted({beta * (n + K) - n, 2 * n, 2 * level} - {0})}
+    hmult_launches = min(ctx.alpha, n) > COLUMN_SOURCES
+    sizes = {ctx.beta(level) * (n + K) - n: "hmult" if hmult_launches else "hoisted", 2 * n: "hmult", 2 * level: "rescale"}
+    return {k: v for k, v in sizes.items() if 0 < k <= 128}
+
+
+def op_launch_sizes(ctx: ckks.Context, level: int) -> dict:
+    """The limb counts of op_launches, ascending."""
+    return {"ntt_fwd": sorted(op_launches(ctx, level))}
 
 
 def tune_op_launches(ctx: ckks.Context, level: int, samples: int = 5, burst: int = 4, cache: Optional[dict] = None,
                      use_cache: bool = True) -> dict:
-    """Tile width of the launches op_launch_sizes names, chosen by timing the
-    operation that contains each (HMult+relin for ModUp's and ModDown's,
-    Rescale for its own) with every candidate width on that launch size."""
+    """Tile width of the launches op_launches names, chosen by timing the
+    operation it names with every candidate width on that launch size."""
     if ctx.logn != 16:
         return {}
     cache = {} if cache is None else cache
@@ -157,7 +169,7 @@ def tune_op_launches(ctx: ckks.Context, level: int, samples: int = 5, burst: int
     allm = list(ctx.q) + list(ctx.p)
     kd = torch.randint(0, int(min(allm)), (ctx.dnum, 2, len(allm), ctx.N), dtype=torch.int64,
                        device="cuda").view(torch.uint64)
-    rlk = ctx.key(kd, 0)
+    rlk, gk = ctx.key(kd, 0), ctx.key(kd, 5)  # 5: the rotation by one slot
     cts = [ckks.Ciphertext(rnd(level + 1), rnd(level + 1), level) for _ in range(4)]
     out = ctx.empty_ct(level)
     low = ctx.empty_ct(level - 1)
@@ -174,12 +186,14 @@ def tune_op_launches(ctx: ckks.Context, level: int, samples: int = 5, burst: int
         turn[0] += 1
         ctx.ckks_rescale(a, low, ws, stream)
 
-    n, K = level + 1, ctx.np
-    sizes = {ctx.beta(level) * (n + K) - n: hmult, 2 * n: hmult, 2 * level: rescale}
+    def hoisted():
+        a = cts[turn[0] % 4]
+        turn[0] += 1
+        ctx.ckks_hrotate_hoisted(a, [1], [gk], [out], ws, stream)
+
     res = {}
-    for size, fn in sorted(sizes.items()):
-        if size <= 0 or size > 128:
-            continue
+    for size, op in sorted(op_launches(ctx, level).items()):
+        fn = {"hmult": hmult, "rescale": rescale, "hoisted": hoisted}[op]
         key = _key(ctx.logn, size, ctx.np, "ntt_fwd", an)
         if use_cache and key in cache:
             ckks.ntt_tile_set(False, size, int(cache[key]["tile"]))
@@ -193,7 +207,7 @@ def tune_op_launches(ctx: ckks.Context, level: int, samples: int = 5, burst: int
         best = min(times, key=times.get)
         ckks.ntt_tile_set(False, size, best)
         rec = {"tile": best, "op_us": {str(t): round(v, 2) for t, v in times.items()},
-               "timed_through": fn.__name__}
+               "timed_through": op}
         cache[key] = rec
         res[size] = rec
     return {"ntt_fwd": res}
