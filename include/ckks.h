@@ -122,16 +122,27 @@ ckks_status ckks_intt(ckks_ctx *ctx, uint64_t *poly, uint32_t limb0, uint32_t n_
  * (rows) with 64 threads on each, 4 elements per thread (512 threads), twice
  * the waves for latency-bound launches over few limbs; every inverse column
  * pass has this form, and the plain inverse row pass (the ModDown and Rescale
- * INTTs, ckks_intt); the gathered and tensor row passes then use tiles of 8.  The choice holds per direction (inverse 0 / 1) and per number of
- * limbs in the launch (1..128), for every NTT launch of every operation in the
- * process; tile 0 restores the default (16 from 8 limbs up, else 8; row passes
- * next to a column launch 8 from 8 limbs up, else 4; inverse launches of at most
- * 8 limbs 2).  Results do not depend on it.  An autotuner sets it from
- * measurements.  ckks_ntt_tile_get returns the code in effect for a whole
- * transform (0 for bad arguments).  Persistent batch kernels always use 16.
+ * INTTs, ckks_intt); the gathered and tensor row passes then use tiles of 8.
+ * The choice holds per direction (inverse 0 / 1), per number of limbs in the
+ * launch (1..128) and per kind of launch, in the whole process:
+ *   CKKS_TILE_TRANSFORM: both passes of a transform, default 16 from 8 limbs up,
+ *     else 8;
+ *   CKKS_TILE_ROWS: a row pass next to a column launch (ModUp, ModDown and
+ *     Rescale with at most 12 source primes), default 8 from 8 limbs up, else 4;
+ * inverse launches of at most 8 limbs default to 2.  Tile 0 restores the default.
+ * ckks_ntt_tile_set sets both kinds, ckks_ntt_tile_set_kind one (an autotuner
+ * measures them apart).  Results do not depend on it.  ckks_ntt_tile_get returns
+ * the code in effect for a whole transform, ckks_ntt_tile_get_kind for a kind (0
+ * for bad arguments).  Persistent batch kernels always use 16.
  */
+enum {
+    CKKS_TILE_TRANSFORM = 0,
+    CKKS_TILE_ROWS = 1
+};
 ckks_status ckks_ntt_tile_set(uint32_t inverse, uint32_t n_limbs, uint32_t tile);
 uint32_t ckks_ntt_tile_get(uint32_t inverse, uint32_t n_limbs);
+ckks_status ckks_ntt_tile_set_kind(uint32_t kind, uint32_t inverse, uint32_t n_limbs, uint32_t tile);
+uint32_t ckks_ntt_tile_get_kind(uint32_t kind, uint32_t inverse, uint32_t n_limbs);
 
 /*
  * ModUp of hybrid key switching (Sec. II-A, III-F.3, Eq. (1)):

@@ -61,6 +61,8 @@ _sigs = {
     "ckks_ntt": (ctypes.c_int, [_vp, _vp, _u32, _u32, _vp]),
     "ckks_ntt_tile_set": (ctypes.c_int, [_u32, _u32, _u32]),
     "ckks_ntt_tile_get": (_u32, [_u32, _u32]),
+    "ckks_ntt_tile_set_kind": (ctypes.c_int, [_u32, _u32, _u32, _u32]),
+    "ckks_ntt_tile_get_kind": (_u32, [_u32, _u32, _u32]),
     "ckks_intt": (ctypes.c_int, [_vp, _vp, _u32, _u32, _vp]),
     "ckks_modup": (ctypes.c_int, [_vp, _vp, _u32, _vp, _vp, _vp]),
     "ckks_inner_product": (ctypes.c_int, [_vp, _vp, _u32, _vp, _u32, _vp, _vp]),
@@ -717,10 +719,23 @@ def probe_mad64(out: torch.Tensor, blocks: int, iters: int, stream=None) -> int:
     return int(n.value)
 
 
+# kinds of N = 2^16 NTT launch: both passes of a transform, or a row pass next to a column launch
+TILE_TRANSFORM, TILE_ROWS = 0, 1
+
+
 def ntt_tile_set(inverse: bool, n_limbs: int, tile: int) -> None:
-    """Tile width of the N = 2^16 NTT grid launches over n_limbs limbs (0: default)."""
+    """Tile width of the N = 2^16 NTT grid launches over n_limbs limbs, of either kind (0: default)."""
     _check(_lib.ckks_ntt_tile_set(1 if inverse else 0, n_limbs, tile), "ckks_ntt_tile_set")
 
 
 def ntt_tile_get(inverse: bool, n_limbs: int) -> int:
     return int(_lib.ckks_ntt_tile_get(1 if inverse else 0, n_limbs))
+
+
+def ntt_tile_set_kind(kind: int, inverse: bool, n_limbs: int, tile: int) -> None:
+    """ntt_tile_set for launches of one kind (TILE_TRANSFORM, TILE_ROWS)."""
+    _check(_lib.ckks_ntt_tile_set_kind(kind, 1 if inverse else 0, n_limbs, tile), "ckks_ntt_tile_set_kind")
+
+
+def ntt_tile_get_kind(kind: int, inverse: bool, n_limbs: int) -> int:
+    return int(_lib.ckks_ntt_tile_get_kind(kind, 1 if inverse else 0, n_limbs))

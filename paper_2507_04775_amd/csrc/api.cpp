@@ -353,14 +353,27 @@ static ckks_status ntt_common(ckks_ctx *ctx, uint64_t *poly, uint32_t limb0, uin
 
 extern "C" ckks_status ckks_ntt_tile_set(uint32_t inverse, uint32_t n_limbs, uint32_t tile)
 {
-    if (!ntt_tile_set(inverse, n_limbs, tile))
+    if (!ntt_tile_set(CKKS_TILE_TRANSFORM, inverse, n_limbs, tile) || !ntt_tile_set(CKKS_TILE_ROWS, inverse, n_limbs, tile))
         return fail(CKKS_E_ARG, "ckks_ntt_tile_set: inverse must be 0 or 1, n_limbs in [1, 128], tile 0, 4, 8 or 16");
+    return CKKS_OK;
+}
+
+extern "C" ckks_status ckks_ntt_tile_set_kind(uint32_t kind, uint32_t inverse, uint32_t n_limbs, uint32_t tile)
+{
+    if (!ntt_tile_set(kind, inverse, n_limbs, tile))
+        return fail(CKKS_E_ARG, "ckks_ntt_tile_set_kind: kind and inverse must be 0 or 1, n_limbs in [1, 128], tile 0, 4, 8 "
+                                "or 16 (inverse: also 2)");
     return CKKS_OK;
 }
 
 extern "C" uint32_t ckks_ntt_tile_get(uint32_t inverse, uint32_t n_limbs)
 {
-    return inverse <= 1 && n_limbs ? ntt_tile_get(inverse, n_limbs) : 0;
+    return ckks_ntt_tile_get_kind(CKKS_TILE_TRANSFORM, inverse, n_limbs);
+}
+
+extern "C" uint32_t ckks_ntt_tile_get_kind(uint32_t kind, uint32_t inverse, uint32_t n_limbs)
+{
+    return kind <= CKKS_TILE_ROWS && inverse <= 1 && n_limbs ? ntt_tile_get(kind, inverse, n_limbs) : 0;
 }
 
 extern "C" ckks_status ckks_ntt(ckks_ctx *ctx, uint64_t *poly, uint32_t limb0, uint32_t n_limbs, void *stream)

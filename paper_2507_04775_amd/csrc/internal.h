@@ -398,8 +398,8 @@ uint32_t ntt_tiles(uint32_t logn);  // tiles per limb of the persistent passes
 // Tile width (16, 8 or 4 columns / rows per workgroup) of the N = 2^16 grid
 // launches over nlimbs limbs, per direction; 0 restores the default rule.
 constexpr uint32_t kMaxTileLimbs = 128;
-bool ntt_tile_set(uint32_t inverse, uint32_t nlimbs, uint32_t tile);
-uint32_t ntt_tile_get(uint32_t inverse, uint32_t nlimbs);
+bool ntt_tile_set(uint32_t kind, uint32_t inverse, uint32_t nlimbs, uint32_t tile);
+uint32_t ntt_tile_get(uint32_t kind, uint32_t inverse, uint32_t nlimbs);
 // N = 2^16: passes first_pass to last_pass; the first pass's output is in a.mid
 hipError_t launch_ntt_stage(NttStage st, const NttArgs &a, uint32_t nlimbs, hipStream_t stream,
                             uint32_t first_pass = 0, uint32_t last_pass = 1);

@@ -2453,10 +2453,11 @@ static void set_heavy(NttArgs &a, uint32_t nlimbs)
     a.n_heavy = nh < nlimbs ? nh : 0;  // all limbs alike: whole-limb placement
 }
 
-// Tile width of the grid launches at N = 2^16, per direction and launch size
-// (0: the default rule below).  Set by ckks_ntt_tile_set (an autotuner), read
-// by every grid launch.
-static std::atomic<uint8_t> g_tile[2][kMaxTileLimbs + 1];
+// Tile width of the grid launches at N = 2^16, per kind (CKKS_TILE_TRANSFORM: both passes of a
+// transform; CKKS_TILE_ROWS: a row pass next to a column launch), direction and launch size (0: the
+// default rule below).  Set by ckks_ntt_tile_set (both kinds) and ckks_ntt_tile_set_kind (the
+// autotuner), read by every grid launch.
+static std::atomic<uint8_t> g_tile[2][2][kMaxTileLimbs + 1];
 
 // The default.  Whole transforms: a column pass reads runs of 8 TW bytes, so 16
 // columns (whole lines) from 8 limbs on (12 limbs 12.4 us, 16.9 with 8, 18.8 with
@@ -2488,7 +2489,7 @@ static uint32_t tile_width(NttStage st, uint32_t logn, uint32_t nlimbs, bool row
 {
     if (logn != 16) return 16;
     const int inv = st == STAGE_INV_PLAIN || st == STAGE_INV_GALOIS || st == STAGE_INV_TENSOR;
-    const uint32_t t = nlimbs <= kMaxTileLimbs ? g_tile[inv][nlimbs].load(std::memory_order_relaxed) : 0;
+    const uint32_t t = nlimbs <= kMaxTileLimbs ? g_tile[row_alone][inv][nlimbs].load(std::memory_order_relaxed) : 0;
     if (t) return t;
     return inv && nlimbs <= 8 ? 2 : default_tile(row_alone, nlimbs);
 }
@@ -2613,18 +2614,18 @@ hipError_t launch_split12_ip(const IpArgs &ip, const NttArgs &ia, const NttArgs 
     return hipGetLastError();
 }
 
-bool ntt_tile_set(uint32_t inverse, uint32_t nlimbs, uint32_t tile)
+bool ntt_tile_set(uint32_t kind, uint32_t inverse, uint32_t nlimbs, uint32_t tile)
 {
-    if (inverse > 1 || nlimbs == 0 || nlimbs > kMaxTileLimbs ||
+    if (kind > CKKS_TILE_ROWS || inverse > 1 || nlimbs == 0 || nlimbs > kMaxTileLimbs ||
         !(tile == 0 || tile == 4 || tile == 8 || tile == 16 || (tile == 2 && inverse == 1)))
         return false;
-    g_tile[inverse][nlimbs].store((uint8_t)tile, std::memory_order_relaxed);
+    g_tile[kind][inverse][nlimbs].store((uint8_t)tile, std::memory_order_relaxed);
     return true;
 }
 
-uint32_t ntt_tile_get(uint32_t inverse, uint32_t nlimbs)
+uint32_t ntt_tile_get(uint32_t kind, uint32_t inverse, uint32_t nlimbs)
 {
-    return tile_width(inverse ? STAGE_INV_PLAIN : STAGE_FWD_PLAIN, 16, nlimbs, false);
+    return tile_width(inverse ? STAGE_INV_PLAIN : STAGE_FWD_PLAIN, 16, nlimbs, kind == CKKS_TILE_ROWS);
 }
 
 hipError_t launch_inner_product_rowpass(const IpArgs &ip, const NttArgs &ia, hipStream_t stream)

@@ -2,9 +2,10 @@
 
 Three choices are measured on the GPU and kept:
 - the NTT tile width (16, 8 or 4 columns or rows per workgroup, 512, 256 or
-  128 threads) of every N = 2^16 NTT grid launch, per direction and number of
+  128 threads) of the N = 2^16 NTT grid launches, per kind (both passes of a
+  transform, or a row pass next to a column launch), direction and number of
   limbs in the launch (the paper's limb-batch knob, Sec. III-F.1: how much of
-  a transform one block takes);
+  a transform one block takes).  Inverse row passes keep the default rule;
 - the persistent grid (workgroups per CU) of each step of a batch of key
   switches, per batch (ckks_batch_tune);
 - the fusion depth of a batch (ckks_batch_set_schedule): one persistent
@@ -14,7 +15,7 @@ Three choices are measured on the GPU and kept:
 Each candidate is timed as the median of several bursts of launches on
 rotating buffers larger than the last-level cache.  Results are kept in a JSON
 cache keyed by (logN, limbs, K, op, arch, launches): op is "ntt_fwd" / "ntt_inv"
-or a batch signature; limbs is the launch's number of limbs; launches is
+for whole transforms, "row_fwd" for row passes or a batch signature; limbs is the launch's number of limbs; launches is
 LAUNCHES, so that what was measured on other kernels is measured again.  A later
 process with the same parameter set and GPU architecture loads the cache instead
 of measuring again.  The tuner only chooses among launch shapes that give the
@@ -36,10 +37,12 @@ TILES = (16, 8, 4)
 # inverse launches also have tile code 2: 8 rows (columns) per workgroup with 4 elements per thread
 INV_TILES = TILES + (2,)
 # Version of the launches the measurements are of: counted up when an operation's launches change.
-LAUNCHES = 2
+LAUNCHES = 3
 # Most source primes a conversion's column launch takes (kFoldMaxTerms of modarith.h).  With digits of
 # at most as many, HMult, rotation and key switch finish ModUp's rows inside the inner product.
 COLUMN_SOURCES = 12
+# Most digits whose finished rows fit ModUp's scratch: a hoisted rotation's take the column launch too.
+FINISHED_DIGITS = 4
 
 
 def cache_path() -> str:
@@ -87,10 +90,10 @@ def _burst_ms(fn, stream, n: int) -> float:
 
 def tune_ntt_tiles(ctx: ckks.Context, limb_counts=None, samples: int = 5, burst: int = 8, cache: Optional[dict] = None,
                    use_cache: bool = True) -> dict:
-    """Chooses the NTT tile width per direction and launch size at N = 2^16
-    (launch sizes up to the number of primes of the context, taken over the
-    context's own primes q_0.. then p_0..), applies it (ckks_ntt_tile_set) and
-    records it in `cache`.  Returns {op: {limbs: {"tile", "us": {tile: us}}}}."""
+    """Chooses the tile width of whole transforms per direction and launch size
+    at N = 2^16 (launch sizes up to the number of primes of the context, taken
+    over the context's own primes q_0.. then p_0..), applies it
+    (ckks_ntt_tile_set_kind) and records it in `cache`.  Returns {op: {limbs: {"tile", "us": {tile: us}}}}."""
     if ctx.logn != 16:
         return {}
     nmax = ctx.nq + ctx.np
@@ -112,12 +115,12 @@ def tune_ntt_tiles(ctx: ckks.Context, limb_counts=None, samples: int = 5, burst:
                 continue
             key = _key(ctx.logn, n, ctx.np, op, an)
             if use_cache and key in cache:
-                ckks.ntt_tile_set(inverse, n, int(cache[key]["tile"]))
+                ckks.ntt_tile_set_kind(ckks.TILE_TRANSFORM, inverse, n, int(cache[key]["tile"]))
                 out[op][n] = cache[key]
                 continue
             times = {}
             for tile in (INV_TILES if inverse else TILES):
-                ckks.ntt_tile_set(inverse, n, tile)
+                ckks.ntt_tile_set_kind(ckks.TILE_TRANSFORM, inverse, n, tile)
 
                 def launch():
                     p = ring[turn[0] % len(ring)][:n]
@@ -128,7 +131,7 @@ def tune_ntt_tiles(ctx: ckks.Context, limb_counts=None, samples: int = 5, burst:
                 xs = [_burst_ms(launch, stream, burst) for _ in range(samples)]
                 times[tile] = statistics.median(xs) * 1e3
             best = min(times, key=times.get)
-            ckks.ntt_tile_set(inverse, n, best)
+            ckks.ntt_tile_set_kind(ckks.TILE_TRANSFORM, inverse, n, best)
             rec = {"tile": best, "us": {str(t): round(v, 2) for t, v in times.items()}}
             cache[key] = rec
             out[op][n] = rec
@@ -136,15 +139,19 @@ def tune_ntt_tiles(ctx: ckks.Context, limb_counts=None, samples: int = 5, burst:
 
 
 def op_launches(ctx: ckks.Context, level: int) -> dict:
-    """Limb counts of the forward NTT launches inside the operations at `level`,
-    which ckks_ntt alone does not launch, and the operation each is timed
-    through: ModDown's 2 (l+1) through HMult+relin, Rescale's 2 l through
-    Rescale, ModUp's beta (l+1+K) - (l+1) through HMult+relin where it launches
-    them, else through a hoisted rotation, whose ModUp always does."""
-    n, K = level + 1, ctx.np
-    hmult_launches = min(ctx.alpha, n) > COLUMN_SOURCES
-    sizes = {ctx.beta(level) * (n + K) - n: "hmult" if hmult_launches else "hoisted", 2 * n: "hmult", 2 * level: "rescale"}
-    return {k: v for k, v in sizes.items() if 0 < k <= 128}
+    """Forward NTT launches inside the operations at `level` that ckks_ntt does
+    not make: {limbs: (operation it is timed through, kind of launch)}.  ModDown's
+    2 (l+1) limbs run in HMult+relin, Rescale's 2 l in Rescale, ModUp's
+    beta (l+1+K) - (l+1) in a hoisted rotation, and in HMult+relin where its
+    inner product does not finish them.  They are row passes next to a column
+    launch, or whole transforms where there is none."""
+    n, K, beta = level + 1, ctx.np, ctx.beta(level)
+    columns = min(ctx.alpha, n) <= COLUMN_SOURCES
+    rows, whole = ckks.TILE_ROWS, ckks.TILE_TRANSFORM
+    launches = {beta * (n + K) - n: ("hoisted", rows if beta <= FINISHED_DIGITS else whole) if columns else ("hmult", whole),
+                2 * n: ("hmult", rows if K <= COLUMN_SOURCES else whole),
+                2 * level: ("rescale", rows)}
+    return {k: v for k, v in launches.items() if 0 < k <= 128}
 
 
 def op_launch_sizes(ctx: ckks.Context, level: int) -> dict:
@@ -155,7 +162,8 @@ def op_launch_sizes(ctx: ckks.Context, level: int) -> dict:
 def tune_op_launches(ctx: ckks.Context, level: int, samples: int = 5, burst: int = 4, cache: Optional[dict] = None,
                      use_cache: bool = True) -> dict:
     """Tile width of the launches op_launches names, chosen by timing the
-    operation it names with every candidate width on that launch size."""
+    operation it names with every candidate width on launches of that size and
+    kind."""
     if ctx.logn != 16:
         return {}
     cache = {} if cache is None else cache
@@ -192,22 +200,22 @@ def tune_op_launches(ctx: ckks.Context, level: int, samples: int = 5, burst: int
         ctx.ckks_hrotate_hoisted(a, [1], [gk], [out], ws, stream)
 
     res = {}
-    for size, op in sorted(op_launches(ctx, level).items()):
+    for size, (op, kind) in sorted(op_launches(ctx, level).items()):
         fn = {"hmult": hmult, "rescale": rescale, "hoisted": hoisted}[op]
-        key = _key(ctx.logn, size, ctx.np, "ntt_fwd", an)
+        key = _key(ctx.logn, size, ctx.np, "row_fwd" if kind == ckks.TILE_ROWS else "ntt_fwd", an)
         if use_cache and key in cache:
-            ckks.ntt_tile_set(False, size, int(cache[key]["tile"]))
+            ckks.ntt_tile_set_kind(kind, False, size, int(cache[key]["tile"]))
             res[size] = cache[key]
             continue
         times = {}
         for tile in TILES:
-            ckks.ntt_tile_set(False, size, tile)
+            ckks.ntt_tile_set_kind(kind, False, size, tile)
             fn()
             times[tile] = statistics.median([_burst_ms(fn, stream, burst) for _ in range(samples)]) * 1e3
         best = min(times, key=times.get)
-        ckks.ntt_tile_set(False, size, best)
+        ckks.ntt_tile_set_kind(kind, False, size, best)
         rec = {"tile": best, "op_us": {str(t): round(v, 2) for t, v in times.items()},
-               "timed_through": op}
+               "timed_through": op, "kind": "rows" if kind == ckks.TILE_ROWS else "transform"}
         cache[key] = rec
         res[size] = rec
     return {"ntt_fwd": res}
