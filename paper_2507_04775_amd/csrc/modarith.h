@@ -3,7 +3,7 @@
 // 64x64->128 instruction).  Methods follow the paper's choice (Table III and
 // Sec. III-F.2): Shoup multiplication when one operand is a precomputed
 // constant, and a two-step Shoup-style folding of exact 128-bit products when
-// both operands vary.  Every modulus is below 2^61, so lazy values up to 4q
+// both operands vary.  Every modulus is below 2^61, so lazy values below 8q
 // fit a word.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -49,13 +49,13 @@ __host__ __device__ __forceinline__ u128 add128(u128 a, u128 b)
     return r;
 }
 
-// Exact sum of products y_i h_i (y_i, h_i < 2^61, fewer than 2^16 terms) with
-// h_i wave-uniform, accumulated by 32-bit columns: lo = sum y0 h0,
+// Exact sum of products y_i h_i (y_i <= 1.5 2^61, h_i < 2^61, at most 16 terms)
+// with h_i wave-uniform, accumulated by 32-bit columns: lo = sum y0 h0,
 // mid = sum (y0 h1 + y1 h0), hi = sum y1 h1, and the carries out of lo and mid
 // counted from the hardware carry-out of v_mad_u64_u32.  A term costs four
 // multiply-adds and three carry additions, where mul_wide + add128 spend
 // about twenty instructions (half of them register moves).  hi stays below
-// 2^62 (y1, h1 < 2^29), so it needs no carry.  The carry-outs go to separate
+// 2^63 (y1 < 1.5 2^29, h1 < 2^29), so it needs no carry.  The carry-outs go to separate
 // scalar pairs and are read three or more instructions later, after an
 // s_nop, which covers the VALU-writes-SGPR read hazard.
 struct MacCols {
