@@ -125,8 +125,8 @@ ckks_status ckks_intt(ckks_ctx *ctx, uint64_t *poly, uint32_t limb0, uint32_t n_
  * INTTs, ckks_intt); the gathered and tensor row passes then use tiles of 8.
  * The choice holds per direction (inverse 0 / 1), per number of limbs in the
  * launch (1..128) and per kind of launch, in the whole process:
- *   CKKS_TILE_TRANSFORM: both passes of a transform, default 16 from 8 limbs up,
- *     else 8;
+ *   CKKS_TILE_TRANSFORM: both passes of a transform, default 16 from 8 limbs up
+ *     (from 25 where ModDown's conversion is in it: 13 to 16 special primes), else 8;
  *   CKKS_TILE_ROWS: a row pass next to a column launch (ModUp, ModDown and
  *     Rescale with at most 12 source primes), default 8 from 8 limbs up, else 4;
  * inverse launches of at most 8 limbs default to 2.  Tile 0 restores the default.

@@ -2467,9 +2467,14 @@ static std::atomic<uint8_t> g_tile[2][2][kMaxTileLimbs + 1];
 // launch) reads whole rows at any width: 8 rows, which spread more evenly than 16
 // (ModDown's over 36 limbs 18.2 us, 19.8 with 16, 18.1 to 23.4 with 4; Rescale's
 // over 24 limbs 11.9, 12.8, 12.7), 4 below 8 limbs (4 limbs 5.1 us, 5.8 with 8).
-static uint32_t default_tile(bool row_alone, uint32_t nlimbs)
+// ModDown's conversion in the column pass (13 to 16 special primes) computes more
+// than it reads, and half as wide tiles fill the chip up to 24 limbs (ModDown at K =
+// 14 over 8, 18 and 24 limbs 40.6, 50.0 and 54.4 us, 45.5, 55.2 and 56.1 with 16; over
+// 26 and 30 limbs 58.3 and 58.8, 56.1 and 56.5 with 16).
+static uint32_t default_tile(NttStage st, bool row_alone, uint32_t nlimbs)
 {
     if (row_alone) return nlimbs >= 8 ? 8 : 4;
+    if (st == STAGE_FWD_BCONV_MODDOWN) return nlimbs > 24 ? 16 : 8;
     return nlimbs >= 8 ? 16 : 8;
 }
 
@@ -2491,7 +2496,7 @@ static uint32_t tile_width(NttStage st, uint32_t logn, uint32_t nlimbs, bool row
     const int inv = st == STAGE_INV_PLAIN || st == STAGE_INV_GALOIS || st == STAGE_INV_TENSOR;
     const uint32_t t = nlimbs <= kMaxTileLimbs ? g_tile[row_alone][inv][nlimbs].load(std::memory_order_relaxed) : 0;
     if (t) return t;
-    return inv && nlimbs <= 8 ? 2 : default_tile(row_alone, nlimbs);
+    return inv && nlimbs <= 8 ? 2 : default_tile(st, row_alone, nlimbs);
 }
 
 hipError_t launch_ntt_stage(NttStage st, const NttArgs &a0, uint32_t nlimbs, hipStream_t stream, uint32_t first_pass,
