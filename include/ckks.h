@@ -515,7 +515,7 @@ void ckks_boot_destroy(ckks_boot *boot);
  * Every result equals the 64-bit definition of the same operation on the same
  * primes.  A twiddle product is a 32-bit Shoup multiplication, butterflies
  * are Harvey's lazy forms (below 4q < 2^32), and sums of products are exact
- * 64-bit sums reduced once (Barrett).  Pointers: device, 16-byte aligned.
+ * 64-bit sums reduced once (by an FP64 quotient).  Pointers: device, 16-byte aligned.
  * Workspaces: ckks32_workspace_bytes(op, l) with op CKKS_OP_KEYSWITCH (also
  * ModUp and ModDown), CKKS_OP_HMULT, CKKS_OP_ROTATE, CKKS_OP_RESCALE.  All
  * calls are asynchronous on `stream`; errors as for the 64-bit calls.

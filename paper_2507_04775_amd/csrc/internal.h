@@ -512,7 +512,7 @@ struct TensorIn {
 
 // Full key switch of phi_{g_in}(d) into out_t = KS_t + phi_{g_add}(add_t) (add_t
 // may be null), workspace of CKKS_OP_KEYSWITCH size; tin: HMult's tensor folded
-// in instead of d and add (N = 2^16).
+// in instead of d and add.
 hipError_t keyswitch_core(const ckks_ctx *c, const uint64_t *d, uint32_t g_in, uint32_t level, const uint64_t *key,
                           uint64_t *out0, uint64_t *out1, const uint64_t *add0, const uint64_t *add1, uint32_t g_add,
                           void *ws, hipStream_t st, const TensorIn *tin = nullptr);

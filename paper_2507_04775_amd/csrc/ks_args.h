@@ -28,7 +28,7 @@ BconvArgs args_modup_bconv(const ckks_ctx *c, const uint64_t *d, uint32_t g, uin
                            uint64_t *ext, bool copy_own);
 // ModUp: forward NTT of the converted rows (beta * rows limbs, own rows skipped)
 NttArgs args_modup_ntt(const ckks_ctx *c, uint32_t level, uint64_t *ext);
-// N = 2^12: the column launch of a conversion at `level` (launch_split12_cols)
+// the column launch of a conversion at `level` (launch_split12_cols, launch_cols16)
 ColsArgs args_cols(const ckks_ctx *c, uint32_t level, const uint64_t *src, int64_t src_stride, uint64_t *dst,
                    int64_t dst_stride);
 // key inner product (rows rows); own rows read from `own` when non-null

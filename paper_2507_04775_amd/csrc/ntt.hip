@@ -1619,7 +1619,7 @@ __global__ __launch_bounds__(64) void k12_ip_rows(IpArgs ip, NttArgs ia, const u
 // converted row goes through memory, three launches are one, and a wave has
 // nothing to wait for but its LDS: the separate passes wrote and read every row
 // once more and spent half their time between loads and stores.  ModUp's three
-// passes of HMult at l = 30 (digits of 12, K = 4) took 67 us, this launch 44;
+// passes of HMult at l = 30 (digits of 11, 11 and 9, K = 4) took 67 us, this launch 44;
 // ModDown's two 38, this 27; Rescale's two at l = 12 17, this 12.  What bounds it
 // is the VALU: ModUp's issues 10.4 M wave instructions, 23 us at the card's rate
 // for 64-bit multiply-adds, over 192 workgroups of a digit's tile each (a CU
@@ -1827,7 +1827,7 @@ __global__ __launch_bounds__(64 * kCols16Waves) void k16_cols(ColsArgs a)
 // accumulated (see IpArgs).
 enum IpMode { IP_MODDOWN, IP_TENSOR, IP_EXTENDED };
 // Four rows a workgroup read 128-byte runs of the tiles: 56 us at l = 30 with a
-// tensor (digits of 12, 35 rows; 250 MB, 50 us at the rate of a copy) where eight
+// tensor (three digits, 35 rows; 250 MB, 50 us at the rate of a copy) where eight
 // rows take 58, two 60, sixteen 65, and the row pass and the inner product apart
 // 25 + 47.  A rotation's at l = 17 takes 24 us for 12 + 20.
 // Loading the next digit's row ahead of this one's rounds gains nothing (58.3 us
@@ -2433,11 +2433,11 @@ static uint32_t ntt_threads(uint32_t logn) { return logn == 12 ? kThreads12 : kT
 // Fills a.heavy with the launch limbs on the integer path.  It leaves none when
 // they do not fit the list, when every limb is on that path, or in launches of
 // more than kHeavyMaxLimbs limbs: the assignment is then the whole-limb one.
-// Measured side by side, placing the heavy limbs apart makes the passes over
-// 31 and 35 limbs 5 to 12 % faster, leaves the 62-limb ModDown passes
-// unchanged and makes the 74-limb ModUp passes 2 to 4 % slower: those run in
-// more than one round of workgroups per CU, where the position of a workgroup
-// in the launch no longer decides its CU.
+// Measured side by side on whole transforms, placing the heavy limbs apart makes
+// the passes over 31 and 35 limbs 5 to 12 % faster, leaves those over 62 limbs
+// unchanged and makes those over 74 limbs 2 to 4 % slower: they run in more than
+// one round of workgroups per CU, where the position of a workgroup in the launch
+// no longer decides its CU.
 constexpr uint32_t kHeavyMaxLimbs = 48;
 static void set_heavy(NttArgs &a, uint32_t nlimbs)
 {
@@ -2466,7 +2466,10 @@ static std::atomic<uint8_t> g_tile[2][2][kMaxTileLimbs + 1];
 // limbs 10.2 us, 11.7 with 16, 11.2 with 4).  A row pass alone (next to a column
 // launch) reads whole rows at any width: 8 rows, which spread more evenly than 16
 // (ModDown's over 36 limbs 18.2 us, 19.8 with 16, 18.1 to 23.4 with 4; Rescale's
-// over 24 limbs 11.9, 12.8, 12.7), 4 below 8 limbs (4 limbs 5.1 us, 5.8 with 8).
+// over 24 limbs 11.9, 12.8, 12.7; the tensor's first inverse pass within HMult of
+// 31, 24 and 9 limbs 157.4, 129.9 and 69.3 us, 157.2, 130.9 and 69.9 with 16; the
+// gathered one within a rotation of 31, 24 and 12 limbs 144.4, 121.4 and 73.7 us,
+// 144.5, 122.4 and 75.0), 4 below 8 limbs (4 limbs 5.1 us, 5.8 with 8).
 // ModDown's conversion in the column pass (13 to 16 special primes) computes more
 // than it reads, and half as wide tiles fill the chip up to 24 limbs (ModDown at K =
 // 14 over 8, 18 and 24 limbs 40.6, 50.0 and 54.4 us, 45.5, 55.2 and 56.1 with 16; over
@@ -2516,10 +2519,11 @@ hipError_t launch_ntt_stage(NttStage st, const NttArgs &a0, uint32_t nlimbs, hip
         const uint32_t pw = tw == 2 ? 8 : tw;  // rows or columns per workgroup
         const uint32_t tiles = a.logn == 12 ? 1 : 256 / pw;
         const uint32_t threads = a.logn == 12 ? kThreads12 : four ? 512 : 32 * pw;
-        // ModDown's conversion reads the same K source rows for every limb: workgroups in (tile, limb)
-        // order send a column tile of every limb to one XCD, whose L2 then holds that tile of the
-        // sources (whole limbs per XCD read all K rows, 5 MB at K = 10, against 4 MB of L2).  Over 48
-        // rows at K = 10 the pass went from 33.0 to 30.8 us, over 36 at K = 4 from 19.4 to 18.6 us.
+        // ModDown's conversion (here with 13 to 16 special primes) reads the same K source rows for every
+        // limb: workgroups in (tile, limb) order send a column tile of every limb to one XCD, whose L2
+        // then holds that tile of the sources (whole limbs per XCD read all K rows, 6.5 MB at K = 13,
+        // against 4 MB of L2).  Key switches at K = 13 and l = 30 take 228 us so and 232 without, at
+        // K = 16 and l = 39 300 and 313.
         a.by_tile = st == STAGE_FWD_BCONV_MODDOWN && pass == 0;
         hipLaunchKernelGGL(k.grid, dim3(tiles, nlimbs), dim3(threads), 0, stream, a);
     }

@@ -79,9 +79,10 @@ __device__ __forceinline__ uint32_t shoup_lazy(uint32_t y, Pair32 w, uint32_t q)
 __device__ __forceinline__ uint32_t shoup(uint32_t y, Pair32 w, uint32_t q) { return csub(shoup_lazy(y, w, q), q); }
 
 // x mod q for a 64-bit x (SIGNED: two's complement).  k = round(x / q) comes
-// from the low word of 1.5 2^52 + x (1/q), within 1/2 + 2^-8 of x / q (x is
-// rounded to 53 bits, q > 2^17), so x - k q, taken in 32 bits, is the centred
-// residue: eight instructions, where Barrett with a 64-bit product takes about
+// from the low word of 1.5 2^52 + x (1/q).  The callers' sums, at most 16 products
+// of words below 2^30 and residues, are below 2^34 q, so that it is within 1/2 +
+// 2^-17 of x / q (x and 1/q are rounded to 53 bits) and x - k q, taken in 32 bits,
+// is the centred residue: eight instructions, where Barrett with a 64-bit product takes about
 // sixteen.
 template <bool SIGNED = false>
 __device__ __forceinline__ uint32_t reduce64(uint64_t x, const Prime32 &P)
@@ -1027,7 +1028,7 @@ extern "C" size_t ckks32_workspace_bytes(const ckks32_ctx *c, uint32_t op, uint3
     const size_t n = level + 1;
     switch (op) {
     case CKKS_OP_KEYSWITCH: return ks_bytes(c, level);
-    case CKKS_OP_HMULT:
+    case CKKS_OP_HMULT:  // as ROTATE, whose rows behind the key switch's hold phi_g(c0) in place
     case CKKS_OP_ROTATE: return ks_bytes(c, level) + align256(2 * n * kN * 4);
     case CKKS_OP_RESCALE: return (2 + 2 * (size_t)level) * kN * 4;
     default: return 0;
