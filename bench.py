@@ -162,11 +162,11 @@ def measured_ip_traffic():
 
 
 def step_inner_products():
-    """The timed step's inner products (the fused forms of k_inner_product that
-    HMult+relin and HRotate launch) from the committed counter and trace
-    summaries, while the kernel sources are the profiled ones (else None): their
-    algorithmic bytes, measured HBM bytes and profiled duration per launch."""
-    prof = os.path.join(ROOT, "profiles", "inner_product_logn16_l30_hbm_counters.md")
+    """The timed step's inner products (k16_ip_rows of HMult+relin and HRotate)
+    and HMult+relin's other launches from the committed counter summary, while
+    the kernel sources are the profiled ones (else None): their algorithmic
+    bytes, measured HBM bytes and profiled duration per launch."""
+    prof = os.path.join(ROOT, "profiles", "step_kernels_logn16_l30_hbm_counters.md")
     try:
         lines = open(prof).read().splitlines()
     except OSError:
@@ -298,7 +298,7 @@ def valu_fractions(probe):
             rate = waves * per / (us / 1e6)
             rows[name] = {"wave_instr_per_launch": waves * per, "avg_us": us,
                           "frac_of_issue_peak": round(rate / VALU_ISSUE_PEAK, 3)}
-    keep = ["k16_cols<0> 32768x3x1", "k16_ip_rows 16384x35x1", "k16_cols<1> 32768x2x2", "k_inv_row_tensor 8192x31x1",
+    keep = ["k16_cols<0> 32768x3x1", "k16_ip_rows<1> 16384x35x1", "k16_ip_rows<0> 16384x35x1", "k16_cols<1> 32768x2x2", "k_inv_row_tensor 8192x31x1",
             "k_fwd_row_moddown 8192x62x1", "k_inner_product 65536x35x1"]
     # the NTT passes appear under the tile width the autotuner chose (suffix _w8 or _w4 for 8 or 4)
     kernels = {}

@@ -1827,7 +1827,8 @@ __global__ __launch_bounds__(64 * kCols16Waves) void k16_cols(ColsArgs a)
 // accumulated (see IpArgs).
 enum IpMode { IP_MODDOWN, IP_TENSOR, IP_EXTENDED };
 // Four rows a workgroup read 128-byte runs of the tiles: 56 us at l = 30 with a
-// tensor (three digits, 35 rows; 250 MB, 50 us at the rate of a copy) where eight
+// tensor (three digits, 35 rows; 294 MB moved, 250 MB of them operands, at the
+// rate of a copy) where eight
 // rows take 58, two 60, sixteen 65, and the row pass and the inner product apart
 // 25 + 47.  A rotation's at l = 17 takes 24 us for 12 + 20.
 // Loading the next digit's row ahead of this one's rounds gains nothing (58.3 us
